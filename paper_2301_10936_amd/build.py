@@ -13,7 +13,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpit_hip.so")
 SOURCES = ["pit_api.hip", "pit_index.hip", "pit_gemm.hip", "pit_gemm_m.hip", "pit_moe.hip", "pit_attn.hip"]
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wno-inline-asm", "-Wno-pass-failed",
+# -amdgpu-mfma-vgpr-form: matrix results in vector registers (a kernel that loads its accumulators from LDS and writes them
+# back otherwise pays a register move per element each way: 212 of the 3000 instructions of k_slab_strip_tall)
+FLAGS = ["--offload-arch=gfx950", "-O3", "-mllvm", "-amdgpu-mfma-vgpr-form", "-std=c++17", "-fPIC", "-shared", "-Wno-inline-asm", "-Wno-pass-failed",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 

@@ -10,6 +10,7 @@
 //             Tiles of 128, 64 or 32 rows x 128 columns.
 //   k_slab_strip  GATHER_M with several k-slabs per row (1 x mt micro-tiles of a row-major A): a strip
 //             of C stays in LDS while the listed rows of every slab are added to it.
+//   k_slab_strip_tall  the same for products that fill the chip with strips of 64 or 128 rows.
 //   k_gather_m_lds (pit_gemm_m.hip)  GATHER_M with whole-row micro-tiles (padded batches, MoE): the
 //             tile's row numbers come from the index once, operands are staged through LDS.
 //
@@ -648,6 +649,298 @@ k_slab_strip(const GemmArgs g) {
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The same product with tall strips, for products large enough to give every compute unit one.
+//
+// k_slab_strip reads B once per 32 rows of C and multiplies blocks of 16 rows of which, at 10 % density, three are
+// real; its four waves each hold a strip, so strips cannot grow.  Here a workgroup owns R x 128 of C in LDS (fp32) and
+// a wavefront owns 64 of the columns for ALL slabs: rows are only ever touched by one wave (no atomics, no barrier
+// between slabs, a fixed order of additions), and the strip is R = 128 rows high: B is read a quarter as often and the
+// blocks of 16 rows are nearly full.  With SG = 2 (R = 64) two pairs of waves take every other slab into strips of
+// their own that are added at the end.  Rows that nothing touched are stored as zeros.
+//   list of a strip: lower bounds of its first row and of the row after it in every slab's ascending list,
+//   searched 8-ary with one slab per lane (64 slabs at once: two waves, four round trips to memory for
+//   lists of thousands); the rows are kept as bytes in LDS.
+//   A operand: 16 bytes (8 k) of a listed row per lane -- already the operand layout.
+//   B operand: 8 k-rows x 4 columns per lane (8-byte loads; 16 lanes side by side fill a 128-byte line of a
+//   k-row), transposed inside the lane: MFMA x of a block works on the columns {4 q + x}.
+//   strip in LDS: [wave][row][64 columns]; a lane moves its four columns of a row as 16 bytes and the 16 lanes
+//   of a row lie side by side (no bank conflicts).  A spare row swallows the results of a block's unused rows.
+// Bound by the vector-load path: per slab and strip 16 KB of B and 2 x 2 KB of A at 40 bytes per clock and CU are about
+// 500 clocks, the LDS read-modify-write of C 220, the issue of a wave's 170 instructions 700 (four waves per CU: the
+// strips fill the LDS); they overlap in part, about 850 are measured.  4096^3, 1 x 64 micro-tiles, 10 % kept: 231 ->
+// 108 us (50 %: 363 -> 285, 1 %: 112 -> 74; 1 x 32, 10 %: 339 -> 149; the launch without its slab loop: 18 us).
+// Tried: waves of 32 columns, eight per CU (twice the load instructions: 121 us), R = 256 with four waves per CU (114).
+// ------------------------------------------------------------------------------------------------
+constexpr int ST_W = 128;                            // columns of C per workgroup (2 waves x 64)
+constexpr int ST_BATCH = 64;                         // slabs whose row lists are in LDS together (one lane each)
+
+// KS = steps of 32 k taken per visit of a row (a slab's k extent is a multiple of 32 KS)
+template <bool BF, int KS, int R, int SG>
+__global__ void __launch_bounds__(128 * SG, 2)
+k_slab_strip_tall(const GemmArgs g) {
+  static_assert(R >= 32 && R <= 256 && R % 32 == 0, "rows of a strip are kept as bytes");
+  static_assert(SG == 1 || SG == 2, "groups of two waves");
+  constexpr int CW = 4, WC = 16 * CW;               // columns of a lane, of a wave
+  constexpr int GW = ST_W / WC;                     // waves of a group
+  constexpr int NW = GW * SG;
+  __shared__ __attribute__((aligned(16))) float s_c[NW][(R + 1) * WC];
+  __shared__ __attribute__((aligned(16))) uint8_t s_list[ST_BATCH][R];
+  __shared__ int s_bound[2][ST_BATCH];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wc = wv % GW, grp = wv / GW;
+  const int q = lane & 15, kb = lane >> 4;
+  int n0, r0;
+  {
+    // the 8 XCDs (own L2 each; consecutive workgroup ids go to different ones) form column groups x row groups
+    const int tn = g.N / ST_W, tm = (g.M + R - 1) / R;
+    const int xc = g.xcd_cols, xr = 8 / xc;
+    const int cols = (tn + xc - 1) / xc, rws = (tm + xr - 1) / xr;
+    const int x = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int c = (x % xc) * cols + slot % cols, r = (x / xc) * rws + slot / cols;
+    if (slot / cols >= rws || c >= tn || r >= tm) return;
+    n0 = c * ST_W; r0 = r * R;
+  }
+  const int rows = min(R, g.M - r0);
+  float* strip = s_c[wv];
+
+  const uint32_t pitch_a = (uint32_t)(g.lda * 2), pitch_b = (uint32_t)(g.ldb * 2);
+  const int cps = g.slab / (32 * KS);               // visits per slab
+  // Both operands come through buffer loads: the lane's 32-bit offset stays in one register, the k position is a scalar
+  // offset.  A lane of A without a listed row asks for an offset outside the buffer: it reads zero and moves nothing.
+  constexpr uint32_t NO_ROW = 0xf0000000u;          // (rows of a strip lie within 2^31 bytes)
+  const uint32_t b_lane = __umul24((uint32_t)(8 * kb), pitch_b) + (uint32_t)(n0 + WC * wc + CW * q) * 2u;
+  const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(uniform_ptr(g.B)), 0, 0xffffffffu, 0x00020000);
+  const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>(uniform_ptr(reinterpret_cast<const char*>(g.A) + (int64_t)r0 * g.lda * 2)), 0,
+      (uint32_t)(rows - 1) * pitch_a + (uint32_t)g.K * 2u, 0x00020000);
+
+  for (int s0 = 0; s0 < g.nseg; s0 += ST_BATCH) {
+    // ---- where the strip's rows lie in the lists of the batch's slabs: wave 0 looks for the first entry >= r0, wave
+    //      1 for the first entry >= r0 + R, one slab per lane.  Invariant: lo <= p* <= hi, entries before lo are below the
+    //      target, entries from hi on are not; a round leaves at most an eighth of a range.
+    if (s0 != 0) __syncthreads();                   // the previous batch's lists have been read
+    if (wv < 2) {
+      const int s = min(s0 + lane, g.nseg - 1);
+      const int target = wv == 0 ? r0 : r0 + R;
+      int lo = g.seg_ptr[s], hi = g.seg_ptr[s + 1];
+      while (__ballot(lo < hi) != 0ull) {
+        const int step = (hi - lo + 7) >> 3;
+        int v[7];
+#pragma unroll
+        for (int k = 0; k < 7; ++k) v[k] = g.idx[max(min(lo + (k + 1) * step, hi) - 1, 0)];
+        int below = 0;                              // probes below the target: a prefix of the valid ones
+#pragma unroll
+        for (int k = 0; k < 7; ++k) below += (lo + (k + 1) * step <= hi && v[k] < target) ? 1 : 0;
+        const int nhi = below < 7 ? lo + (below + 1) * step - 1 : hi;   // (there is no eighth probe)
+        lo += below * step;
+        hi = max(lo, min(hi, nhi));
+      }
+      s_bound[wv][lane] = lo;
+    }
+    // (the strip is private to its wave; cleared while the searches travel)
+    if (s0 == 0)
+      for (int i = lane * 4; i < (R + 1) * WC; i += 256) *reinterpret_cast<f32x4_t*>(strip + i) = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    __syncthreads();
+    // lane j: number of rows that slab j of the batch lists inside the strip
+    const int begv = s_bound[0][lane];
+    const int cntv = s0 + lane < g.nseg ? max(0, min(rows, s_bound[1][lane] - begv)) : 0;
+    // the rows themselves, as bytes: wave w fills the lists of slabs w, w + NW, ..., eight at a time
+#pragma unroll 1
+    for (int j0 = 0; j0 < ST_BATCH / NW; j0 += 8) {
+      int v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int slab = wv + NW * (j0 + j), beg = __builtin_amdgcn_readlane(begv, slab), n = __builtin_amdgcn_readlane(cntv, slab);
+        v[j] = g.idx[max(beg + min(lane, n - 1), 0)];
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int slab = wv + NW * (j0 + j), beg = __builtin_amdgcn_readlane(begv, slab), n = __builtin_amdgcn_readlane(cntv, slab);
+        // (clamped: an index that breaks its own rules must not lead outside the strip)
+        if (lane < n) s_list[slab][lane] = (uint8_t)max(0, min(v[j] - r0, rows - 1));
+        if constexpr (R > 64)
+          for (int i = lane + 64; i < n; i += 64) s_list[slab][i] = (uint8_t)max(0, min(g.idx[beg + i] - r0, rows - 1));
+      }
+    }
+    __syncthreads();
+    // slabs of this group with at least one listed row
+    unsigned long long live = __ballot(cntv > 0);
+    if constexpr (SG == 2) live &= 0x5555555555555555ull << grp;
+    if (live == 0ull) continue;
+
+    // ---- one visit = KS steps of 32 k of one live slab, all its listed rows.  The loads of the two visits after the one
+    //      being computed are in flight; they cover the first two blocks of 16 rows (further blocks load their A rows one
+    //      pair of blocks ahead).
+    struct Visit { int j, c, n; };                  // slab of the batch, k chunk of the slab, listed rows
+    struct Regs { u32x2_t b[8 * KS]; uint4 a[2][KS]; };
+    auto next = [&](const Visit& u) -> Visit {      // after the last visit the same one is named again: its loads are repeated and dropped
+      if (u.c + 1 < cps) return Visit{u.j, u.c + 1, u.n};
+      if (live == 0ull) return u;
+      const int j = __builtin_ctzll(live);
+      live &= live - 1ull;
+      return Visit{j, 0, __builtin_amdgcn_readlane(cntv, j)};
+    };
+    auto k_of = [&](const Visit& u) -> uint32_t { return (uint32_t)((s0 + u.j) * g.slab + u.c * (32 * KS)); };
+    // this lane's offset of A for block b
+    auto row_of = [&](const Visit& u, int b) -> uint32_t {
+      const int pos = 16 * b + q;
+      const uint32_t off = __umul24((uint32_t)s_list[u.j][min(pos, R - 1)], pitch_a) + 16u * (uint32_t)kb;
+      return off | (pos < u.n ? 0u : NO_ROW);
+    };
+    auto load_a = [&](uint32_t k, uint32_t off, uint4 (&a)[KS]) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        a[ks] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(a_rsrc, (int)off, (int)(2u * k + 64u * ks), 0));
+    };
+    // row i of the B rows of the visit that starts at k
+    auto load_b = [&](uint32_t kp, int i) -> u32x2_t {
+      const int so = (int)(kp + (uint32_t)(32 * (i >> 3) + (i & 7)) * pitch_b);
+      return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(b_rsrc, (int)b_lane, so, 0));
+    };
+    // addresses (in floats) of the rows of C that this lane holds of block b
+    auto c_at = [&](const Visit& u, int b, uint32_t rl, uint32_t (&at)[4]) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        at[e] = (16 * b + 4 * kb + e < u.n ? ((rl >> (8 * e)) & 255u) : (uint32_t)R) * (uint32_t)WC + (uint32_t)CW * (uint32_t)q;
+    };
+    auto rows4 = [&](const Visit& u, int b) -> uint32_t { return *reinterpret_cast<const uint32_t*>(&s_list[u.j][16 * b + 4 * kb]); };
+    auto c_read = [&](const uint32_t (&at)[4], f32x4_t (&acc)[CW]) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(strip + at[e]);
+#pragma unroll
+        for (int x = 0; x < CW; ++x) acc[x][e] = v[x];
+      }
+    };
+    auto c_write = [&](const uint32_t (&at)[4], const f32x4_t (&acc)[CW]) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        *reinterpret_cast<f32x4_t*>(strip + at[e]) = f32x4_t{acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
+      }
+    };
+    auto mfmas = [&](const uint4 (&a)[KS], const uint4 (&bop)[KS][CW], f32x4_t (&acc)[CW]) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int x = 0; x < CW; ++x) acc[x] = mfma16<BF>(a[ks], bop[ks][x], acc[x]);
+    };
+    auto block = [&](const Visit& u, int b, const uint4 (&a)[KS], const uint4 (&bop)[KS][CW]) {
+      uint32_t at[4];
+      f32x4_t acc[CW];
+      c_at(u, b, rows4(u, b), at);
+      c_read(at, acc);
+      mfmas(a, bop, acc);
+      c_write(at, acc);
+    };
+    // rl: the listed rows of block 0 (fetched during the previous visit); returns those of the next visit
+    auto visit = [&](const Visit& u, const Visit& following, const Visit& ahead, Regs& r, uint32_t rl) -> uint32_t {
+      const uint32_t off0 = row_of(ahead, 0), off1 = row_of(ahead, 1), rl_next = rows4(following, 0);
+      uint32_t at[4];
+      f32x4_t acc[CW];
+      c_at(u, 0, rl, at);
+      c_read(at, acc);
+      // (opaque: keeps the transposes behind the loads of the two visits ahead -- the compiler otherwise carries the
+      // transposed registers around the loop and waits for loads just issued)
+#pragma unroll
+      for (int i = 0; i < 8 * KS; i += 8)
+        asm volatile("" : "+v"(r.b[i]), "+v"(r.b[i + 1]), "+v"(r.b[i + 2]), "+v"(r.b[i + 3]), "+v"(r.b[i + 4]), "+v"(r.b[i + 5]), "+v"(r.b[i + 6]), "+v"(r.b[i + 7]));
+      // block 0, with the B rows of the visit after the next requested between the MFMAs, as soon as a step's registers
+      // are free: a wave that requests them all in a row stands still while the load path takes them
+      const uint32_t kp = k_of(ahead) * pitch_b;    // (K * ldb * 2 < 2^32: checked on the host)
+      uint4 bop[KS][CW];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+        for (int x = 0; x < CW; ++x) {
+          const uint32_t sel = (x & 1) ? 0x07060302u : 0x05040100u;
+          uint32_t d[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) d[i] = r.b[8 * ks + i][x >> 1];
+          bop[ks][x] = make_uint4(__builtin_amdgcn_perm(d[1], d[0], sel), __builtin_amdgcn_perm(d[3], d[2], sel),
+                                  __builtin_amdgcn_perm(d[5], d[4], sel), __builtin_amdgcn_perm(d[7], d[6], sel));
+        }
+        PIT_SCHED_FENCE();
+#pragma unroll
+        for (int x = 0; x < CW; ++x) {
+          acc[x] = mfma16<BF>(r.a[0][ks], bop[ks][x], acc[x]);
+#pragma unroll
+          for (int i = 0; i < 8 / CW; ++i) r.b[8 * ks + (8 / CW) * x + i] = load_b(kp, 8 * ks + (8 / CW) * x + i);
+          PIT_SCHED_FENCE();
+        }
+      }
+      load_a(k_of(ahead), off0, r.a[0]);
+      asm volatile("" ::: "memory");                // (the loads are not to be moved behind what follows)
+      PIT_SCHED_FENCE();
+      c_write(at, acc);
+      if (u.n > 16) {
+        block(u, 1, r.a[1], bop);
+        if constexpr (R > 32)
+          if (u.n > 32) {
+            uint4 ax[2][KS], ay[2][KS];
+            const uint32_t k = k_of(u);
+            load_a(k, row_of(u, 2), ax[0]); load_a(k, row_of(u, 3), ax[1]);
+            for (int b = 2; 16 * b < u.n; b += 4) {   // (two pairs per trip: no register copies)
+              load_a(k, row_of(u, b + 2), ay[0]); load_a(k, row_of(u, b + 3), ay[1]);
+              block(u, b, ax[0], bop);
+              if (u.n > 16 * (b + 1)) block(u, b + 1, ax[1], bop);
+              load_a(k, row_of(u, b + 4), ax[0]); load_a(k, row_of(u, b + 5), ax[1]);
+              if (u.n > 16 * (b + 2)) block(u, b + 2, ay[0], bop);
+              if (u.n > 16 * (b + 3)) block(u, b + 3, ay[1], bop);
+            }
+            // (no load of this branch may stay under way: the common path would have to wait for it, and with it for its
+            // own loads, wherever it reuses one of these registers)
+            __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
+          }
+      }
+      PIT_SCHED_FENCE();
+      if (ahead.n > 16) load_a(k_of(ahead), off1, r.a[1]);
+      asm volatile("" ::: "memory");
+      PIT_SCHED_FENCE();
+      return rl_next;
+    };
+    const int visits = __builtin_popcountll(live) * cps;
+    Visit u0 = next(Visit{0, cps, 0}), u1 = next(u0);
+    Regs ra, rb;
+    // (in the order in which they are awaited, and not to be mixed)
+    auto first = [&](const Visit& u, Regs& r) {
+      const uint32_t off0 = row_of(u, 0), off1 = row_of(u, 1), kp = k_of(u) * pitch_b;
+      PIT_SCHED_FENCE();
+#pragma unroll
+      for (int i = 0; i < 8 * KS; ++i) r.b[i] = load_b(kp, i);
+      load_a(k_of(u), off0, r.a[0]);
+      load_a(k_of(u), off1, r.a[1]);
+      asm volatile("" ::: "memory");
+      PIT_SCHED_FENCE();
+    };
+    first(u0, ra);
+    first(u1, rb);
+    uint32_t rl = rows4(u0, 0);
+    // (two visits per trip, no exit between them and no copy of one behind the loop -- an odd last visit gets a partner
+    // without rows: otherwise the compiler folds the bodies into one that copies registers with loads still under
+    // way, i.e. waits for everything)
+    for (int i = 0; i < visits; i += 2) {
+      const Visit u2 = next(u1);
+      rl = visit(u0, u1, u2, ra, rl);
+      const Visit u3 = next(u2);
+      if (i + 1 == visits) u1.n = 0;
+      rl = visit(u1, u2, u3, rb, rl);
+      u0 = u2; u1 = u3;
+    }
+  }
+  __syncthreads();
+  // SWrite: the groups' strips in a fixed order; consecutive lanes store the contiguous bytes of a row that a wave's columns make
+  for (int i = tid; i < R * 32; i += 64 * NW) {
+    const int row = i >> 5, w = (i & 31) / (WC / 4), c = (i % (WC / 4)) * 4;
+    if (row >= rows) break;
+    f32x4_t v = *reinterpret_cast<const f32x4_t*>(&s_c[w][row * WC + c]);
+#pragma unroll
+    for (int gi = 1; gi < SG; ++gi) v += *reinterpret_cast<const f32x4_t*>(&s_c[GW * gi + w][row * WC + c]);
+    *reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(g.C) + (int64_t)(r0 + row) * g.ldc + n0 + WC * w + c) = v;
+  }
+}
+
 __global__ void __launch_bounds__(256) k_zero_rows(void* C, int64_t ld_bytes, int M, int64_t row_bytes) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= M) return;
@@ -698,6 +991,37 @@ static int launch_sread_gemm_k(bool bf, int c_is_in_type, const GemmArgs& g, int
   if ((int64_t)g.K * g.lda * 2 >= (1ll << 32) || (int64_t)g.K * g.ldb * 2 >= (1ll << 32)) return PIT_ESHAPE;
   if (bf) return c_is_in_type ? launch_gather_k<true, 1>(g, tm_tiles, st) : launch_gather_k<true, 0>(g, tm_tiles, st);
   return c_is_in_type ? launch_gather_k<false, 1>(g, tm_tiles, st) : launch_gather_k<false, 0>(g, tm_tiles, st);
+}
+
+// k-slabs of a row-major A.  Tall strips where they fill the chip (two workgroups fit a compute unit), the 32-row kernel
+// for smaller products, whose time is the latency of one workgroup.  Measured (us; 32-row kernel / R = 64 / R = 128):
+//   128 x 128 tiles = 512: 52 / 35 / 30 and 47 / 43 / 41;  437: 129 / 74 / 52;  384: 81 / 70 / 91 (30 % kept), 56 / 45 / 39 (2 %)
+//   64 x 128 tiles = 512: 49 / 30 / 43, 31 / 30 / 32;  384: 31 / 36 / 56 -- but 42 / 29 / 42 with micro-tiles of 32 k, where the
+//   32-row kernel pays its read-modify-write twice as often;  256 of those: 47 / 39, 15.8 / 15.9;  128: 13.0 / 14.7
+template <bool BF, int R, int SG>
+static int launch_slab_tall(GemmArgs g, hipStream_t st) {
+  // XCDs as 2 row groups x 4 column groups (1, 2, 4 or 8 column groups measure within 4 %, 8 row groups 10 % slower)
+  g.xcd_cols = 4;
+  const int64_t cols = ceil_div(g.N / ST_W, 4), rws = ceil_div(ceil_div(g.M, R), 2);
+  dim3 grid((unsigned)(8 * cols * rws));
+  if (g.slab % 64 == 0) hipLaunchKernelGGL((k_slab_strip_tall<BF, 2, R, SG>), grid, dim3(128 * SG), 0, st, g);
+  else                  hipLaunchKernelGGL((k_slab_strip_tall<BF, 1, R, SG>), grid, dim3(128 * SG), 0, st, g);
+  PIT_LAUNCH_CHECK();
+  return PIT_OK;
+}
+template <bool BF>
+static int launch_slab_strip(const GemmArgs& g, hipStream_t st) {
+  const int64_t tn = g.N / ST_W, cus = compute_units();
+  const int64_t strips = ceil_div(g.M, StripShape<8>::R);
+  if (strips > 65535) return PIT_ESHAPE;
+  if (3 * ceil_div(g.M, 128) * tn >= 5 * cus) return launch_slab_tall<BF, 128, 1>(g, st);
+  if (ceil_div(g.M, 64) * tn >= (g.slab % 64 == 0 ? 2 : 1) * cus) return launch_slab_tall<BF, 64, 2>(g, st);
+  // 32 x 128 strips.  (64 x 64 strips, CW = 4, halve the traffic of B and double that of A: measured 10-15 %
+  // faster at 90-95 % sparsity of a 4096^3 product, 10-20 % slower at 50 % and at 99 %.)
+  constexpr int CW = 8;
+  hipLaunchKernelGGL((k_slab_strip<BF, CW>), dim3((unsigned)(g.N / StripShape<CW>::W), (unsigned)strips), dim3(256), 0, st, g);
+  PIT_LAUNCH_CHECK();
+  return PIT_OK;
 }
 
 int launch_zero_rows(void* C, int64_t ld_bytes, int M, int64_t row_bytes, hipStream_t st) {
@@ -770,16 +1094,7 @@ extern "C" int pit_sread_gemm(int mode, const void* d_A, int64_t lda, const void
   // several k-slabs per row: C-stationary strips (every element of C is written, nothing to clear)
   if (g.lda * 2 >= (1ll << 24) || g.ldb * 2 >= (1ll << 24) || (int64_t)M >= (1ll << 24) || (int64_t)K >= (1ll << 24)) return PIT_ESHAPE;
   if ((int64_t)M * g.lda * 2 >= (1ll << 32) || (int64_t)K * g.ldb * 2 >= (1ll << 32)) return PIT_ESHAPE;
-  // 32 x 128 strips.  (64 x 64 strips, CW = 4, halve the traffic of B and double that of A: measured 10-15 %
-  // faster at 90-95 % sparsity of a 4096^3 product, 10-20 % slower at 50 % and at 99 %.)
-  constexpr int CW = 8;
-  const int64_t strips = ceil_div(M, StripShape<CW>::R);
-  if (strips > 65535 || N % StripShape<CW>::W) return PIT_ESHAPE;
-  dim3 grid((unsigned)(N / StripShape<CW>::W), (unsigned)strips);
-  if (in_dt == PIT_BF16) hipLaunchKernelGGL((k_slab_strip<true, CW>), grid, dim3(256), 0, st, g);
-  else                   hipLaunchKernelGGL((k_slab_strip<false, CW>), grid, dim3(256), 0, st, g);
-  PIT_LAUNCH_CHECK();
-  return PIT_OK;
+  return in_dt == PIT_BF16 ? launch_slab_strip<true>(g, st) : launch_slab_strip<false>(g, st);
 }
 
 // ------------------------------------------------------------------------------------------------

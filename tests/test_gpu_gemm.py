@@ -339,6 +339,21 @@ def test_microtile_wider_slab(pit):
     assert np.array_equal(C.cpu().numpy().astype(np.float64), orc.gemm(w.A, w.B))
 
 
+# strips of 64 rows (one or two k-steps per visit) and of 128 rows: last strips of 32, 56, 72 and 1 rows, more than 64 slabs,
+# three visits per slab, lists of up to two blocks, of many blocks and of every row, both types
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("M,K,N,mt,p", [(2080, 96, 1024, 32, 0.5), (2040, 192, 2048, 64, 0.1), (3400, 2112, 2048, 32, 0.02),
+                                        (3400, 288, 2048, 96, 0.2), (3457, 256, 2048, 128, 1.0)])
+def test_microtile_tall_strips(pit, M, K, N, mt, p, dtype):
+    w = wl.microtile_gemm(M=M, K=K, N=N, mt_k=mt, p_keep=p, seed=M + mt, integer=True)
+    ref = orc.gemm(w.A, w.B)
+    A, B = (to_dev(x).to(torch.bfloat16 if dtype == "bf16" else torch.float16) for x in (w.A, w.B))
+    C = torch.full((M, N), 3.0, device=dev())
+    ix = pit.pit_build_index(A, 1, mt, 0)
+    pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, A, B, ix, mt, M, N, K, out=C)
+    assert np.array_equal(C.cpu().numpy().astype(np.float64), ref)
+
+
 def test_c1_full_size(pit):
     w = wl.microtile_gemm()
     C = _run_microtile(pit, w)
