@@ -7,7 +7,7 @@
 //             names the rows of At and of B to multiply.  Operands go global -> registers directly
 //             and are transposed inside each lane; the waves of a workgroup split the k-list and
 //             reduce their partial tiles through LDS at the end (details above the kernel).
-//             Tiles of 128, 64 or 32 rows x 128 columns.
+//             Tiles of 128, 64 or 32 rows x 128 columns (at most the height of the micro-tile).
 //   k_slab_strip  GATHER_M with several k-slabs per row (1 x mt micro-tiles of a row-major A): a strip
 //             of C stays in LDS while the listed rows of every slab are added to it.
 //   k_slab_strip_tall  the same for products that fill the chip with strips of 64 or 128 rows.
@@ -145,29 +145,73 @@ __device__ __forceinline__ void red_store(const f32x4_t (&acc)[JA][8], const Gem
   }
 }
 
+// Four waves on a low tile: vector ((ja * 4 + e) * 2 + h) of a wave's slot = columns 4 h .. 4 h + 3 of the
+// rows JA * (4 * (lane / 16) + e) + ja.
+template <int JA>
+__device__ __forceinline__ void red_send_all(const f32x4_t (&acc)[JA][8], PIT_LDS char* slot) {
+#pragma unroll
+  for (int ja = 0; ja < JA; ++ja)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        *(PIT_LDS f32x4_t*)(slot + ((ja * 4 + e) * 2 + h) * 1024) = f32x4_t{acc[ja][4 * h][e], acc[ja][4 * h + 1][e], acc[ja][4 * h + 2][e], acc[ja][4 * h + 3][e]};
+}
+template <bool BF, int CT, int NW, int JA>
+__device__ __forceinline__ void red_sum_store(PIT_LDS char* red, const GemmArgs& g, int m_base, int n0, int wv, int lane) {
+  constexpr int U = 4 * JA / NW;                    // row sets (ja, e) of a wave
+  const int q = lane & 15, kb = lane >> 4;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int unit = wv * U + u;
+    f32x4_t part[NW][2];
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) part[w][h] = *(PIT_LDS f32x4_t*)(red + w * (JA * 8 * 1024) + (unit * 2 + h) * 1024);
+    f32x4_t s[2] = {part[0][0], part[0][1]};
+#pragma unroll
+    for (int w = 1; w < NW; ++w) { s[0] += part[w][0]; s[1] += part[w][1]; }
+    const int64_t row = m_base + JA * (4 * kb + (unit & 3)) + (unit >> 2);
+    const int col = n0 + 8 * q;
+    if constexpr (CT == 0) {
+      f32x4_t* d = reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(g.C) + row * g.ldc + col);
+      __builtin_nontemporal_store(s[0], d);
+      __builtin_nontemporal_store(s[1], d + 1);
+    } else {
+      __builtin_nontemporal_store(u32x4_t{pack2_in<BF>(s[0][0], s[0][1]), pack2_in<BF>(s[0][2], s[0][3]), pack2_in<BF>(s[1][0], s[1][1]), pack2_in<BF>(s[1][2], s[1][3])},
+                                  reinterpret_cast<u32x4_t*>(reinterpret_cast<uint16_t*>(g.C) + row * g.ldc + col));
+    }
+  }
+}
+
 // what a wave needs to know about one tile
 struct DirectTile {
-  int seg, n0, list_len, n_w;      // tile row (= index segment), first column, length of the k-list, this wave's slabs
+  int row, n0, list_len, n_w;      // tile row, first column, length of the k-list, this wave's slabs
   const char* list;                // the k-list
   uint32_t a_col, b_col;           // this lane's byte offsets into a row of At and of B
 };
 
-// NW = waves per workgroup that split the k-list: 4 (one workgroup fills a compute unit) or 2 (two
+// NW = waves per workgroup that split the k-list: 4 (one 128-row tile fills a compute unit), 2 (two
 // workgroups, i.e. two tiles, share a compute unit at the same register cost, and the set-up, drain,
-// reduction and stores of one tile run under the MFMA loop of the other; used when there are at
-// least two tiles per compute unit).
-// JA = row groups of the tile: the tile is 16 * JA rows high (128, 64 or 32 = the micro-tile height of the
-// index), a lane loads JA consecutive m of each listed row of At (16, 8 or 4 bytes) and a slab takes JA x 8
-// MFMAs.  Lower tiles follow a finer sparsity pattern (fewer all-zero micro-tiles are multiplied) and pay for
-// it with more traffic of B per row of C; they always run as two-wave workgroups, several per compute unit.
+// reduction and stores of one tile run under the MFMA loop of the other) or 1 (no reduction at all).
+// JA = row groups of the tile: the tile is 16 * JA rows high (128, 64 or 32), a lane loads JA consecutive m of
+// each listed row of At (16, 8 or 4 bytes) and a slab takes JA x 8 MFMAs.  Lower tiles follow a finer sparsity
+// pattern (the micro-tile height of the index; fewer all-zero micro-tiles are multiplied) or spread a small
+// product over more compute units, and pay for it with more traffic of B per row of C.  The rule that chooses is at
+// launch_gather_k.
 template <bool BF, int CT, int NW, int JA>
-__global__ void __launch_bounds__(64 * NW)
+__global__ void __launch_bounds__(64 * NW, JA == 2 ? 2 : 1)
 k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
-  static_assert(JA == 8 || (NW == 2 && (JA == 4 || JA == 2)), "tile heights: 128 (2 or 4 waves), 64 and 32 (2 waves)");
+  static_assert((JA == 8 && (NW == 2 || NW == 4)) || (JA == 4 && (NW == 1 || NW == 2 || NW == 4)) ||
+                (JA == 2 && (NW == 1 || NW == 2 || NW == 4)), "tile heights and waves");
   constexpr int SK = 32;   // list entries per slab = k extent of one MFMA
   constexpr int TMJ = 16 * JA;   // tile rows
   constexpr int RED_HALF_BYTES = red_half_bytes<JA>();
-  __shared__ __attribute__((aligned(16))) char s_red[NW == 4 ? 2 * RED_BUF_BYTES : 2 * RED_HALF_BYTES];
+  constexpr int RED_ALL_BYTES = 2 * RED_HALF_BYTES;   // one wave's whole partial tile
+  constexpr bool RED_QUARTERS = NW == 4 && JA == 8;
+  __shared__ __attribute__((aligned(16)))
+  char s_red[NW == 1 ? 16 : RED_QUARTERS ? 2 * RED_BUF_BYTES : NW == 2 ? 2 * RED_HALF_BYTES : NW * RED_ALL_BYTES];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -186,24 +230,29 @@ k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
   // 4 tile rows x all columns fetch (almost) the union of 4 lists of B over all columns instead, and that traffic, not
   // the MFMAs, bounded sparse products (4096^3, live in runs of 32 tokens with probability 0.1: 32-row tiles 79.8 us
   // there, 48.5 here; 64 rows 69.2, 53.6; 128 rows 61.6, 55.4; full lists: the same).  Bands of 2 columns are 5 % better
-  // for 32-row tiles at that density and 7 % worse at 50 %, bands of 8 columns 17 % and 6 % worse.
+  // for 32-row tiles at that density and 7 % worse at 50 %, bands of 8 columns 17 % and 6 % worse;
+  // where tiles are few along m (8 x 32 tiles, 1024 x 16384 x 4096 half listed) rows are better by 1 %.
   const bool dense = g.idx == nullptr;
+  const bool wide = tn > 2 * tm_tiles;
+  const int sub = g.slab / TMJ;       // tiles that share one list (the tile may be lower than the micro-tile)
   auto tile_of = [&](int lin) -> DirectTile {
     const int x = lin & 7, qq = total >> 3, rr = total & 7;
     const int lp = x * qq + min(x, rr) + (lin >> 3);
-    constexpr int GN = 4;
-    const int band = lp / (GN * tm_tiles), within = lp - band * (GN * tm_tiles);
-    const int cols = min(GN, tn - band * GN);
     DirectTile t;
-    t.seg = within / cols;
-    t.n0 = (band * GN + within % cols) * TN;
+    constexpr int G = 4;
+    const int across = wide ? tn : tm_tiles, along = wide ? tm_tiles : tn;   // a band: G of `along` x all of `across`
+    const int band = lp / (G * across), within = lp - band * (G * across), n = min(G, along - band * G);
+    const int thin = band * G + within % n, len = within / n;
+    t.row = wide ? thin : len;
+    t.n0 = (wide ? len : thin) * TN;
     // dense mode (no index): every tile's list is 0, 1, .., K - 1 and is never read from memory
-    const int list_begin = dense ? 0 : g.seg_ptr[t.seg];
-    t.list_len = dense ? g.K : g.seg_ptr[t.seg + 1] - list_begin;
+    const int seg = t.row / sub;
+    const int list_begin = dense ? 0 : g.seg_ptr[seg];
+    t.list_len = dense ? g.K : g.seg_ptr[seg + 1] - list_begin;
     const int nslab = (t.list_len + SK - 1) / SK;
     t.n_w = nslab > wv ? (nslab - wv + NW - 1) / NW : 0;   // this wave's slabs: wv, wv + NW, ...
     t.list = uniform_ptr(g.idx + list_begin);
-    t.a_col = (uint32_t)(t.seg * TMJ + JA * q) * 2u;
+    t.a_col = (uint32_t)(t.row * TMJ + JA * q) * 2u;
     t.b_col = (uint32_t)(t.n0 + 8 * q) * 2u;
     return t;
   };
@@ -341,8 +390,17 @@ k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
     }
     PIT_SCHED_FENCE();
 
-    const int m_base = T.seg * TMJ;
-    if constexpr (NW == 4) {
+    const int m_base = T.row * TMJ;
+    if constexpr (NW == 1) {
+      red_store<BF, CT, JA, 0, JA>(acc, g, m_base, T.n0, lane);
+    } else if constexpr (!RED_QUARTERS && NW > 2) {
+      // Every wave leaves its whole partial tile in LDS as the vectors of four columns that are stored later; each then
+      // adds up, in the order of the waves, and stores an NW-th of the tile.
+      __syncthreads();
+      red_send_all<JA>(acc, red + wv * RED_ALL_BYTES + lane * 16);
+      __syncthreads();
+      red_sum_store<BF, CT, NW, JA>(red + lane * 16, g, m_base, T.n0, wv, lane);
+    } else if constexpr (NW == 4) {
       // Reduction across the four waves, one quarter of the tile rows per round, double-buffered in
       // LDS: round P's partial sums are written before barrier P and read by wave P after it, while the
       // other waves already write round P + 1 into the other buffer.
@@ -966,25 +1024,37 @@ static int compute_units() {
   return n & ~7;
 }
 
-template <bool BF, int CT>
-static int launch_gather_k(const GemmArgs& g, int tm_tiles, hipStream_t st) {
-  // one workgroup of the 128-row tile fits on a compute unit: with more tiles than compute units the workgroups loop
-  const int total = (int)(g.N / TN) * tm_tiles, cus = compute_units();
-  if (g.slab == 64 || g.slab == 32) {
-    // lower tiles: two-wave workgroups; as many as the registers let a compute unit hold (64 rows: two,
-    // 32 rows: four, i.e. two waves per SIMD)
-    const int resident = (g.slab == 64 ? 2 : 4) * cus;
-    const unsigned wgs = (unsigned)(total <= resident ? total : resident);
-    if (g.slab == 64) hipLaunchKernelGGL((k_gather_k_direct<BF, CT, 2, 4>), dim3(wgs), dim3(128), 0, st, g, tm_tiles);
-    else              hipLaunchKernelGGL((k_gather_k_direct<BF, CT, 2, 2>), dim3(wgs), dim3(128), 0, st, g, tm_tiles);
-  } else if (total >= 2 * cus) {      // two workgroups of two waves per compute unit
-    hipLaunchKernelGGL((k_gather_k_direct<BF, CT, 2, 8>), dim3((unsigned)(2 * cus)), dim3(128), 0, st, g, tm_tiles);
-  } else {
-    const unsigned wgs = (unsigned)(total <= cus ? total : cus);
-    hipLaunchKernelGGL((k_gather_k_direct<BF, CT, 4, 8>), dim3(wgs), dim3(256), 0, st, g, tm_tiles);
-  }
+template <bool BF, int CT, int NW, int JA>
+static int launch_gather_k_tile(const GemmArgs& g, int resident, hipStream_t st) {
+  const int64_t tm = g.M / (16 * JA), total = tm * (g.N / TN);
+  // with more tiles than `resident` per compute unit the workgroups loop
+  const unsigned wgs = (unsigned)std::min<int64_t>(total, (int64_t)resident * compute_units());
+  hipLaunchKernelGGL((k_gather_k_direct<BF, CT, NW, JA>), dim3(wgs), dim3(64 * NW), 0, st, g, (int)tm);
   PIT_LAUNCH_CHECK();
   return PIT_OK;
+}
+
+// Tile height and waves per tile by the number of tiles the product has at each height (128 columns wide; cus compute
+// units).  A tile may be lower than the micro-tile: the tiles of a micro-tile row share its list.
+//   32-row tiles <= cus: those, four waves each.  The taller tile leaves compute units idle, or alone with the latency of
+//     one long tile: 128 rows and four waves / 32 rows and four waves, full lists, us: 256 x 512 x 256 10.8 / 7.2,
+//     512 x 4096 x 512 31.6 / 21.8, 1024 x 2048 x 1024 19.2 / 12.4, 1024 x 8192 x 1024 49.8 / 35.4; lists of micro-tiles
+//     of 64 or 32 rows, two waves before: 32.4 / 22.2 and 31.6 / 22.0 at 512 x 4096 x 512.
+//   64-row tiles <= cus: those, four waves each: 2048 x 2048 x 1024 19.4 / 14.8 (at 512 tiles of 64 rows, 2048 x 4096 x
+//     2048, 128-row tiles are better: 32.6 / 43.6).
+//   otherwise the micro-tile's own height.  128 rows: four waves up to two tiles per compute unit, two beyond.  Lower
+//     tiles: two waves, and from eight tiles per compute unit on one wave, without a reduction (4096^3, two waves / one:
+//     32 rows at 10 % 48.5 / 47.3, at 50 % 171 / 147; 64 rows at 10 % 53.6 / 49.5, at 50 % 88.6 / 89.0; with four tiles
+//     per compute unit and lists of 200 entries, 32 rows, 10.1 / 11.2).
+template <bool BF, int CT>
+static int launch_gather_k(const GemmArgs& g, int tm_tiles, hipStream_t st) {
+  const int64_t cus = compute_units(), tn = g.N / TN;
+  if (g.M / 32 * tn <= cus) return launch_gather_k_tile<BF, CT, 4, 2>(g, 2, st);
+  if (g.slab >= 64 && g.M / 64 * tn <= cus) return launch_gather_k_tile<BF, CT, 4, 4>(g, 1, st);
+  const int64_t total = tm_tiles * tn;
+  if (g.slab == 32) return total >= 8 * cus ? launch_gather_k_tile<BF, CT, 1, 2>(g, 8, st) : launch_gather_k_tile<BF, CT, 2, 2>(g, 4, st);
+  if (g.slab == 64) return total >= 8 * cus ? launch_gather_k_tile<BF, CT, 1, 4>(g, 4, st) : launch_gather_k_tile<BF, CT, 2, 4>(g, 2, st);
+  return total >= 2 * cus ? launch_gather_k_tile<BF, CT, 2, 8>(g, 2, st) : launch_gather_k_tile<BF, CT, 4, 8>(g, 1, st);
 }
 
 // GATHER_K: tm_tiles = number of row tiles = segments of the index
@@ -1075,7 +1145,7 @@ extern "C" int pit_sread_gemm(int mode, const void* d_A, int64_t lda, const void
     if ((mt != 128 && mt != 64 && mt != 32) || M % mt) return PIT_ESHAPE;
     if (ix->nseg != M / mt) return PIT_ECAPACITY;
     if (K > 0 && lda < M) return PIT_EINVAL;
-    g.slab = mt;       // GATHER_K: the tile height (= micro-tile height of the index)
+    g.slab = mt;       // GATHER_K: the micro-tile height of the index
     return launch_sread_gemm_k(in_dt == PIT_BF16, c_dt != PIT_F32, g, ix->nseg, st);
   }
 

@@ -162,6 +162,13 @@ def test_gather_k_more_tiles_than_compute_units(pit, tiles_m, tiles_n, mt):
     assert np.array_equal(C.cpu().numpy().astype(np.float64), orc.gemm_at(xb, wb))
 
 
+@pytest.mark.parametrize("tiles_m,tiles_n,mt", [(2, 32, 128), (2, 32, 32), (12, 10, 128), (12, 10, 64), (33, 16, 32), (66, 16, 64)])
+def test_gather_k_tile_heights_and_waves(pit, tiles_m, tiles_n, mt):
+    """Tiles lower than the micro-tile (32 and 64 rows under lists of 128 and 64, four waves each; one tile per compute
+    unit at most) and one wave per tile (eight tiles per compute unit and more).  Bit for bit on integers."""
+    test_gather_k_more_tiles_than_compute_units(pit, tiles_m, tiles_n, mt)
+
+
 @pytest.mark.parametrize("mt", MTS)
 def test_gather_k_strided_operands_and_large_last_row(pit, mt):
     """Row pitches larger than the row length (views into wider buffers); the last listed row holds
