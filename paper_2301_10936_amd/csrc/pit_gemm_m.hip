@@ -31,6 +31,7 @@
 // the row the index names (or to compact rows), optionally GELU + rounding to the input type.
 #include "pit_gemm.hpp"
 #include "pit_gemm_dev.hpp"
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
@@ -457,6 +458,188 @@ k_gather_m_lds(const GemmArgs g) {
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Segments of few rows with a B of their own (a decode step of a mixture of experts: a handful of tokens, most experts
+// with one or two of them).
+//
+// k_gather_m_lds gives such a segment 128 x 256 or 128 x 128 tiles: 12 or 6 workgroups per expert, each walking all of
+// k behind a barrier per 32 -- latency from end to end.  The bound is the memory's rate for the listed experts' weights,
+// so here a workgroup takes 64 columns of one expert and its eight waves split k (slabs of 32, wave w takes w, w + 8,
+// ..), each with four slabs of B on their way in registers: 256 KB in flight per compute unit.  A tile is 16 rows;
+// an expert with more reads its weights again, mostly from L2.
+//   B operand: 8 k-rows x 4 columns per lane (16 lanes side by side fill a 128-byte line), transposed inside the lane.
+//   A operand: 16 bytes (8 k) of a listed row per lane -- already the operand layout.
+//   The waves' partial tiles meet in LDS and are added in the order of the waves.
+// Whole mixture-of-experts calls, k_gather_m_lds / this, us (tokens, d_model x d_ff, experts):
+//   1 and 48, 768 x 3072, 64: 45 / 17.6 and 62.8 / 50.9 (200 MB of weights: 4.6 TB/s);  128 and 512: 76.5 / 74.6,
+//   135 / 127;  16, 1024 x 2048, 128: 58 / 31;  64, 512 x 2048, 8: 32 / 20.  Hence up to eight rows per segment on
+//   average.  Not with more than 64 segments (256, 1024 x 2048, 128: 127.6 / 130.5), unless there are as many
+//   segments as rows; and 2048 tokens on 64 experts take 154 / 219.
+// Tried: 32 rows per tile with three or four slabs in flight: 57 at 48 tokens; 128 columns, 16-byte loads: 55 - 68.
+// ------------------------------------------------------------------------------------------------
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+template <bool BF>
+__device__ __forceinline__ f32x4_t mfma16x16(const u32x4_t& a, const u32x4_t& b, const f32x4_t& c) {
+  if constexpr (BF)
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
+}
+
+template <bool BF, int EPI, int CT>
+__global__ void __launch_bounds__(512, 4)
+k_gather_m_few(const GemmArgs g) {
+  constexpr int CW = 4, NB = 1, DEPTH = 4;               // columns of a lane, blocks of 16 rows, slabs in flight
+  constexpr int WC = 16 * CW, NW = 8, R = 16 * NB, KS = 32;
+  constexpr int H = CW / 4, VEC = NB * 4 * H;          // 16-byte vectors of a lane's share of a partial tile
+  __shared__ __attribute__((aligned(16))) char s_red[NW * VEC * 1024];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane & 15, kb = lane >> 4;
+
+  // the tile: row tile blockIdx.y of all segments' row tiles (the grid holds the worst case), columns n0 ..
+  int seg = -1, begin = 0, cnt = 0, base = 0;
+  const int tile = blockIdx.y;
+  for (int s0 = 0; s0 < g.nseg; s0 += 64) {
+    const int s = s0 + lane;
+    int beg = 0, c = 0;
+    if (s < g.nseg) { beg = g.seg_ptr[s]; c = g.seg_ptr[s + 1] - beg; }
+    const int nt = (c + R - 1) / R;
+    int inc = nt;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int t = __shfl_up(inc, d);
+      if (lane >= d) inc += t;
+    }
+    const unsigned long long hit = __ballot(base + inc > tile);
+    if (hit != 0ull) {
+      const int l = __builtin_ctzll(hit);
+      const int in_seg = tile - (base + __shfl(inc, l) - __shfl(nt, l));
+      seg = s0 + l;
+      begin = __shfl(beg, l) + in_seg * R;
+      cnt = min(R, __shfl(c, l) - in_seg * R);
+      break;
+    }
+    base += __shfl(inc, 63);
+  }
+  if (seg < 0) return;                                  // (uniform over the workgroup)
+  seg = __builtin_amdgcn_readfirstlane(seg);
+  begin = __builtin_amdgcn_readfirstlane(begin);
+  cnt = __builtin_amdgcn_readfirstlane(cnt);
+
+  const int n0 = blockIdx.x * WC;
+  const char* a_src = uniform_ptr(g.A);
+  const char* b_src = uniform_ptr(reinterpret_cast<const char*>(g.B) + (int64_t)seg * g.b_seg_stride * 2);
+  const uint32_t pitch_a = (uint32_t)(g.lda * 2), pitch_b = (uint32_t)(g.ldb * 2);
+  const int nslab = g.slab / KS;
+  const int n_w = nslab > wv ? (nslab - wv + NW - 1) / NW : 0;   // this wave's slabs: wv, wv + NW, ...
+
+  f32x4_t acc[NB][CW];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int x = 0; x < CW; ++x) acc[b][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  if (n_w > 0) {
+    uint32_t b_off[8], a_off[NB];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b_off[i] = __umul24((uint32_t)(8 * kb + i), pitch_b) + (uint32_t)(n0 + CW * q) * 2u;
+    ACols<CW> rb[DEPTH][8];
+    uint4 ra[DEPTH][NB];
+    // (slabs past this wave's last: the last once more, never multiplied)
+    auto load_b = [&](int t, int u) {
+      const uint32_t k = (uint32_t)(KS * (wv + NW * min(t, n_w - 1)));
+      const char* p = b_src + (uint64_t)k * pitch_b;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) rb[u][i] = load_cols<CW>(p, b_off[i]);
+    };
+    auto load_a = [&](int t, int u) {
+      const char* p = a_src + 2u * (uint32_t)(KS * (wv + NW * min(t, n_w - 1)));
+#pragma unroll
+      for (int b = 0; b < NB; ++b) ra[u][b] = load16(p, a_off[b]);
+    };
+    auto process = [&](int u) {
+#pragma unroll
+      for (int x = 0; x < CW; ++x) {
+        u32x4_t bop;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) bop[jj] = transpose_cols_dword<CW>(rb[u], x, jj);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b][x] = mfma16x16<BF>(__builtin_bit_cast(u32x4_t, ra[u][b]), bop, acc[b][x]);
+      }
+    };
+    // the weights do not depend on the row numbers: they are requested first
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) load_b(u, u);
+    PIT_SCHED_FENCE();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int p = begin + min(16 * b + q, cnt - 1);   // rows past the end: the last listed row, never stored
+      a_off[b] = __umul24((uint32_t)(g.a_gather ? g.idx[p] : p), pitch_a) + 16u * (uint32_t)kb;
+    }
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) load_a(u, u);
+    PIT_SCHED_FENCE();
+    int t = 0;
+    for (; t + DEPTH < n_w; t += DEPTH) {
+#pragma unroll
+      for (int u = 0; u < DEPTH; ++u) {
+        process(u);
+        PIT_SCHED_FENCE();
+        load_a(t + u + DEPTH, u);
+        load_b(t + u + DEPTH, u);
+        PIT_SCHED_FENCE();
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u)
+      if (t + u < n_w) process(u);
+  }
+
+  // vector (b * 4 + e) * H + h of a wave's slot = columns CW q + 4 h .. + 3 of row 16 b + 4 kb + e
+  PIT_LDS char* red = (PIT_LDS char*)s_red + lane * 16;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+        *(PIT_LDS f32x4_t*)(red + (wv * VEC + (b * 4 + e) * H + h) * 1024) =
+            f32x4_t{acc[b][4 * h][e], acc[b][4 * h + 1][e], acc[b][4 * h + 2][e], acc[b][4 * h + 3][e]};
+  __syncthreads();
+#pragma unroll
+  for (int v = wv; v < VEC; v += NW) {                   // wave w adds up and stores the vectors w, w + NW, ..
+    const int unit = v / H, h = v % H;
+    const int row = 16 * (unit >> 2) + 4 * kb + (unit & 3);
+    const bool live = row < cnt;
+    const int crow = live ? (g.c_scatter ? g.idx[begin + row] : begin + row) : 0;
+    float scale = 1.f;
+    if constexpr (EPI == EPI_STORE) { if (g.gate && live) scale = g.gate[crow]; }
+    f32x4_t s = *(PIT_LDS f32x4_t*)(red + v * 1024);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += *(PIT_LDS f32x4_t*)(red + (w * VEC + v) * 1024);
+    if (!live) continue;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      if constexpr (EPI == EPI_GELU) s[x] = gelu_erf_fast(s[x]);
+      if constexpr (EPI == EPI_STORE) s[x] *= scale;
+    }
+    const int64_t at = (int64_t)crow * g.ldc + n0 + CW * q + 4 * h;
+    if constexpr (CT == 0) *reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(g.C) + at) = s;
+    else *reinterpret_cast<u32x2_t*>(reinterpret_cast<uint16_t*>(g.C) + at) = u32x2_t{pack2_in<BF>(s[0], s[1]), pack2_in<BF>(s[2], s[3])};
+  }
+}
+
+template <bool BF, int EPI, int CT>
+int launch_few(const GemmArgs& g, int64_t total_rows, hipStream_t st) {
+  // sum over segments of ceil(count / 16): at most one tile per row, and one partly filled tile per segment
+  const int64_t tiles = std::min<int64_t>(total_rows, total_rows / 16 + g.nseg);
+  if (tiles > 65535) return PIT_ESHAPE;
+  hipLaunchKernelGGL((k_gather_m_few<BF, EPI, CT>), dim3((unsigned)(g.N / 64), (unsigned)tiles), dim3(512), 0, st, g);
+  PIT_LAUNCH_CHECK();
+  return PIT_OK;
+}
+
 template <bool BF, int EPI, int CT, int WM, int WN, int NST, int GN = 2>
 int launch_cfg(GemmArgs g, int64_t total_rows, hipStream_t st) {
   using T = MTile<WM, WN, NST, GN>;
@@ -489,6 +672,9 @@ int launch_shape(const GemmArgs& g, int64_t total_rows, hipStream_t st) {
   // (a product too small to give every compute unit a 128 x 256 tile even in the worst case takes 128 x 128)
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
+  // few rows per segment, a B of its own each: k_gather_m_few (the rule and its measurements are above that kernel)
+  if (g.b_seg_stride != 0 && (total_rows <= g.nseg || (total_rows <= 8 * (int64_t)g.nseg && g.nseg <= 64)))
+    return launch_few<BF, EPI, CT>(g, total_rows, st);
   const int64_t wide_tiles = (total_rows / 128 + g.nseg) * (g.N / 256);
   if (g.N % 256 == 0 && wide_tiles >= cus) return launch_cfg<BF, EPI, CT, 2, 4, 3>(g, total_rows, st);
   return launch_cfg<BF, EPI, CT, 2, 2, 4>(g, total_rows, st);

@@ -42,6 +42,21 @@ def test_exact_on_integers_identity_activation(pit, T, d_model, d_ff, E):
     assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref)
 
 
+@pytest.mark.parametrize("T,d_model,d_ff,E", [(1, 128, 128, 64), (17, 128, 256, 3), (48, 768, 384, 64), (130, 256, 1152, 20),
+                                              (100, 640, 256, 128)])
+@pytest.mark.parametrize("y_dtype", [torch.float32, torch.bfloat16])
+def test_few_rows_per_expert(pit, T, d_model, d_ff, E, y_dtype):
+    """At most eight rows per expert on average: waves without a slab of k, with one, with more than are in flight; experts
+    without a row, with one, with more than a tile of 16.  Exact on integers (bf16: the rounded exact sum)."""
+    w = wl.moe_ffn(T=T, d_model=d_model, d_ff=d_ff, E=E, seed=T, integer=True, unit_gate=True)
+    Y, st = _run(pit, w, act=1, gate=False, y_dtype=y_dtype, sentinel=99.0)
+    ref = orc.moe_ffn(w.X, w.expert_id, None, w.W1, w.W2, activation="identity")
+    assert st == 0
+    if y_dtype == torch.bfloat16:      # one rounding of an exact sum
+        ref = torch.from_numpy(ref).float().to(torch.bfloat16).double().numpy()
+    assert np.array_equal(Y.double().cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("T,E", [(512, 8), (777, 3)])
 def test_gelu_and_gate(pit, T, E):
     w = wl.moe_ffn(T=T, d_model=256, d_ff=512, E=E, seed=E)
