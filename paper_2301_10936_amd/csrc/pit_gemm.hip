@@ -65,6 +65,13 @@ __device__ __forceinline__ void mfma16_acc(const uint4& a, const uint4& b, f32x4
 constexpr int RED_SLOT_BYTES = 16 * 64 * 16;        // 16 accumulator quads x 64 lanes x 16 B
 constexpr int RED_BUF_BYTES = 4 * RED_SLOT_BYTES;   // one slot per sending wave
 
+// LDS accesses of the wave's lanes before this point are done before those after it (the hardware keeps a wave's LDS
+// accesses in order; this keeps the compiler from exchanging accesses of different lanes that no single lane sees meet)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Round P of the reduction: the partial sums of tile rows {8r + ja : ja in {2P, 2P + 1}} go to wave
 // P.  P is a compile-time constant so that every accumulator index is static.
 template <int P>
@@ -115,9 +122,16 @@ __device__ __forceinline__ void red_recv_half(f32x4_t (&acc)[JA][8], PIT_LDS cha
   }
 }
 // Store the row groups ja in [J0, J0 + NJ) of the tile: rows JA * (4 * (lane / 16) + e) + ja; a lane holds 8
-// consecutive columns of such a row (one per jb), so 16 lanes write 512 (fp32) or 256 contiguous bytes.
-template <bool BF, int CT, int JA, int J0, int NJ>
-__device__ __forceinline__ void red_store(const f32x4_t (&acc)[JA][8], const GemmArgs& g, int m_base, int n0, int lane) {
+// consecutive columns of such a row (one per jb): 16 lanes write 256 contiguous bytes of 16-bit results.  Of fp32
+// results a lane's 32 bytes are two stores, i.e. two instructions that each leave every second 16 bytes of a row to
+// the other.  Where workgroups store tile after tile (at most two waves per tile) these half-filled lines are what the
+// memory sees, so there the rows go through 4 KiB of LDS of the wave (STAGED) and an instruction stores two whole rows:
+// 4096^3, live in runs of 32 at 10 %: 128-row tiles 55.5 -> 47.7 us, 64 rows 49.4 -> 39.9, 32 rows 47.5 -> 42.5 (without
+// any store 41, 34, 37); 2944 x 3001 x 3072, full lists, 79.4 -> 75.4.  With four waves per tile, one or two tiles per
+// compute unit, the way through LDS costs what it gains (2048 x 8192 x 2048: 58.4 and 58.9).
+constexpr int STAGE_OUT_BYTES = 4096;              // two rows sets (four rows x 512 bytes each), used in turn
+template <bool BF, int CT, int JA, int J0, int NJ, bool STAGED = false>
+__device__ __forceinline__ void red_store(const f32x4_t (&acc)[JA][8], const GemmArgs& g, int m_base, int n0, int lane, PIT_LDS char* stage = nullptr) {
   const int q = lane & 15, kb = lane >> 4;
 #pragma unroll
   for (int a = 0; a < NJ; ++a) {
@@ -126,7 +140,19 @@ __device__ __forceinline__ void red_store(const f32x4_t (&acc)[JA][8], const Gem
     for (int e = 0; e < 4; ++e) {
       const int64_t row = m_base + JA * (4 * kb + e) + ja;
       const int col = n0 + 8 * q;
-      if constexpr (CT == 0) {
+      if constexpr (CT == 0 && STAGED) {
+        PIT_LDS char* s = stage + ((a * 4 + e) & 1) * (STAGE_OUT_BYTES / 2);   // row kb of the four at 512 kb
+        *(PIT_LDS f32x4_t*)(s + lane * 32) = f32x4_t{acc[ja][0][e], acc[ja][1][e], acc[ja][2][e], acc[ja][3][e]};
+        *(PIT_LDS f32x4_t*)(s + lane * 32 + 16) = f32x4_t{acc[ja][4][e], acc[ja][5][e], acc[ja][6][e], acc[ja][7][e]};
+        wave_lds_fence();
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const f32x4_t v = *(PIT_LDS f32x4_t*)(s + i * 1024 + lane * 16);
+          const int64_t r = m_base + JA * (4 * (2 * i + (lane >> 5)) + e) + ja;
+          __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(g.C) + r * g.ldc + n0 + 4 * (lane & 31)));
+        }
+        wave_lds_fence();
+      } else if constexpr (CT == 0) {
         // (streaming stores: the result is not read again by this kernel and should not displace the
         // operand panels from L2)
         typedef float f4_t __attribute__((ext_vector_type(4)));
@@ -212,9 +238,11 @@ k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
   constexpr bool RED_QUARTERS = NW == 4 && JA == 8;
   __shared__ __attribute__((aligned(16)))
   char s_red[NW == 1 ? 16 : RED_QUARTERS ? 2 * RED_BUF_BYTES : NW == 2 ? 2 * RED_HALF_BYTES : NW * RED_ALL_BYTES];
+  __shared__ __attribute__((aligned(16))) char s_out[CT == 0 && NW <= 2 ? NW * STAGE_OUT_BYTES : 16];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  PIT_LDS char* stage = (PIT_LDS char*)s_out + (CT == 0 && NW <= 2 ? wv * STAGE_OUT_BYTES : 0);
   const int q = lane & 15, kb = lane >> 4;
   const char* a_src = uniform_ptr(g.A);
   const char* b_src = uniform_ptr(g.B);
@@ -392,7 +420,7 @@ k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
 
     const int m_base = T.row * TMJ;
     if constexpr (NW == 1) {
-      red_store<BF, CT, JA, 0, JA>(acc, g, m_base, T.n0, lane);
+      red_store<BF, CT, JA, 0, JA, true>(acc, g, m_base, T.n0, lane, stage);
     } else if constexpr (!RED_QUARTERS && NW > 2) {
       // Every wave leaves its whole partial tile in LDS as the vectors of four columns that are stored later; each then
       // adds up, in the order of the waves, and stores an NW-th of the tile.
@@ -426,10 +454,10 @@ k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
       __syncthreads();
       if (wv == 0) {
         red_recv_half<JA, 0>(acc, red + RED_HALF_BYTES + lane * 16);
-        red_store<BF, CT, JA, 0, JA / 2>(acc, g, m_base, T.n0, lane);
+        red_store<BF, CT, JA, 0, JA / 2, true>(acc, g, m_base, T.n0, lane, stage);
       } else {
         red_recv_half<JA, 1>(acc, red + lane * 16);
-        red_store<BF, CT, JA, JA / 2, JA / 2>(acc, g, m_base, T.n0, lane);
+        red_store<BF, CT, JA, JA / 2, JA / 2, true>(acc, g, m_base, T.n0, lane, stage);
       }
     }
     if (!more) break;
