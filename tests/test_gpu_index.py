@@ -300,3 +300,18 @@ def test_check_index_counts_violations(pit):
     sp3 = torch.tensor([0, 3, 3, 9], dtype=torch.int32, device="cuda")      # beyond the capacity
     assert int(pit.pit_check_index(pit.PitIndex(sp3, idx, None, 3, 8), 10).item()) == 1
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("rows", [1, 63, 1023, 1024, 1025, 3000, 16384, 17409, 65536])
+@pytest.mark.parametrize("ld,offset", [(1, 0), (1, 3), (5, 0)])
+def test_row_mask_of_several_workgroups(pit, rows, ld, offset):
+    """A byte mask over rows: a workgroup per 1024 rows, each counting the rows before its own; contiguous and aligned,
+    misaligned, strided.  Bytes other than 0 and 1 among them; the whole index bit for bit."""
+    g = np.random.default_rng(rows + ld + offset)
+    m = np.where(g.random(rows) < 0.4, g.choice([1, 2, 128, 255], size=rows), 0).astype(np.uint8).reshape(-1, 1)
+    flat = torch.zeros(offset + rows * ld, dtype=torch.uint8, device=dev())
+    src = flat[offset:].view(rows, ld)[:, :1]
+    src.copy_(torch.from_numpy(m))
+    ix = pit.pit_build_index(src, 1, 1, 0)
+    torch.cuda.synchronize()
+    assert_index_equal(ix, orc.build_index(m, 1, 1, 0))
