@@ -262,7 +262,8 @@ k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
   // where tiles are few along m (8 x 32 tiles, 1024 x 16384 x 4096 half listed) rows are better by 1 %.
   const bool dense = g.idx == nullptr;
   const bool wide = tn > 2 * tm_tiles;
-  const int sub = g.slab / TMJ;       // tiles that share one list (the tile may be lower than the micro-tile)
+  // 1, 2 or 4 tiles share one list (the tile may be lower than the micro-tile)
+  const int sub_shift = JA == 8 ? 0 : __builtin_ctz((unsigned)g.slab / (unsigned)TMJ);
   auto tile_of = [&](int lin) -> DirectTile {
     const int x = lin & 7, qq = total >> 3, rr = total & 7;
     const int lp = x * qq + min(x, rr) + (lin >> 3);
@@ -274,7 +275,7 @@ k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
     t.row = wide ? thin : len;
     t.n0 = (wide ? len : thin) * TN;
     // dense mode (no index): every tile's list is 0, 1, .., K - 1 and is never read from memory
-    const int seg = t.row / sub;
+    const int seg = t.row >> sub_shift;
     const int list_begin = dense ? 0 : g.seg_ptr[seg];
     t.list_len = dense ? g.K : g.seg_ptr[seg + 1] - list_begin;
     const int nslab = (t.list_len + SK - 1) / SK;
