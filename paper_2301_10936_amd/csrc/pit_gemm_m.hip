@@ -642,7 +642,7 @@ template <bool BF, int EPI, int CT>
 int launch_few(const GemmArgs& g, int64_t total_rows, hipStream_t st) {
   // sum over segments of ceil(count / 16): at most one tile per row, and one partly filled tile per segment
   const int64_t tiles = std::min<int64_t>(total_rows, total_rows / 16 + g.nseg);
-  if (tiles > 65535) return PIT_ESHAPE;
+  if (total_rows / 128 + g.nseg > 65520) return PIT_ESHAPE;     // (the limit of launch_cfg: tiles <= 65520 then, too)
   hipLaunchKernelGGL((k_gather_m_few<BF, EPI, CT>), dim3((unsigned)(g.N / 64), (unsigned)tiles), dim3(512), 0, st, g);
   PIT_LAUNCH_CHECK();
   return PIT_OK;
