@@ -58,6 +58,10 @@ __device__ __forceinline__ void mfma16_acc(const uint4& a, const uint4& b, f32x4
   if constexpr (BF) asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(av), "v"(bv));
   else              asm("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(av), "v"(bv));
 }
+// acc = z z + 0 (z = zeros), in place as well and under the same rules
+__device__ __forceinline__ void mfma16_zero(const u32x4_t& z, f32x4_t& c) {
+  asm("v_mfma_f32_16x16x32_bf16 %0, %1, %1, 0" : "+a"(c) : "v"(z));
+}
 // wait until the matrix pipe has written every accumulator (a 4-pass MFMA needs at most 10 idle
 // issue slots before another kind of instruction may read its result)
 #define PIT_MFMA_DRAIN() do { PIT_SCHED_FENCE(); asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); PIT_SCHED_FENCE(); } while (0)
@@ -130,12 +134,21 @@ __device__ __forceinline__ void red_recv_half(f32x4_t (&acc)[JA][8], PIT_LDS cha
 // any store 41, 34, 37); 2944 x 3001 x 3072, full lists, 79.4 -> 75.4.  With four waves per tile, one or two tiles per
 // compute unit, the way through LDS costs what it gains (2048 x 8192 x 2048: 58.4 and 58.9).
 constexpr int STAGE_OUT_BYTES = 4096;              // two rows sets (four rows x 512 bytes each), used in turn
-template <bool BF, int CT, int JA, int J0, int NJ, bool STAGED = false>
-__device__ __forceinline__ void red_store(const f32x4_t (&acc)[JA][8], const GemmArgs& g, int m_base, int n0, int lane, PIT_LDS char* stage = nullptr) {
+// PART: with has_part another partial tile of the lane (quad (ja, jb) at part + 1024 (8 ja + jb)) is added first.
+template <bool BF, int CT, int JA, int J0, int NJ, bool STAGED = false, bool PART = false>
+__device__ __forceinline__ void red_store(f32x4_t (&acc)[JA][8], const GemmArgs& g, int m_base, int n0, int lane, PIT_LDS char* stage = nullptr,
+                                          bool has_part = false, PIT_LDS char* part = nullptr) {
   const int q = lane & 15, kb = lane >> 4;
 #pragma unroll
   for (int a = 0; a < NJ; ++a) {
     const int ja = J0 + a;
+    if constexpr (PART) {
+      if (has_part) {
+#pragma unroll
+        for (int jb = 0; jb < 8; ++jb) acc[ja][jb] += *(PIT_LDS f32x4_t*)(part + (8 * ja + jb) * 1024 + lane * 16);
+      }
+      PIT_SCHED_FENCE();
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int64_t row = m_base + JA * (4 * kb + e) + ja;
@@ -220,7 +233,10 @@ struct DirectTile {
 
 // NW = waves per workgroup that split the k-list: 4 (one 128-row tile fills a compute unit), 2 (two
 // workgroups, i.e. two tiles, share a compute unit at the same register cost, and the set-up, drain,
-// reduction and stores of one tile run under the MFMA loop of the other) or 1 (no reduction at all).
+// reduction and stores of one tile run under the MFMA loop of the other) or 1 (no reduction between waves).
+// One wave sums the first half of its slabs, puts that partial tile away in LDS, sums the other half and adds the two:
+// chains of additions as long as those of two waves.  (One chain over all slabs has up to 1.4 times their rounding error:
+// 4096^3, half live, 32-row tiles 1.05e-7 of the result, 7.8e-8 with two chains and with two waves.)
 // JA = row groups of the tile: the tile is 16 * JA rows high (128, 64 or 32), a lane loads JA consecutive m of
 // each listed row of At (16, 8 or 4 bytes) and a slab takes JA x 8 MFMAs.  Lower tiles follow a finer sparsity
 // pattern (the micro-tile height of the index; fewer all-zero micro-tiles are multiplied) or spread a small
@@ -237,7 +253,7 @@ k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
   constexpr int RED_ALL_BYTES = 2 * RED_HALF_BYTES;   // one wave's whole partial tile
   constexpr bool RED_QUARTERS = NW == 4 && JA == 8;
   __shared__ __attribute__((aligned(16)))
-  char s_red[NW == 1 ? 16 : RED_QUARTERS ? 2 * RED_BUF_BYTES : NW == 2 ? 2 * RED_HALF_BYTES : NW * RED_ALL_BYTES];
+  char s_red[NW == 1 ? RED_ALL_BYTES : RED_QUARTERS ? 2 * RED_BUF_BYTES : NW == 2 ? 2 * RED_HALF_BYTES : NW * RED_ALL_BYTES];
   __shared__ __attribute__((aligned(16))) char s_out[CT == 0 && NW <= 2 ? NW * STAGE_OUT_BYTES : 16];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -308,6 +324,28 @@ k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
   for (int i = 0; i < JA; ++i)
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // A wave on its own puts the sums of the first half of its slabs away in LDS.  The accumulators are then set to zero by
+  // the matrix pipe: written by vector instructions, in a branch inside the loop, they come out in other registers, and
+  // the kernel spills.
+  auto half_done = [&](const DirectTile& T, int done) {
+    if constexpr (NW == 1) {
+      if (done == T.n_w >> 1) {
+        u32x4_t z = {0u, 0u, 0u, 0u};
+        asm volatile("" : "+v"(z));
+        PIT_MFMA_DRAIN();
+#pragma unroll
+        for (int i = 0; i < JA; ++i)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) *(PIT_LDS f32x4_t*)((PIT_LDS char*)s_red + (8 * i + j) * 1024 + lane * 16) = acc[i][j];
+        PIT_SCHED_FENCE();
+#pragma unroll
+        for (int i = 0; i < JA; ++i)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) mfma16_zero(z, acc[i][j]);
+        PIT_SCHED_FENCE();
+      }
+    }
+  };
 
   // JA x 8 MFMAs on one slab (64 for the 128-row tile, which the description below is written for).  All B operands are transposed first; the A operand of column group
   // ja + 1 is transposed (4 v_perm_b32) in the shadow of the first MFMAs of group ja.  The order is
@@ -399,10 +437,13 @@ k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
       int t = 0;
       for (; t + 2 < T.n_w; t += 2) {
         process_issue(T, ra0, rb0, k0); k0 = load_list(T, t + 4); PIT_SCHED_FENCE();
+        half_done(T, t + 1);
         process_issue(T, ra1, rb1, k1); k1 = load_list(T, t + 5); PIT_SCHED_FENCE();
+        half_done(T, t + 2);
       }
       if (T.n_w - t == 2) {
         process(T, ra0, rb0);
+        half_done(T, t + 1);
 #pragma unroll
         for (int i = 0; i < 8; ++i) { ra0[i] = ra1[i]; rb0[i] = rb1[i]; }
         ++t;
@@ -421,7 +462,7 @@ k_gather_k_direct(const GemmArgs g, const int tm_tiles) {
 
     const int m_base = T.row * TMJ;
     if constexpr (NW == 1) {
-      red_store<BF, CT, JA, 0, JA, true>(acc, g, m_base, T.n0, lane, stage);
+      red_store<BF, CT, JA, 0, JA, true, true>(acc, g, m_base, T.n0, lane, stage, T.n_w > 1, red);
     } else if constexpr (!RED_QUARTERS && NW > 2) {
       // Every wave leaves its whole partial tile in LDS as the vectors of four columns that are stored later; each then
       // adds up, in the order of the waves, and stores an NW-th of the tile.
@@ -1074,7 +1115,8 @@ static int launch_gather_k_tile(const GemmArgs& g, int resident, hipStream_t st)
 //   otherwise the micro-tile's own height.  128 rows: four waves up to two tiles per compute unit, two beyond.  Lower
 //     tiles: two waves, and from eight tiles per compute unit on one wave, without a reduction (4096^3, two waves / one:
 //     32 rows at 10 % 48.5 / 47.3, at 50 % 171 / 147; 64 rows at 10 % 53.6 / 49.5, at 50 % 88.6 / 89.0; with four tiles
-//     per compute unit and lists of 200 entries, 32 rows, 10.1 / 11.2).
+//     per compute unit and lists of 200 entries, 32 rows, 10.1 / 11.2; measured with one chain of additions: the second
+//     adds 0 - 0.5 us to the 32-row, 0.6 - 1.5 to the 64-row products).
 template <bool BF, int CT>
 static int launch_gather_k(const GemmArgs& g, int tm_tiles, hipStream_t st) {
   const int64_t cus = compute_units(), tn = g.N / TN;

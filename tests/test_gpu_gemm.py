@@ -169,6 +169,22 @@ def test_gather_k_tile_heights_and_waves(pit, tiles_m, tiles_n, mt):
     test_gather_k_more_tiles_than_compute_units(pit, tiles_m, tiles_n, mt)
 
 
+@pytest.mark.parametrize("M,K,mt", [(4224, 1300, 32), (8448, 1300, 64)])
+def test_gather_k_one_wave_rounds_no_more_than_two(pit, M, K, mt):
+    """From eight tiles per compute unit on a wave works alone on a tile.  It adds in two chains, like the two waves that
+    a narrower product has: the rounding error of the whole result is theirs (the two are estimates over millions of
+    elements: 5 %; a single chain over the 41 slabs of these lists has 1.35 times as much)."""
+    N = 2048
+    g = torch.Generator(device="cuda").manual_seed(mt)
+    X, W = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((K, M), (K, N)))
+    ix = pit.pit_build_index(X, 1, mt, 0)
+    run = lambda w: pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_K, X, w, ix, mt, M, w.shape[1], K)
+    ref = X.double().t().contiguous() @ W.double()
+    one = (run(W) - ref).norm()
+    two = (torch.cat([run(W[:, n:n + 512]) for n in range(0, N, 512)], dim=1) - ref).norm()
+    assert one <= 1.05 * two, (float(one / ref.norm()), float(two / ref.norm()))
+
+
 @pytest.mark.parametrize("mt", MTS)
 def test_gather_k_strided_operands_and_large_last_row(pit, mt):
     """Row pitches larger than the row length (views into wider buffers); the last listed row holds
