@@ -787,10 +787,15 @@ k_slab_strip(const GemmArgs g) {
 //
 // k_slab_strip reads B once per 32 rows of C and multiplies blocks of 16 rows of which, at 10 % density, three are
 // real; its four waves each hold a strip, so strips cannot grow.  Here a workgroup owns R x 128 of C in LDS (fp32) and
-// a wavefront owns 64 of the columns for ALL slabs: rows are only ever touched by one wave (no atomics, no barrier
+// a wavefront owns 64 of the columns: rows are only ever touched by one wave (no atomics, no barrier
 // between slabs, a fixed order of additions), and the strip is R = 128 rows high: B is read a quarter as often and the
-// blocks of 16 rows are nearly full.  With SG = 2 (R = 64) two pairs of waves take every other slab into strips of
+// blocks of 16 rows are nearly full.  With SG = 2 two pairs of waves take every other slab into strips of
 // their own that are added at the end.  Rows that nothing touched are stored as zeros.
+// Rounding: a visit's products are summed from zero and then added to the strip, one rounding of the running sum per
+// visit where the matrix unit makes one per eight products.  With 64 k per visit that makes one chain of additions more
+// exact than k_slab_strip's four, with 32 k two chains (error against 64 bits, 4096^3, four chains / here: 1 x 64 at
+// 10 % and 50 % 7.7e-8 / 6.8e-8 and 1.36e-7 / 1.15e-7; 1 x 32 7.3e-8 / 6.6e-8 and 1.34e-7 / 1.15e-7; one chain at 1 x 32:
+// 7.7e-8 and 1.52e-7).  Hence SG = 2 with R = 128 as well where KS = 1.
 //   list of a strip: lower bounds of its first row and of the row after it in every slab's ascending list,
 //   searched 8-ary with one slab per lane (64 slabs at once: two waves, four round trips to memory for
 //   lists of thousands); the rows are kept as bytes in LDS.
@@ -802,8 +807,9 @@ k_slab_strip(const GemmArgs g) {
 // Bound by the vector-load path: per slab and strip 16 KB of B and 2 x 2 KB of A at 40 bytes per clock and CU are about
 // 500 clocks, the LDS read-modify-write of C 220, the issue of a wave's 170 instructions 700 (four waves per CU: the
 // strips fill the LDS); they overlap in part, about 850 are measured.  4096^3, 1 x 64 micro-tiles, 10 % kept: 231 ->
-// 108 us (50 %: 363 -> 285, 1 %: 112 -> 74; 1 x 32, 10 %: 339 -> 149; the launch without its slab loop: 18 us).
-// Tried: waves of 32 columns, eight per CU (twice the load instructions: 121 us), R = 256 with four waves per CU (114).
+// 112 us (50 %: 363 -> 267, 1 %: 112 -> 78; 1 x 32, 10 %: 339 -> 156; the launch without its slab loop: 18 us).
+// Tried: waves of 32 columns, eight per CU (twice the load instructions: 121 us), R = 256 with four waves per CU (114),
+// four chains in 64-row strips, one workgroup of eight waves per CU (205: B is read twice as often).
 // ------------------------------------------------------------------------------------------------
 constexpr int ST_W = 128;                            // columns of C per workgroup (2 waves x 64)
 constexpr int ST_BATCH = 64;                         // slabs whose row lists are in LDS together (one lane each)
@@ -939,19 +945,17 @@ k_slab_strip_tall(const GemmArgs g) {
         at[e] = (16 * b + 4 * kb + e < u.n ? ((rl >> (8 * e)) & 255u) : (uint32_t)R) * (uint32_t)WC + (uint32_t)CW * (uint32_t)q;
     };
     auto rows4 = [&](const Visit& u, int b) -> uint32_t { return *reinterpret_cast<const uint32_t*>(&s_list[u.j][16 * b + 4 * kb]); };
-    auto c_read = [&](const uint32_t (&at)[4], f32x4_t (&acc)[CW]) {
+    auto c_read = [&](const uint32_t (&at)[4], f32x4_t (&c)[4]) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(strip + at[e]);
-#pragma unroll
-        for (int x = 0; x < CW; ++x) acc[x][e] = v[x];
-      }
+      for (int e = 0; e < 4; ++e) c[e] = *reinterpret_cast<const f32x4_t*>(strip + at[e]);
     };
-    auto c_write = [&](const uint32_t (&at)[4], const f32x4_t (&acc)[CW]) {
+    auto c_write = [&](const uint32_t (&at)[4], const f32x4_t (&c)[4], const f32x4_t (&acc)[CW]) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        *reinterpret_cast<f32x4_t*>(strip + at[e]) = f32x4_t{acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
-      }
+      for (int e = 0; e < 4; ++e) *reinterpret_cast<f32x4_t*>(strip + at[e]) = c[e] + f32x4_t{acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
+    };
+    auto zero = [&](f32x4_t (&acc)[CW]) {
+#pragma unroll
+      for (int x = 0; x < CW; ++x) acc[x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     };
     auto mfmas = [&](const uint4 (&a)[KS], const uint4 (&bop)[KS][CW], f32x4_t (&acc)[CW]) {
 #pragma unroll
@@ -961,19 +965,21 @@ k_slab_strip_tall(const GemmArgs g) {
     };
     auto block = [&](const Visit& u, int b, const uint4 (&a)[KS], const uint4 (&bop)[KS][CW]) {
       uint32_t at[4];
-      f32x4_t acc[CW];
+      f32x4_t c[4], acc[CW];
       c_at(u, b, rows4(u, b), at);
-      c_read(at, acc);
+      c_read(at, c);
+      zero(acc);
       mfmas(a, bop, acc);
-      c_write(at, acc);
+      c_write(at, c, acc);
     };
     // rl: the listed rows of block 0 (fetched during the previous visit); returns those of the next visit
     auto visit = [&](const Visit& u, const Visit& following, const Visit& ahead, Regs& r, uint32_t rl) -> uint32_t {
       const uint32_t off0 = row_of(ahead, 0), off1 = row_of(ahead, 1), rl_next = rows4(following, 0);
       uint32_t at[4];
-      f32x4_t acc[CW];
+      f32x4_t c[4], acc[CW];
       c_at(u, 0, rl, at);
-      c_read(at, acc);
+      c_read(at, c);
+      zero(acc);
       // (opaque: keeps the transposes behind the loads of the two visits ahead -- the compiler otherwise carries the
       // transposed registers around the loop and waits for loads just issued)
 #pragma unroll
@@ -1006,7 +1012,7 @@ k_slab_strip_tall(const GemmArgs g) {
       load_a(k_of(ahead), off0, r.a[0]);
       asm volatile("" ::: "memory");                // (the loads are not to be moved behind what follows)
       PIT_SCHED_FENCE();
-      c_write(at, acc);
+      c_write(at, c, acc);
       if (u.n > 16) {
         block(u, 1, r.a[1], bop);
         if constexpr (R > 32)
@@ -1144,14 +1150,13 @@ static int launch_sread_gemm_k(bool bf, int c_is_in_type, const GemmArgs& g, int
 //   128 x 128 tiles = 512: 52 / 35 / 30 and 47 / 43 / 41;  437: 129 / 74 / 52;  384: 81 / 70 / 91 (30 % kept), 56 / 45 / 39 (2 %)
 //   64 x 128 tiles = 512: 49 / 30 / 43, 31 / 30 / 32;  384: 31 / 36 / 56 -- but 42 / 29 / 42 with micro-tiles of 32 k, where the
 //   32-row kernel pays its read-modify-write twice as often;  256 of those: 47 / 39, 15.8 / 15.9;  128: 13.0 / 14.7
-template <bool BF, int R, int SG>
+template <bool BF, int KS, int R, int SG>
 static int launch_slab_tall(GemmArgs g, hipStream_t st) {
   // XCDs as 2 row groups x 4 column groups (1, 2, 4 or 8 column groups measure within 4 %, 8 row groups 10 % slower)
   g.xcd_cols = 4;
   const int64_t cols = ceil_div(g.N / ST_W, 4), rws = ceil_div(ceil_div(g.M, R), 2);
   dim3 grid((unsigned)(8 * cols * rws));
-  if (g.slab % 64 == 0) hipLaunchKernelGGL((k_slab_strip_tall<BF, 2, R, SG>), grid, dim3(128 * SG), 0, st, g);
-  else                  hipLaunchKernelGGL((k_slab_strip_tall<BF, 1, R, SG>), grid, dim3(128 * SG), 0, st, g);
+  hipLaunchKernelGGL((k_slab_strip_tall<BF, KS, R, SG>), grid, dim3(128 * SG), 0, st, g);
   PIT_LAUNCH_CHECK();
   return PIT_OK;
 }
@@ -1160,8 +1165,9 @@ static int launch_slab_strip(const GemmArgs& g, hipStream_t st) {
   const int64_t tn = g.N / ST_W, cus = compute_units();
   const int64_t strips = ceil_div(g.M, StripShape<8>::R);
   if (strips > 65535) return PIT_ESHAPE;
-  if (3 * ceil_div(g.M, 128) * tn >= 5 * cus) return launch_slab_tall<BF, 128, 1>(g, st);
-  if (ceil_div(g.M, 64) * tn >= (g.slab % 64 == 0 ? 2 : 1) * cus) return launch_slab_tall<BF, 64, 2>(g, st);
+  const bool wide = g.slab % 64 == 0;               // 64 k per visit
+  if (3 * ceil_div(g.M, 128) * tn >= 5 * cus) return wide ? launch_slab_tall<BF, 2, 128, 1>(g, st) : launch_slab_tall<BF, 1, 128, 2>(g, st);
+  if (ceil_div(g.M, 64) * tn >= (wide ? 2 : 1) * cus) return wide ? launch_slab_tall<BF, 2, 64, 2>(g, st) : launch_slab_tall<BF, 1, 64, 2>(g, st);
   // 32 x 128 strips.  (64 x 64 strips, CW = 4, halve the traffic of B and double that of A: measured 10-15 %
   // faster at 90-95 % sparsity of a 4096^3 product, 10-20 % slower at 50 % and at 99 %.)
   constexpr int CW = 8;
