@@ -832,14 +832,15 @@ k_slab_strip_tall(const GemmArgs g) {
   const int q = lane & 15, kb = lane >> 4;
   int n0, r0;
   {
-    // the 8 XCDs (own L2 each; consecutive workgroup ids go to different ones) form column groups x row groups
-    const int tn = g.N / ST_W, tm = (g.M + R - 1) / R;
-    const int xc = g.xcd_cols, xr = 8 / xc;
-    const int cols = (tn + xc - 1) / xc, rws = (tm + xr - 1) / xr;
-    const int x = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int c = (x % xc) * cols + slot % cols, r = (x / xc) * rws + slot / cols;
-    if (slot / cols >= rws || c >= tn || r >= tm) return;
-    n0 = c * ST_W; r0 = r * R;
+    // Consecutive workgroup ids go to different XCDs (8, own L2 each): renumber so that each takes a contiguous run of the
+    // strips, the runs equal but for one strip, in bands of 4 tile columns x all rows.  (4 column groups x 2 row groups of
+    // XCDs, us / here: 16 or 32 tile columns the same; 17, 3456 x 2048 x 2176, 58.9 / 35.3; 5, 11000 x 1024 x 640, 43.8 / 25.2;
+    // 1, 60000 x 1024 x 128, 86.4 / 25.9: XCDs without work.)
+    const int tn = g.N / ST_W, tm = (g.M + R - 1) / R, total = tn * tm;
+    const int x = blockIdx.x & 7, lp = x * (total >> 3) + min(x, total & 7) + ((int)blockIdx.x >> 3);
+    const int band = lp / (4 * tm), within = lp - band * (4 * tm), n = min(4, tn - 4 * band);
+    n0 = (4 * band + within % n) * ST_W;
+    r0 = within / n * R;
   }
   const int rows = min(R, g.M - r0);
   float* strip = s_c[wv];
@@ -1151,11 +1152,8 @@ static int launch_sread_gemm_k(bool bf, int c_is_in_type, const GemmArgs& g, int
 //   64 x 128 tiles = 512: 49 / 30 / 43, 31 / 30 / 32;  384: 31 / 36 / 56 -- but 42 / 29 / 42 with micro-tiles of 32 k, where the
 //   32-row kernel pays its read-modify-write twice as often;  256 of those: 47 / 39, 15.8 / 15.9;  128: 13.0 / 14.7
 template <bool BF, int KS, int R, int SG>
-static int launch_slab_tall(GemmArgs g, hipStream_t st) {
-  // XCDs as 2 row groups x 4 column groups (1, 2, 4 or 8 column groups measure within 4 %, 8 row groups 10 % slower)
-  g.xcd_cols = 4;
-  const int64_t cols = ceil_div(g.N / ST_W, 4), rws = ceil_div(ceil_div(g.M, R), 2);
-  dim3 grid((unsigned)(8 * cols * rws));
+static int launch_slab_tall(const GemmArgs& g, hipStream_t st) {
+  const dim3 grid((unsigned)(ceil_div(g.M, R) * (g.N / ST_W)));
   hipLaunchKernelGGL((k_slab_strip_tall<BF, KS, R, SG>), grid, dim3(128 * SG), 0, st, g);
   PIT_LAUNCH_CHECK();
   return PIT_OK;

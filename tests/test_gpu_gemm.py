@@ -363,10 +363,11 @@ def test_microtile_wider_slab(pit):
 
 
 # strips of 64 rows (one or two k-steps per visit) and of 128 rows: last strips of 32, 56, 72 and 1 rows, more than 64 slabs,
-# three visits per slab, lists of up to two blocks, of many blocks and of every row, both types
+# three visits per slab, lists of up to two blocks, of many blocks and of every row, both types; 5 and 9 tile columns
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("M,K,N,mt,p", [(2080, 96, 1024, 32, 0.5), (2040, 192, 2048, 64, 0.1), (3400, 2112, 2048, 32, 0.02),
-                                        (3400, 288, 2048, 96, 0.2), (3457, 256, 2048, 128, 1.0)])
+                                        (3400, 288, 2048, 96, 0.2), (3457, 256, 2048, 128, 1.0),
+                                        (3700, 128, 1152, 64, 0.3), (6600, 64, 1152, 32, 0.3), (11000, 128, 640, 64, 0.1)])
 def test_microtile_tall_strips(pit, M, K, N, mt, p, dtype):
     w = wl.microtile_gemm(M=M, K=K, N=N, mt_k=mt, p_keep=p, seed=M + mt, integer=True)
     ref = orc.gemm(w.A, w.B)
