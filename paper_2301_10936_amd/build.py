@@ -5,40 +5,61 @@ and is what the ctypes binding loads.
 """
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpit_hip.so")
-SOURCES = ["pit_api.hip", "pit_index.hip", "pit_gemm.hip", "pit_gemm_m.hip", "pit_moe.hip", "pit_attn.hip"]
-# -amdgpu-mfma-vgpr-form: matrix results in vector registers (a kernel that loads its accumulators from LDS and writes them
-# back otherwise pays a register move per element each way: 212 of the 3000 instructions of k_slab_strip_tall)
-FLAGS = ["--offload-arch=gfx950", "-O3", "-mllvm", "-amdgpu-mfma-vgpr-form", "-std=c++17", "-fPIC", "-shared", "-Wno-inline-asm", "-Wno-pass-failed",
+SOURCES = ["pit_api.hip", "pit_index.hip", "pit_gemm.hip", "pit_gemm_m.hip", "pit_slab.hip", "pit_moe.hip", "pit_attn.hip"]
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wno-inline-asm", "-Wno-pass-failed",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# Options of one source, left out where the compiler does not know them.
+# -amdgpu-mfma-vgpr-form: matrix results in vector registers.  The 128-row k_slab_strip_tall adds them to values from LDS and
+# pays a register move per element otherwise (4096^3, 1 x 32 micro-tiles, 10 % kept: 157 us with, 163 without; 1 x 64 at
+# 50 % 269, 282).  No other kernel gains, and the hand-placed distances between matrix instructions in pit_gemm.hip are
+# those of code generated without it.
+OPTIONAL = {"pit_slab.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 PROBE_LIB = os.path.join(HERE, "libpit_probe.so")     # measurement probes (bench_micro.py --probe), not the product
 
 
-def _compile(srcs, lib, verbose):
-    cmd = ["hipcc", *FLAGS, "-o", lib, *srcs]
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     noise = "is not a recognized feature for this target"
-    out = "\n".join(l for l in proc.stdout.splitlines() if noise not in l)
-    if proc.returncode != 0:
+    return proc.returncode, "\n".join(l for l in proc.stdout.splitlines() if noise not in l)
+
+
+def _compile(src, obj, verbose):
+    optional = OPTIONAL.get(os.path.basename(src), [])
+    rc, out = _run(["hipcc", *FLAGS, *optional, "-c", "-o", obj, src], verbose)
+    if rc != 0 and optional and "unknown command line argument" in out.lower():
+        rc, out = _run(["hipcc", *FLAGS, "-c", "-o", obj, src], verbose)
+    if rc != 0:
         raise RuntimeError("hipcc failed:\n" + out)
     if verbose and out.strip():
-        print(out)
+        print(out, flush=True)
+
+
+def _library(srcs, lib, verbose):
+    with tempfile.TemporaryDirectory() as tmp, concurrent.futures.ThreadPoolExecutor(4) as pool:
+        objs = [os.path.join(tmp, os.path.basename(s) + ".o") for s in srcs]
+        list(pool.map(_compile, srcs, objs, [verbose] * len(srcs)))
+        rc, out = _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *objs], verbose)
+    if rc != 0:
+        raise RuntimeError("hipcc failed:\n" + out)
 
 
 def build(verbose: bool = False) -> str:
     srcs = [os.path.join(CSRC, s) for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
-    _compile(srcs, LIB, verbose)
-    _compile([os.path.join(CSRC, "pit_probe.hip")], PROBE_LIB, verbose)
+    _library(srcs, LIB, verbose)
+    _library([os.path.join(CSRC, "pit_probe.hip")], PROBE_LIB, verbose)
     return LIB
 
 

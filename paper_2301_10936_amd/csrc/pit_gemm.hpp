@@ -1,6 +1,7 @@
 // Types, tile constants and host-side launchers shared by the SRead -> dense MFMA tile -> SWrite
 // kernels for gfx950 (paper Section 3.1, sparse kernel template).  The kernels themselves:
-//   pit_gemm.hip    GATHER_K (k is the PIT-axis, operands register-direct) and the k-slab strips
+//   pit_gemm.hip    GATHER_K (k is the PIT-axis, operands register-direct)
+//   pit_slab.hip    GATHER_M with several k-slabs per row (strips of C in LDS)
 //   pit_gemm_m.hip  GATHER_M with whole-row micro-tiles (operands staged through LDS by direct loads)
 // Their device-side helpers are in pit_gemm_dev.hpp.
 #pragma once
@@ -44,5 +45,15 @@ struct GemmArgs {
 // number of listed rows over all segments (the grid is sized for the worst case; the counts stay on the device).
 int launch_gather_m(bool bf, int epi, int c_is_in_type, const GemmArgs& g, int64_t total_rows, hipStream_t st);
 int launch_zero_rows(void* C, int64_t ld_bytes, int M, int64_t row_bytes, hipStream_t st);
+// GATHER_M with several k-slabs per row (pit_slab.hip); fp32 results
+int launch_slab_strip(bool bf, const GemmArgs& g, hipStream_t st);
+
+// compute units of the current device rounded down to a multiple of 8 (one share per XCD)
+inline int compute_units() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
+  return n & ~7;
+}
 
 }  // namespace pit

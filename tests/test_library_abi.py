@@ -97,3 +97,16 @@ def test_selection_with_the_profiled_tile_costs():
         picks[name] = pit.pit_select_kernel(cands, num, grid)[0]
         assert picks[name] == orc.select_kernel([orc.to_f64(w.Xt)], cands)[0]
     assert picks == {"iid": 1, "correlated": 0}
+
+
+def test_build_leaves_out_an_option_the_compiler_does_not_know(tmp_path, monkeypatch):
+    """An option that one source asks for is an optimisation: a compiler without it still builds the library."""
+    import shutil
+    import pytest
+    from paper_2301_10936_amd import build
+    if shutil.which("hipcc") is None:
+        pytest.skip("no hipcc")
+    monkeypatch.setattr(build, "OPTIONAL", {"pit_api.hip": ["-mllvm", "-no-such-option-of-the-compiler"]})
+    obj = tmp_path / "pit_api.o"
+    build._compile(os.path.join(build.CSRC, "pit_api.hip"), str(obj), False)
+    assert obj.stat().st_size > 0
