@@ -38,6 +38,7 @@ struct GemmArgs {
   int xcd_cols;      // GATHER_M, set by the launcher: the 8 XCDs form 8 / xcd_cols row groups x xcd_cols column groups
   int zero_rest;     // GATHER_M, one segment: 1 = the rows of C that the list does not name are set to zero by the
                      // workgroups of the grid that have no tile
+  int stream_c;      // GATHER_M, set by the launcher: 1 = C is written by streaming stores
 };
 
 // Host-side launchers shared by pit_sread_gemm and pit_moe_dispatch_gemm.

@@ -58,6 +58,19 @@ __device__ __forceinline__ uint2 lds_tr(uint32_t addr) {
 #define PIT_LDS_BARRIER() do { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); __builtin_amdgcn_s_barrier(); \
                                asm volatile("" ::: "memory"); } while (0)
 
+// f(store), where store(value, address) is an ordinary or a streaming store of 16 bytes of C (the rule is at launch_cfg).
+// (The marks keep the compiler from merging the two paths, which would make all stores ordinary ones.)
+template <bool CHOICE = true, typename F>
+__device__ __forceinline__ void with_stores_of(const GemmArgs& g, F&& f) {
+  if (CHOICE && g.stream_c) {
+    asm volatile("; streaming stores");
+    f([](const u32x4_t& v, void* at) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(at)); });
+    asm volatile("; end of streaming stores");
+  } else {
+    f([](const u32x4_t& v, void* at) { *reinterpret_cast<u32x4_t*>(at) = v; });
+  }
+}
+
 // Zero the rows of C that an ascending list does not name, for the rows [r_begin, r_end): the share of one
 // workgroup without a tile (all of these shares together cover [0, M)).  One 64-ary search finds the list
 // position of the first row (three or four dependent loads for a list of thousands); from there the list is
@@ -89,8 +102,9 @@ __device__ __forceinline__ void zero_unlisted_rows(const GemmArgs& g, int r_begi
     for (int r = r0 + wv; r < min(r0 + 64, r_end); r += 4) {
       if ((m >> (r - r0)) & 1) continue;
       char* p = reinterpret_cast<char*>(g.C) + (int64_t)r * g.ldc * ESIZE;
-      for (int64_t b = (int64_t)lane * 16; b < nbytes; b += 64 * 16)
-        __builtin_nontemporal_store(u32x4_t{0u, 0u, 0u, 0u}, reinterpret_cast<u32x4_t*>(p + b));
+      with_stores_of(g, [&](auto store) {
+        for (int64_t b = (int64_t)lane * 16; b < nbytes; b += 64 * 16) store(u32x4_t{0u, 0u, 0u, 0u}, p + b);
+      });
     }
   }
 }
@@ -397,9 +411,7 @@ k_gather_m_lds(const GemmArgs g) {
   // took 114 us that way, 99 us with whole lines).  So the wave's
   // 32 x (32 WN) row blocks go through LDS (the ring is free now; each wave has a region of its own): written as
   // the accumulators hold them, read back row-contiguous, and stored with 16 bytes per lane so that consecutive
-  // lanes fill whole 128-byte lines of the destination row.  Streaming stores, here and where unlisted rows are
-  // cleared: the results are as large as the operands together and drove them out of L2 (padded batch, 32 x 512 rows,
-  // 1024 -> 4096: step 126.4 -> 106.0 us with fp32 results, 100.6 -> 98.7 with bf16; 48 x 512, 512 -> 2048: 57.6 -> 54.5).
+  // lanes fill whole 128-byte lines of the destination row.
   constexpr int WCOLS = 32 * WN;                 // columns of the wave's tile
   constexpr int PITCH = WCOLS + 4;               // floats per row in LDS: rows 16 bytes apart in the banks
   static_assert(4 * 32 * PITCH * 4 <= NST * T::STAGE, "the four waves' row blocks must fit the ring");
@@ -429,39 +441,31 @@ k_gather_m_lds(const GemmArgs g) {
         }
     }
     __builtin_amdgcn_wave_barrier();
-    if constexpr (CT == 0) {
-      constexpr int LPR = WCOLS / 4, RPI = 64 / LPR;        // lanes per row, rows per store instruction
-      const int rr = lane / LPR, c4 = (lane % LPR) * 4;
+    with_stores_of<EPI == EPI_STORE>(g, [&](auto store) {
+      if constexpr (CT == 0) {
+        constexpr int LPR = WCOLS / 4, RPI = 64 / LPR;        // lanes per row, rows per store instruction
+        const int rr = lane / LPR, c4 = (lane % LPR) * 4;
 #pragma unroll
-      for (int t = 0; t < 32 / RPI; ++t) {
-        const int row = t * RPI + rr;
-        const int64_t crow = s_rows_c[rb + row];
-        const float4 v = *reinterpret_cast<const float4*>(cw + row * PITCH + c4);
-        if (crow >= 0)
-          __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v),
-                                      reinterpret_cast<u32x4_t*>(reinterpret_cast<float*>(g.C) + crow * g.ldc + n0 + wn * WCOLS + c4));
-      }
-    } else {
-      constexpr int LPR = WCOLS / 8, RPI = 64 / LPR;
-      const int rr = lane / LPR, c8 = (lane % LPR) * 8;
+        for (int t = 0; t < 32 / RPI; ++t) {
+          const int row = t * RPI + rr;
+          const int64_t crow = s_rows_c[rb + row];
+          const float4 v = *reinterpret_cast<const float4*>(cw + row * PITCH + c4);
+          if (crow >= 0) store(__builtin_bit_cast(u32x4_t, v), reinterpret_cast<float*>(g.C) + crow * g.ldc + n0 + wn * WCOLS + c4);
+        }
+      } else {
+        constexpr int LPR = WCOLS / 8, RPI = 64 / LPR;
+        const int rr = lane / LPR, c8 = (lane % LPR) * 8;
 #pragma unroll
-      for (int t = 0; t < 32 / RPI; ++t) {
-        const int row = t * RPI + rr;
-        const int64_t crow = s_rows_c[rb + row];
-        const float4 a = *reinterpret_cast<const float4*>(cw + row * PITCH + c8);
-        const float4 b = *reinterpret_cast<const float4*>(cw + row * PITCH + c8 + 4);
-        uint4 pk;
-        pk.x = pack2_in<BF>(a.x, a.y);
-        pk.y = pack2_in<BF>(a.z, a.w);
-        pk.z = pack2_in<BF>(b.x, b.y);
-        pk.w = pack2_in<BF>(b.z, b.w);
-        if (crow >= 0) {
-          u32x4_t* d = reinterpret_cast<u32x4_t*>(reinterpret_cast<uint16_t*>(g.C) + crow * g.ldc + n0 + wn * WCOLS + c8);
-          if constexpr (EPI == EPI_STORE) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, pk), d);
-          else *d = __builtin_bit_cast(u32x4_t, pk);      // (the hidden rows: the second matmul reads them next)
+        for (int t = 0; t < 32 / RPI; ++t) {
+          const int row = t * RPI + rr;
+          const int64_t crow = s_rows_c[rb + row];
+          const float4 a = *reinterpret_cast<const float4*>(cw + row * PITCH + c8);
+          const float4 b = *reinterpret_cast<const float4*>(cw + row * PITCH + c8 + 4);
+          const u32x4_t pk = {pack2_in<BF>(a.x, a.y), pack2_in<BF>(a.z, a.w), pack2_in<BF>(b.x, b.y), pack2_in<BF>(b.z, b.w)};
+          if (crow >= 0) store(pk, reinterpret_cast<uint16_t*>(g.C) + crow * g.ldc + n0 + wn * WCOLS + c8);
         }
       }
-    }
+    });
     __builtin_amdgcn_wave_barrier();             // the next row block reuses the region
   }
 }
@@ -659,6 +663,14 @@ int launch_cfg(GemmArgs g, int64_t total_rows, hipStream_t st) {
     g.xcd_cols = tn % 4 == 0 ? 4 : tn % 2 == 0 ? 2 : 1;
   }
   g.k_stagger = g.b_seg_stride != 0 ? 1 : 0;
+  // Streaming stores where the result of one B is as large as the Infinity Cache.  A product on its own, over inputs and
+  // outputs used in turn, gains from 64 MiB on (32 x 512 rows, 1024 -> 4096, ordinary / streaming, us: bf16, 128 MiB, 90.3 /
+  // 77.5; fp32, 256 MiB, 110 / 94; with everything cold 98.3 / 95.0 and 117 / 113) -- but what reads the result next finds it
+  // further away.  Padded linear, GELU or ReLU in place, padded linear, per layer of eight: 12 MiB 44.5 / 47.3 and 45.7 /
+  // 47.9; 64 MiB 144.4 / 149.8 and 141.7 / 139.8; 128 MiB 249.8 / 253.6 and 236 / 246; 256 MiB 743 / 742 and 715 / 704.
+  // Never with a B per segment: the hidden rows of a mixture of experts are read by its second product (8192 x 512 x
+  // 2048, 16 experts, identity: 90.6 / 93.0), and its results are small.
+  g.stream_c = g.b_seg_stride == 0 && (int64_t)g.M * g.N * (CT ? 2 : 4) >= (256ll << 20) ? 1 : 0;
   const int64_t max_tiles = total_rows / T::TMW + g.nseg;      // sum over segments of ceil(count / TMW)
   if (max_tiles > 65520) return PIT_ESHAPE;
   // (row tiles rounded up to a multiple of 8: every XCD then has room for its share of the tiles that exist;

@@ -305,6 +305,26 @@ def test_padded_linear_bf16_output(pit):
     assert not got[w.row_mask == 0].any()
 
 
+def test_padded_linear_result_as_large_as_the_cache(pit):
+    """From 256 MiB on the result leaves by streaming stores, listed and cleared rows alike: every element, from a
+    sentinel-filled buffer, against the same product in column slices, which are written by ordinary stores."""
+    M, K, N = 16500, 64, 4096
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X, W = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16) for s in ((M, K), (K, N)))
+    mask = (torch.rand((M, 1), generator=g, device="cuda") < 0.5).to(torch.uint8)
+    ix = pit.pit_build_index(mask, 1, 1, 0)
+    for c_dtype, rows in ((torch.float32, M), (torch.bfloat16, 2 * M)):
+        if rows > M:
+            X, mask = torch.cat([X, X]), torch.cat([mask, mask])
+            ix = pit.pit_build_index(mask, 1, 1, 0)
+        run = lambda w: pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, X, w, ix, K, rows, w.shape[1], K,
+                                           out=torch.full((rows, w.shape[1]), 3.0, dtype=c_dtype, device="cuda"), zero_uncovered=True)
+        Y = run(W)
+        for n in range(0, N, 1024):
+            assert torch.equal(Y[:, n:n + 1024], run(W[:, n:n + 1024].contiguous()))
+        assert not Y[mask[:, 0] == 0].any()
+
+
 def test_c4_full_size(pit):
     w = wl.padded_linear()
     Y = _run_padded(pit, w, sentinel=7.0)
