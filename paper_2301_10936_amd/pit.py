@@ -163,8 +163,8 @@ def pit_build_index_workspace(rows, cols, mt_rows, mt_cols, pit_dim, want_bits=F
 def pit_build_index(src: torch.Tensor, mt_rows: int, mt_cols: int, pit_dim: int, want_bits: bool = False,
                     out: PitIndex | None = None, ws: torch.Tensor | None = None) -> PitIndex:
     """Online sparsity detection on a 2-D tensor (last dim contiguous).  See include/pit.h."""
-    (rows, cols), (ld, unit) = src.shape, src.stride()
-    assert unit == 1
+    assert src.dim() == 2 and src.stride(1) == 1
+    (rows, cols), ld = src.shape, src.stride(0)
     if out is None:
         if rows % mt_rows or cols % mt_cols:
             raise PitError(PIT_ESHAPE, "pit_build_index")

@@ -110,3 +110,17 @@ def test_build_leaves_out_an_option_the_compiler_does_not_know(tmp_path, monkeyp
     obj = tmp_path / "pit_api.o"
     build._compile(os.path.join(build.CSRC, "pit_api.hip"), str(obj), False)
     assert obj.stat().st_size > 0
+
+
+def test_index_calls_refuse_a_tensor_that_is_not_a_matrix_in_the_same_way():
+    """Checked before anything else is done with the tensor: no GPU needed."""
+    import pytest
+    import torch
+    from paper_2301_10936_amd import pit
+    for shape in ((8,), (2, 4, 8)):
+        for call in (lambda t: pit.pit_build_index(t, 1, 1, 0), lambda t: pit.pit_build_index_static(t, 1, 1, 0, None),
+                     lambda t: pit.pit_cover_count(t, 1, 1)):
+            with pytest.raises(AssertionError):
+                call(torch.zeros(shape))
+    with pytest.raises(AssertionError):
+        pit.pit_build_index(torch.zeros((4, 8)).t(), 1, 1, 0)
