@@ -33,6 +33,7 @@
 #include "pit_gemm_dev.hpp"
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <type_traits>
 
 namespace pit {
@@ -482,11 +483,9 @@ k_gather_m_lds(const GemmArgs g) {
 //   B operand: 8 k-rows x 4 columns per lane (16 lanes side by side fill a 128-byte line), transposed inside the lane.
 //   A operand: 16 bytes (8 k) of a listed row per lane -- already the operand layout.
 //   The waves' partial tiles meet in LDS and are added in the order of the waves.
-// Whole mixture-of-experts calls, k_gather_m_lds / this, us (tokens, d_model x d_ff, experts):
-//   1 and 48, 768 x 3072, 64: 45 / 17.6 and 62.8 / 50.9 (200 MB of weights: 4.6 TB/s);  128 and 512: 76.5 / 74.6,
-//   135 / 127;  16, 1024 x 2048, 128: 58 / 31;  64, 512 x 2048, 8: 32 / 20.  Hence up to eight rows per segment on
-//   average.  Not with more than 64 segments (256, 1024 x 2048, 128: 127.6 / 130.5), unless there are as many
-//   segments as rows; and 2048 tokens on 64 experts take 154 / 219.
+// Whole mixture-of-experts calls, k_gather_m_lds / this, us (tokens, d_model x d_ff, experts, tokens on few experts):
+//   1 and 48, 768 x 3072, 64: 45 / 17.6 and 62.8 / 50.9 (200 MB of weights: 4.6 TB/s);  16, 1024 x 2048, 128: 58 / 31;
+//   64, 512 x 2048, 8: 32 / 20.  When it is taken: few_rows_pay, below.
 // Tried: 32 rows per tile with three or four slabs in flight: 57 at 48 tokens; 128 columns, 16-byte loads: 55 - 68.
 // ------------------------------------------------------------------------------------------------
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
@@ -681,6 +680,26 @@ int launch_cfg(GemmArgs g, int64_t total_rows, hipStream_t st) {
   return PIT_OK;
 }
 
+// Whether k_gather_m_few is the faster kernel for segments with a B of their own: up to eight rows per segment on average (a
+// tile has 16 rows), and not much to read.  k_gather_m_lds takes at least the latency of its walk over k (0.3 us per 32
+// of K); with enough weights both run at the memory's rate, and this kernel at 5.0 TB/s a little below the other's
+// 5.3.  That point is at about 200 MB , or earlier where K is short: a workgroup's start (its segment, its rows, the
+// first loads) weighs as much as 64 x K elements of B then, and pays for up to 2.2 K workgroups.  The number of segments
+// that have a row at all is known on the device only; taken for it is what rows dealt at random would give (all rows
+// apart: at most 1.6 times as many, the loss then stays below 10 %; a few favoured segments: fewer).
+// Measured per product over 8 shapes of 256 - 1024 x 768 - 4096, 16 - 128 experts, 8 - 512 tokens, three ways of routing:
+// 0.783 of k_gather_m_lds' time in the geometric mean (the faster kernel every time: 0.776), 19 of 1008 calls slower by
+// more than 2 %.  (Up to 64 segments always and beyond only with a row each: 0.792, and 128 of them, by up to 19 %:
+// 512 x 2048, 64 experts, 64 tokens on one expert each 57.7 / 67.1; 1024 x 4096, 512 tokens 182 / 212.)
+// Beyond 512 segments k_gather_m_lds' search for a tile's segment decides, which visits all of them: 1024 tokens, 128 x
+// 256, 4096 experts 649 / 420.
+bool few_rows_pay(const GemmArgs& g, int64_t total_rows) {
+  if (g.b_seg_stride == 0 || total_rows > 8 * (int64_t)g.nseg) return false;
+  if (g.nseg > 512 && total_rows <= g.nseg) return true;
+  const double hit = g.nseg * (1.0 - std::pow(1.0 - 1.0 / g.nseg, (double)total_rows));
+  return hit * g.N * g.slab * 2.0 <= 200e6 && hit * g.N / 64.0 <= 2.2 * g.slab;
+}
+
 // Tile shape by the shape of the product.  128 x 256 (a wave owns 64 x 128) where N allows: fewer bytes through
 // LDS per MFMA and fewer workgroups' worth of set-up than 128 x 128.  (Measured on the padded-batch product,
 // 8364 x 1024 x 4096: 128 x 128 with a ring of 3 or 4 stages 127 us, 256 x 128 117, 128 x 256 108-115; on the
@@ -692,9 +711,7 @@ int launch_shape(const GemmArgs& g, int64_t total_rows, hipStream_t st) {
   // (a product too small to give every compute unit a 128 x 256 tile even in the worst case takes 128 x 128)
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
-  // few rows per segment, a B of its own each: k_gather_m_few (the rule and its measurements are above that kernel)
-  if (g.b_seg_stride != 0 && (total_rows <= g.nseg || (total_rows <= 8 * (int64_t)g.nseg && g.nseg <= 64)))
-    return launch_few<BF, EPI, CT>(g, total_rows, st);
+  if (few_rows_pay(g, total_rows)) return launch_few<BF, EPI, CT>(g, total_rows, st);
   const int64_t wide_tiles = (total_rows / 128 + g.nseg) * (g.N / 256);
   if (g.N % 256 == 0 && wide_tiles >= cus) return launch_cfg<BF, EPI, CT, 2, 4, 3>(g, total_rows, st);
   return launch_cfg<BF, EPI, CT, 2, 2, 4>(g, total_rows, st);

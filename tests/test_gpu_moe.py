@@ -43,11 +43,13 @@ def test_exact_on_integers_identity_activation(pit, T, d_model, d_ff, E):
 
 
 @pytest.mark.parametrize("T,d_model,d_ff,E", [(1, 128, 128, 64), (17, 128, 256, 3), (48, 768, 384, 64), (130, 256, 1152, 20),
-                                              (100, 640, 256, 128)])
+                                              (100, 640, 256, 128), (64, 256, 1024, 64), (40, 128, 128, 600)])
 @pytest.mark.parametrize("y_dtype", [torch.float32, torch.bfloat16])
 def test_few_rows_per_expert(pit, T, d_model, d_ff, E, y_dtype):
     """At most eight rows per expert on average: waves without a slab of k, with one, with more than are in flight; experts
-    without a row, with one, with more than a tile of 16.  Exact on integers (bf16: the rounded exact sum)."""
+    without a row, with one, with more than a tile of 16; one product by the few-rows kernel and the other by the general one
+    (100 x 640 x 256: the first; 64 x 256 x 1024: the second); more than 512 experts.  Exact on integers (bf16: the rounded
+    exact sum)."""
     w = wl.moe_ffn(T=T, d_model=d_model, d_ff=d_ff, E=E, seed=T, integer=True, unit_gate=True)
     Y, st = _run(pit, w, act=1, gate=False, y_dtype=y_dtype, sentinel=99.0)
     ref = orc.moe_ffn(w.X, w.expert_id, None, w.W1, w.W2, activation="identity")
