@@ -579,11 +579,21 @@ k_slab_strip_tall(const GemmArgs g) {
   }
 }
 
-// k-slabs of a row-major A.  Tall strips where they fill the chip (two workgroups fit a compute unit), the 32-row kernel
-// for smaller products, whose time is the latency of one workgroup.  Measured (us; 32-row kernel / R = 64 / R = 128):
-//   128 x 128 tiles = 512: 52 / 35 / 30 and 47 / 43 / 41;  437: 129 / 74 / 52;  384: 81 / 70 / 91 (30 % kept), 56 / 45 / 39 (2 %)
-//   64 x 128 tiles = 512: 49 / 30 / 43, 31 / 30 / 32;  384: 31 / 36 / 56 -- but 42 / 29 / 42 with micro-tiles of 32 k, where the
-//   32-row kernel pays its read-modify-write twice as often;  256 of those: 47 / 39, 15.8 / 15.9;  128: 13.0 / 14.7
+// Which strips, by how many 128-column strips of 128 or 64 rows the product has (t128, t64) on 512 slots: two workgroups fit
+// a compute unit (one with KS = 1 and 128 rows).  A taller strip reads B less often, and a last round of them that is
+// nearly empty costs more.  Time over the 32-row kernel's, R = 64 / R = 128, as the mean over 1.5, 10 and 40 % kept
+// (the sparsity is known on the device only), in parentheses the worst of the three:
+//   64 k per visit (slabs of 64 / 128; K 768 - 3840)
+//     t128 = 432 - 504  .92 (1.0) / .74 (1.0) and .96 (1.1) / .79 (1.1)     R = 128 from 400 to 512
+//     t128 = 520 - 696  .78 - .91 / .88 - 1.01 and .88 - .96 / .93 - 1.06   R = 64; its t64 is beyond 1024
+//     t128 = 792, 1024  .85 / .77 (1.05); .75 / .52 and .90 / .83 (1.17); .83 / .56      R = 128 again (768: the same)
+//     t64 = 400 - 512   .83 - .88 (1.0) and .90 - .94 (1.1)                R = 64
+//     t64 = 520 - 600   .92 - .99 (1.1) and .98 - 1.05 (1.2)               the 32-row kernel
+//     t64 = 640 - 792   .82 - .93 (1.0) and .92 - .99 (1.2)                R = 64 for slabs of 64
+//   slabs of 32: R = 64 from t64 = 250 (.95; 264 - 510 .82 - .72; 1008 .69).  R = 128 is as good in the mean from t128 = 1024
+//     on, .58 (1.0) and .58 at 1.5 and 10 % against .62 (.69) -- and better where such micro-tiles are used, 4096^3 at 5 and
+//     10 % kept 146 and 157 us against 184 and 197, at 40 % 406 against 278; below that it is not (t128 = 520: 1.3 at 40 %).
+//   other slabs (96): R = 64 at t64 = 400 - 512 (.90 - .96) and from 820 on (.88 - 1.0); in between 1.0 - 1.1.
 template <bool BF, int KS, int R, int SG>
 int launch_slab_tall(const GemmArgs& g, hipStream_t st) {
   const dim3 grid((unsigned)(ceil_div(g.M, R) * (g.N / ST_W)));
@@ -593,12 +603,20 @@ int launch_slab_tall(const GemmArgs& g, hipStream_t st) {
 }
 template <bool BF>
 int launch_slab_strip_bf(const GemmArgs& g, hipStream_t st) {
-  const int64_t tn = g.N / ST_W, cus = compute_units();
   const int64_t strips = ceil_div(g.M, StripShape<8>::R);
   if (strips > 65535) return PIT_ESHAPE;
-  const bool wide = g.slab % 64 == 0;               // 64 k per visit
-  if (3 * ceil_div(g.M, 128) * tn >= 5 * cus) return wide ? launch_slab_tall<BF, 2, 128, 1>(g, st) : launch_slab_tall<BF, 1, 128, 2>(g, st);
-  if (ceil_div(g.M, 64) * tn >= (wide ? 2 : 1) * cus) return wide ? launch_slab_tall<BF, 2, 64, 2>(g, st) : launch_slab_tall<BF, 1, 64, 2>(g, st);
+  const int64_t tn = g.N / ST_W, slots = 2 * compute_units();
+  const int64_t t128 = ceil_div(g.M, 128) * tn, t64 = ceil_div(g.M, 64) * tn;
+  const bool t64_fill = 32 * t64 >= 25 * slots && t64 <= slots;      // one round, 400 - 512 strips
+  if (g.slab % 64 == 0) {                            // 64 k per visit
+    if (32 * t128 >= 25 * slots && (t128 <= slots || 2 * t128 > 3 * slots)) return launch_slab_tall<BF, 2, 128, 1>(g, st);
+    if (t64_fill || t64 > 2 * slots || (g.slab == 64 && 4 * t64 >= 5 * slots)) return launch_slab_tall<BF, 2, 64, 2>(g, st);
+  } else if (g.slab == 32) {
+    if (t128 >= 2 * slots) return launch_slab_tall<BF, 1, 128, 2>(g, st);
+    if (2 * t64 >= slots) return launch_slab_tall<BF, 1, 64, 2>(g, st);
+  } else if (t64_fill || 5 * t64 > 8 * slots) {
+    return launch_slab_tall<BF, 1, 64, 2>(g, st);
+  }
   // 32 x 128 strips.  (64 x 64 strips, CW = 4, halve the traffic of B and double that of A: measured 10-15 %
   // faster at 90-95 % sparsity of a 4096^3 product, 10-20 % slower at 50 % and at 99 %.)
   constexpr int CW = 8;

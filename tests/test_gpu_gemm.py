@@ -383,11 +383,12 @@ def test_microtile_wider_slab(pit):
 
 
 # strips of 64 rows (one or two k-steps per visit) and of 128 rows: last strips of 32, 56, 72 and 1 rows, more than 64 slabs,
-# three visits per slab, lists of up to two blocks, of many blocks and of every row, both types; 5 and 9 tile columns
+# three visits per slab, lists of up to two blocks, of many blocks and of every row, both types; 5, 9 and 13 tile columns
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("M,K,N,mt,p", [(2080, 96, 1024, 32, 0.5), (2040, 192, 2048, 64, 0.1), (3400, 2112, 2048, 32, 0.02),
                                         (3400, 288, 2048, 96, 0.2), (3457, 256, 2048, 128, 1.0),
-                                        (3700, 128, 1152, 64, 0.3), (6600, 64, 1152, 32, 0.3), (11000, 128, 640, 64, 0.1)])
+                                        (3000, 128, 1152, 64, 0.3), (6600, 64, 1152, 32, 0.3), (11000, 128, 640, 64, 0.1),
+                                        (4200, 64, 4096, 32, 0.3), (8900, 128, 1024, 128, 0.2), (2040, 192, 1664, 96, 0.3)])
 def test_microtile_tall_strips(pit, M, K, N, mt, p, dtype):
     w = wl.microtile_gemm(M=M, K=K, N=N, mt_k=mt, p_keep=p, seed=M + mt, integer=True)
     ref = orc.gemm(w.A, w.B)
@@ -399,7 +400,7 @@ def test_microtile_tall_strips(pit, M, K, N, mt, p, dtype):
 
 
 @pytest.mark.parametrize("M,K,N,mt,p", [(2048, 2048, 1024, 32, 0.5), (2048, 2048, 2048, 64, 0.5),        # strips of 64 rows
-                                        (3456, 2048, 2176, 32, 0.5), (3456, 2048, 2176, 32, 0.1),       # of 128 rows, 32 k
+                                        (4096, 1024, 4096, 32, 0.5), (4096, 1024, 4096, 32, 0.1),       # of 128 rows, 32 k
                                         (3456, 2048, 2176, 64, 0.5), (3456, 2048, 2176, 64, 0.1), (3456, 2048, 2176, 128, 0.2)])
 def test_microtile_tall_strips_round_no_more_than_the_others(pit, M, K, N, mt, p):
     """A product that fills the chip with tall strips and its slices of 128 columns, which the 32-row kernel takes with four
