@@ -169,6 +169,61 @@ def test_gather_k_tile_heights_and_waves(pit, tiles_m, tiles_n, mt):
     test_gather_k_more_tiles_than_compute_units(pit, tiles_m, tiles_n, mt)
 
 
+# a product for every form of the kernel (waves per tile, rows of a tile), by the number of tiles on 256 compute units
+FORMS = {(4, 32): (256, 256, 128), (4, 64): (1152, 1024, 128), (4, 128): (2176, 2048, 128), (2, 128): (4224, 2048, 128),
+         (2, 64): (2176, 2048, 64), (1, 64): (8448, 2048, 64), (2, 32): (1152, 1024, 32), (1, 32): (4224, 2048, 32)}
+
+
+@pytest.mark.parametrize("in_dtype,c_dtype", [(torch.bfloat16, torch.float32), (torch.bfloat16, torch.bfloat16),
+                                              (torch.float16, torch.float32), (torch.float16, torch.float16)])
+@pytest.mark.parametrize("form", FORMS)
+def test_gather_k_every_form(pit, form, in_dtype, c_dtype):
+    """Each form with both input types and both kinds of result, lists of every length around the slabs' boundaries (waves
+    without work, with one slab, with a partial last one, odd and even numbers of slabs; empty lists), operands and
+    result with row pitches beyond their rows: NaN beyond the operands, a sentinel beyond the result.  Exact on integers
+    (16-bit results: the rounded exact sum).  The dense mode on the same operands, too."""
+    M, N, mt = FORMS[form]
+    K = 300
+    lengths = [0, 1, 2, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 161, 193, 224, 255, 257, 300]
+    g = np.random.default_rng(M + N + mt)
+    Xt = np.zeros((K, M), dtype=np.float32)
+    for s in range(M // mt):
+        live = lengths[(5 * s + 3) % len(lengths)]
+        rows = g.choice(K, size=live, replace=False)
+        Xt[rows, mt * s:mt * (s + 1)] = g.integers(-2, 3, size=(live, mt))
+        Xt[rows, mt * s] = 1.0                                            # keep the listed rows non-zero
+    W = g.integers(-2, 3, size=(K, N)).astype(np.float32)
+    ref = torch.from_numpy(Xt.T.astype(np.float64) @ W.astype(np.float64)).to(c_dtype)
+    bigX, bigW = (torch.full((K, n), float("nan"), dtype=in_dtype, device=dev()) for n in (M + 64, N + 128))
+    bigX[:, :M] = torch.from_numpy(Xt).to(in_dtype)
+    bigW[:, :N] = torch.from_numpy(W).to(in_dtype)
+    X, B = bigX[:, :M], bigW[:, :N]
+    ix = pit.pit_build_index(X, 1, mt, 0)
+    for mode, index in ((pit.PIT_GEMM_GATHER_K, ix), (pit.PIT_GEMM_DENSE_K, None)):
+        C = torch.full((M, N + 32), 9.0, dtype=c_dtype, device=dev())
+        pit.pit_sread_gemm(mode, X, B, index, mt, M, N, K, out=C[:, :N])
+        torch.cuda.synchronize()
+        assert torch.equal(C[:, :N].cpu(), ref), mode
+        assert bool((C[:, N:] == 9.0).all())
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_gather_k_every_form_large_last_row(pit, form):
+    """The last listed row holds the largest finite values: positions past the end of a list re-read it and must add
+    nothing."""
+    M, N, mt = FORMS[form]
+    K = 203
+    g = torch.Generator(device="cuda").manual_seed(M)
+    X = torch.randint(-2, 3, (K, M), generator=g, device="cuda").float() * (torch.rand((K, M), generator=g, device="cuda") < 0.3)
+    X[K - 1] = 3.0e38
+    W = torch.randint(-2, 3, (K, N), generator=g, device="cuda").float()
+    W[K - 1] = 1.0
+    X, W = X.to(torch.bfloat16), W.to(torch.bfloat16)
+    ix = pit.pit_build_index(X, 1, mt, 0)
+    C = pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_K, X, W, ix, mt, M, N, K)
+    assert torch.equal(C, X[K - 1].float()[:, None].expand(M, N))          # the other rows' sums are far below half a unit
+
+
 @pytest.mark.parametrize("M,K,mt", [(4224, 1300, 32), (8448, 1300, 64)])
 def test_gather_k_one_wave_rounds_no_more_than_two(pit, M, K, mt):
     """From eight tiles per compute unit on a wave works alone on a tile.  It adds in two chains, like the two waves that
@@ -397,6 +452,35 @@ def test_microtile_tall_strips(pit, M, K, N, mt, p, dtype):
     ix = pit.pit_build_index(A, 1, mt, 0)
     pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, A, B, ix, mt, M, N, K, out=C)
     assert np.array_equal(C.cpu().numpy().astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("M,K,N,mt", [(2040, 512, 1024, 32), (1700, 512, 2048, 64), (4000, 192, 4096, 32), (3500, 256, 2048, 64)])
+def test_microtile_tall_strips_clustered_strided_reproducible(pit, M, K, N, mt, dtype):
+    """Strips of 64 and of 128 rows, 32 and 64 k per visit: live micro-tiles bunched in row ranges (long runs in some strips,
+    none in most, one slab without any, the last row everywhere), pitches beyond the rows with NaN beyond the operands
+    and a sentinel beyond the result; exact on integers, the same bits twice."""
+    g = np.random.default_rng(M + mt)
+    keep = np.zeros((M, K // mt), dtype=bool)
+    for s in range(K // mt):
+        start = int(g.integers(0, M - 400))
+        keep[start:start + int(g.integers(1, 400)), s] = True
+        keep[g.integers(0, M, size=20), s] = True
+    keep[M - 1, :] = True
+    keep[:, 2] = False
+    A = (g.integers(-4, 5, size=(M, K)).reshape(M, K // mt, mt) * keep[:, :, None]).reshape(M, K).astype(np.float32)
+    B = g.integers(-4, 5, size=(K, N)).astype(np.float32)
+    bigA, bigB = (torch.full(s, float("nan"), dtype=dtype, device=dev()) for s in ((M, K + 64), (K, N + 128)))
+    bigA[:, :K] = torch.from_numpy(A).to(dtype)
+    bigB[:, :N] = torch.from_numpy(B).to(dtype)
+    ix = pit.pit_build_index(bigA[:, :K], 1, mt, 0)
+    ref = torch.from_numpy((A.astype(np.float64) @ B.astype(np.float64)).astype(np.float32))
+    for _ in range(2):
+        C = torch.full((M, N + 32), -7.0, device=dev())
+        pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, bigA[:, :K], bigB[:, :N], ix, mt, M, N, K, out=C[:, :N])
+        torch.cuda.synchronize()
+        assert torch.equal(C[:, :N].cpu(), ref)
+        assert bool((C[:, N:] == -7.0).all())
 
 
 @pytest.mark.parametrize("M,K,N,mt,p", [(2048, 2048, 1024, 32, 0.5), (2048, 2048, 2048, 64, 0.5),        # strips of 64 rows

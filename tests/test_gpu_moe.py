@@ -59,6 +59,39 @@ def test_few_rows_per_expert(pit, T, d_model, d_ff, E, y_dtype):
     assert np.array_equal(Y.double().cpu().numpy(), ref)
 
 
+@pytest.mark.parametrize("T,d_model,d_ff,E", [(48, 256, 512, 64), (17, 128, 256, 3), (100, 256, 256, 128)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_few_rows_gelu_and_gate(pit, T, d_model, d_ff, E, dtype):
+    """A decode step as it is used: GELU, gate, both input types and both kinds of result; every token's row against the
+    oracle (a gate read for the wrong row would change one row only)."""
+    w = wl.moe_ffn(T=T, d_model=d_model, d_ff=d_ff, E=E, seed=T)
+    X, W1, W2 = (orc.bf16_bits_to_f64(a).astype(np.float16 if dtype == torch.float16 else np.float32) for a in (w.X, w.W1, w.W2))
+    tX, tW1, tW2 = (to_dev(a).to(dtype) for a in (X, W1, W2))
+    gate = np.random.default_rng(T).uniform(0.1, 2.0, size=T).astype(np.float32)
+    ref = orc.moe_ffn(X, w.expert_id, gate, W1, W2, round_hidden=False)
+    for y_dtype in (torch.float32, dtype):
+        Y = pit.pit_moe_dispatch_gemm(tX, to_dev(w.expert_id), to_dev(gate), tW1, tW2, out=torch.full((T, d_model), 7.0, dtype=y_dtype, device=dev()))
+        got = Y.double().cpu().numpy()
+        err = np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)
+        # the hidden row and, where it is 16 bits wide, the result are rounded to `dtype`: unit roundoff 2^-8 or 2^-11,
+        # about 0.42 of it rms for each of the two over a row; twice that
+        assert float(err.max()) <= 2 * 0.42 * 2 ** 0.5 * (2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -11), float(err.max())
+
+
+@pytest.mark.parametrize("bad", ["some", "all"])
+def test_few_rows_invalid_expert_ids(pit, bad):
+    """Tokens without an expert are listed nowhere: fewer tiles than the grid holds, or none; their rows come out zero."""
+    w = wl.moe_ffn(T=48, d_model=256, d_ff=384, E=64, seed=8, integer=True, unit_gate=True)
+    lost = np.zeros(48, dtype=bool)
+    lost[slice(None) if bad == "all" else [0, 7, 8, 47]] = True
+    w.expert_id[lost] = np.where(np.arange(lost.sum()) % 2 == 0, 64, -1)
+    Y, st = _run(pit, w, act=1, gate=False, sentinel=5.0)
+    assert st == lost.sum()
+    ref = orc.moe_ffn(w.X, np.where(lost, 0, w.expert_id), None, w.W1, w.W2, activation="identity")
+    got = Y.cpu().numpy().astype(np.float64)
+    assert np.array_equal(got[~lost], ref[~lost]) and np.all(got[lost] == 0)
+
+
 @pytest.mark.parametrize("T,E", [(512, 8), (777, 3)])
 def test_gelu_and_gate(pit, T, E):
     w = wl.moe_ffn(T=T, d_model=256, d_ff=512, E=E, seed=E)
