@@ -545,7 +545,8 @@ static int launch_gather_k_tile(const GemmArgs& g, int resident, hipStream_t st)
 //     tiles: two waves, and from eight tiles per compute unit on one wave, without a reduction (4096^3, two waves / one:
 //     32 rows at 10 % 48.5 / 47.3, at 50 % 171 / 147; 64 rows at 10 % 53.6 / 49.5, at 50 % 88.6 / 89.0; with four tiles
 //     per compute unit and lists of 200 entries, 32 rows, 10.1 / 11.2; measured with one chain of additions: the second
-//     adds 0 - 0.5 us to the 32-row, 0.6 - 1.5 to the 64-row products).
+//     adds 0 - 0.5 us to the 32-row, 0.6 - 1.5 to the 64-row products; the most seen: 64 rows, 4096^3, live in
+//     runs of 32 at 10 %, 42.6 -> 46.4).
 template <bool BF, int CT>
 static int launch_gather_k(const GemmArgs& g, int tm_tiles, hipStream_t st) {
   const int64_t cus = compute_units(), tn = g.N / TN;

@@ -302,10 +302,11 @@ k_slab_strip(const GemmArgs g) {
 //   k-row), transposed inside the lane: MFMA x of a block works on the columns {4 q + x}.
 //   strip in LDS: [wave][row][64 columns]; a lane moves its four columns of a row as 16 bytes and the 16 lanes
 //   of a row lie side by side (no bank conflicts).  A spare row swallows the results of a block's unused rows.
-// Bound by the vector-load path: per slab and strip 16 KB of B and 2 x 2 KB of A at 40 bytes per clock and CU are about
-// 500 clocks, the LDS read-modify-write of C 220, the issue of a wave's 170 instructions 700 (four waves per CU: the
-// strips fill the LDS); they overlap in part, about 850 are measured.  4096^3, 1 x 64 micro-tiles, 10 % kept: 231 ->
-// 112 us (50 %: 363 -> 267, 1 %: 112 -> 78; 1 x 32, 10 %: 339 -> 156; the launch without its slab loop: 18 us).
+// Bound by the vector L1 (rocprofv3, 4096^3, 1 x 64, 10 % kept): a visit takes 1900 clocks, in which a wave issues 105 vector,
+// 14 LDS and 20 load instructions (430, 140 and 200 clocks of issue); a load of B is 20 accesses for 512 bytes, the L1
+// serves 0.74 accesses per clock, its address unit is busy 69 % of the time, the matrix pipe 7 %.  One wave per SIMD:
+// the strips fill the LDS.  4096^3, 1 x 64 micro-tiles, 10 % kept: 231 -> 111 us (50 %: 363 -> 267, 1 %: 112 -> 76; 1 x 32,
+// 10 %: 339 -> 156; the launch without its slab loop: 18 us).
 // Tried: waves of 32 columns, eight per CU (twice the load instructions: 121 us), R = 256 with four waves per CU (114),
 // four chains in 64-row strips, one workgroup of eight waves per CU (205: B is read twice as often).
 // ------------------------------------------------------------------------------------------------
