@@ -6,7 +6,7 @@
 //      listed key a 32-bit word saying which of the 32 queries do.  It is built in one launch
 //      (k_mask_index_q32: the lists sit at fixed places, one workgroup per query block), or by
 //      pit_build_index when the mask cannot be read 16 bytes at a time.
-//   2. One workgroup per (query block, head); its 4 wavefronts take the key list in chunks of 32
+//   2. One workgroup per (query block, head); its 4 (or 2) wavefronts take the key list in chunks of 32
 //      keys, round-robin, each with its own running softmax state, merged at the end.  A wave's
 //      loop has no workgroup barrier and keeps the loads of its next chunk (and the list entries
 //      of the one after) in flight while it computes.
@@ -27,6 +27,10 @@
 // and P enters as the sum of two bf16 terms, P = hi + lo with hi = P rounded to bf16 and lo = the
 // exact fp32 remainder rounded to bf16 (relative error of the pair below 2^-17), in 8 MFMAs per chunk
 // that share their V operands.
+// The error of P is smallest where P is exactly 1: at the largest score of each chain of chunks, i.e. once per wave and query.
+// With two waves instead of four that alone makes the result's error 5 % larger; there one in eight keys of a chunk takes the
+// next term of its P as well (2 more MFMAs per chunk), and the error is 1 - 2 % below that of four waves (12 x 4096, window
+// 256: 1.900e-6 with four, 2.007e-6 with two, 1.875e-6 with the term; fp16 inputs, 10 heads, window 512: 1.693e-4, 1.663e-4).
 #include "pit_common.hpp"
 
 namespace pit {
@@ -65,6 +69,15 @@ __device__ __forceinline__ void split_bf16x2(float a, float b, uint32_t& hi2, ui
   const f32x2_t r = {a - __builtin_bit_cast(float, hi2 << 16), b - __builtin_bit_cast(float, hi2 & 0xFFFF0000u)};
   lo2 = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2_t));
 }
+// what the pair's 16-bit terms leave of {a, b} (exact in fp32), rounded to the same type
+__device__ __forceinline__ uint32_t rest_bf16x2(float a, float b, uint32_t hi2, uint32_t lo2) {
+  const f32x2_t r = {(a - __builtin_bit_cast(float, hi2 << 16)) - __builtin_bit_cast(float, lo2 << 16),
+                     (b - __builtin_bit_cast(float, hi2 & 0xFFFF0000u)) - __builtin_bit_cast(float, lo2 & 0xFFFF0000u)};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2_t));
+}
+__device__ __forceinline__ uint32_t rest_f16x2(float a, float b, uint32_t h2) {
+  return pack_f16x2(a - (float)__builtin_bit_cast(_Float16, (uint16_t)h2), b - (float)__builtin_bit_cast(_Float16, (uint16_t)(h2 >> 16)));
+}
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   uint32_t u = __builtin_bit_cast(uint32_t, f);
   if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0;
@@ -100,18 +113,18 @@ __device__ __forceinline__ uint32_t v_off(int r, int c16) {
   return (uint32_t)(r * 128 + ((((c16 >> 2) ^ ((r >> 1) & 1)) << 6) | ((c16 & 3) << 4)));
 }
 
-// OT: 0 = fp32, 1 = bf16, 2 = fp16 output
-template <bool BF, int OT>
-__global__ void __launch_bounds__(256, 3)
+// OT: 0 = fp32, 1 = bf16, 2 = fp16 output; NW waves per workgroup (the rule is at the launch)
+template <bool BF, int OT, int NW>
+__global__ void __launch_bounds__(64 * NW, 3)
 k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
               const int32_t* __restrict__ seg_ptr, const int32_t* __restrict__ idx, const uint32_t* __restrict__ bits,
               int list_stride, void* __restrict__ O, int S, float scale_log2e) {
   // per wave (private): two V tiles and one K tile of 4 KiB; after the loop the first 8 KiB carry the
   // wave's partial output to wave 0 (32 floats per lane, laid out [value][lane])
-  __shared__ __attribute__((aligned(1024))) char s_kv[4][3 * V_TILE_BYTES];
+  __shared__ __attribute__((aligned(1024))) char s_kv[NW][3 * V_TILE_BYTES];
   // per wave, for two chunks: the 32 listed keys, then their 32 occupancy words
-  __shared__ __attribute__((aligned(256))) uint32_t s_list[4][2][2 * KC];
-  __shared__ float s_ml[3][2][64];
+  __shared__ __attribute__((aligned(256))) uint32_t s_list[NW][2][2 * KC];
+  __shared__ float s_ml[NW - 1][2][64];
 
   // Consecutive workgroup ids go to different XCDs (8, each with its own L2): renumber so that an XCD
   // works on a contiguous run of (head, query block) pairs, i.e. on the K and V of one or two heads
@@ -152,10 +165,10 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   const char* k_head = reinterpret_cast<const char*>(K + head_off);
   const char* v_head = reinterpret_cast<const char*>(V + head_off);
 
-  // This wave's chunks are wv, wv + 4, ...  The tiles and the mask words in LDS are private to the wave, so
+  // This wave's chunks are wv, wv + NW, ...  The tiles and the mask words in LDS are private to the wave, so
   // the loop needs no workgroup barrier, and it is software-pipelined: while chunk i is computed, the list
   // entries of chunk i + 2 and the K and V rows of chunk i + 1 are under way.
-  const int my_chunks = nchunks > wv ? (nchunks - wv + 3) >> 2 : 0;
+  const int my_chunks = nchunks > wv ? (nchunks - wv + NW - 1) / NW : 0;
   // SRead.  The K and V rows of a chunk (32 x 128 B each) travel global -> LDS directly, 8 lanes x 16 B per
   // row, so that every 128-byte line is requested once; the place of a 16-byte piece inside its row of the
   // tile (the bank swizzle) is expressed by which piece of the source row a lane asks for.
@@ -165,7 +178,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   // nothing.  (The loop only runs when the list is not empty.)
   const uint32_t my_row = (uint32_t)(lane >> 3), my_slot = (uint32_t)(lane & 7);
   auto key_request = [&](int i, int slot) {                          // issue only
-    const int kk = (wv + 4 * i) * KC + ql;
+    const int kk = (wv + NW * i) * KC + ql;
     const uint32_t pos = (uint32_t)(list_begin + min(kk, list_len - 1)) * 4u;
     const uint32_t at = (uint32_t)(uintptr_t)(PIT_LDS char*)&s_list[wv][slot][0];
     if (lane < KC) {
@@ -175,7 +188,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   };
   // (after the entries have landed) positions past the end of the list get an occupancy word of zero
   auto key_finish = [&](int i, int slot) {
-    if (!(i < my_chunks && (wv + 4 * i) * KC + ql < list_len)) s_list[wv][slot][KC + ql] = 0u;
+    if (!(i < my_chunks && (wv + NW * i) * KC + ql < list_len)) s_list[wv][slot][KC + ql] = 0u;
     __builtin_amdgcn_wave_barrier();
   };
   // byte offset of this lane's row of the key tile, instruction `it` (tile rows 8 it + lane / 8)
@@ -276,18 +289,25 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
       // O^T += V'^T . P^T ; k-step t covers chunk keys 16t .. 16t+15 in the order the accumulator holds them
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        uint4 pb, pl = make_uint4(0, 0, 0, 0);
+        uint4 pb, pl = make_uint4(0, 0, 0, 0), px = make_uint4(0, 0, 0, 0);
+        constexpr bool MORE = NW == 2;
         if constexpr (BF) {
           uint32_t hi2[4], lo2[4];
 #pragma unroll
           for (int x = 0; x < 4; ++x) split_bf16x2(st[8 * t + 2 * x], st[8 * t + 2 * x + 1], hi2[x], lo2[x]);
           pb = make_uint4(hi2[0], hi2[1], hi2[2], hi2[3]);
           pl = make_uint4(lo2[0], lo2[1], lo2[2], lo2[3]);
+          if constexpr (MORE) {
+            if (t == 0) px.x = rest_bf16x2(st[0], st[1], hi2[0], lo2[0]);
+          }
         } else {
           pb.x = pack_f16x2(st[8 * t + 0], st[8 * t + 1]);
           pb.y = pack_f16x2(st[8 * t + 2], st[8 * t + 3]);
           pb.z = pack_f16x2(st[8 * t + 4], st[8 * t + 5]);
           pb.w = pack_f16x2(st[8 * t + 6], st[8 * t + 7]);
+          if constexpr (MORE) {
+            if (t == 0) px.x = rest_f16x2(st[0], st[1], pb.x);
+          }
         }
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt) {
@@ -301,6 +321,9 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
           const uint4 vt = make_uint4(lo.x, lo.y, hi.x, hi.y);
           o[dt] = mfma_in<BF>(vt, pb, o[dt]);
           if constexpr (BF) o[dt] = mfma_in<BF>(vt, pl, o[dt]);
+          if constexpr (MORE) {
+            if (t == 0) o[dt] = mfma_in<BF>(vt, px, o[dt]);
+          }
         }
       }
     }
@@ -314,7 +337,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   wait_loads();
   wait_lds();
 
-  // merge the 4 wavefronts' partial (m, l, O) per lane; wave 0 finishes
+  // merge the wavefronts' partial (m, l, O) per lane; wave 0 finishes
   if (wv > 0) {
     float* dst = reinterpret_cast<float*>(s_kv[wv]);      // this wave's own tiles: nobody else reads them
     s_ml[wv - 1][0][lane] = m_run;
@@ -328,7 +351,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   if (wv != 0) return;
   float m_all = m_run;
 #pragma unroll
-  for (int w = 0; w < 3; ++w) m_all = fmaxf(m_all, s_ml[w][0][lane]);
+  for (int w = 0; w < NW - 1; ++w) m_all = fmaxf(m_all, s_ml[w][0][lane]);
   const float m_safe = m_all == -INFINITY ? 0.f : m_all;
   float a = exp2f(m_run - m_safe);
   float l_all = l_run * a;
@@ -337,7 +360,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[t][e] *= a;
 #pragma unroll
-  for (int w = 0; w < 3; ++w) {
+  for (int w = 0; w < NW - 1; ++w) {
     const float* src = reinterpret_cast<const float*>(s_kv[w + 1]);
     a = exp2f(s_ml[w][0][lane] - m_safe);
     l_all += s_ml[w][1][lane] * a;
@@ -532,8 +555,19 @@ extern "C" int pit_sparse_attn(const void* d_Q, const void* d_K, const void* d_V
   const uint16_t* k = reinterpret_cast<const uint16_t*>(d_K);
   const uint16_t* v = reinterpret_cast<const uint16_t*>(d_V);
   dim3 grid((unsigned)L.nseg, (unsigned)H);
-#define PIT_ATTN_LAUNCH(BF, OT) \
-  hipLaunchKernelGGL((k_sparse_attn<BF, OT>), grid, dim3(256), 0, st, q, k, v, ix.seg_ptr, ix.idx, ix.bits, list_stride, d_O, S, c)
+  // Waves per query block.  12 waves of this kernel fit a compute unit: three blocks of four waves, six of two.  Two where
+  // that makes one round of what four make two: each wave then has twice the chunks behind its start, and half as many
+  // partial results are merged.  us a call, four / two waves: 12 heads, S = 4096, window 256 and 5 % of the columns (1536 blocks
+  // on 256 compute units) 30.9 / 29.1; 7 heads, window 64 and 2 %, 19.0 / 15.7; 16 heads, S = 1600, window 64, 14.5 / 12.0.
+  // With fewer blocks four waves are faster (768: 19.4 / 21.1; 512: 16.7 / 20.6), and with more than one round of two-wave
+  // blocks (14 heads, window 512 and 10 %: 48.8 / 53.4).  Between four and five blocks per compute unit the four-wave
+  // blocks' second round is the emptier one, and long lists are faster that way (9 heads, window 512 and 10 %: 37.6 / 39.0).
+  const int64_t blocks = (int64_t)L.nseg * H, cus = compute_units();
+  const bool two = (blocks > 3 * cus && blocks <= 4 * cus) || (blocks >= 5 * cus && blocks <= 6 * cus);
+#define PIT_ATTN_LAUNCH(BF, OT) do { \
+    if (two) hipLaunchKernelGGL((k_sparse_attn<BF, OT, 2>), grid, dim3(128), 0, st, q, k, v, ix.seg_ptr, ix.idx, ix.bits, list_stride, d_O, S, c); \
+    else     hipLaunchKernelGGL((k_sparse_attn<BF, OT, 4>), grid, dim3(256), 0, st, q, k, v, ix.seg_ptr, ix.idx, ix.bits, list_stride, d_O, S, c); \
+  } while (0)
   const int ot = o_dt == PIT_F32 ? 0 : (o_dt == PIT_BF16 ? 1 : 2);
   if (in_dt == PIT_BF16) {
     if (ot == 0) PIT_ATTN_LAUNCH(true, 0); else if (ot == 1) PIT_ATTN_LAUNCH(true, 1); else PIT_ATTN_LAUNCH(true, 2);

@@ -36,6 +36,14 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 constexpr int kWave = 64;
 
+// compute units of the current device rounded down to a multiple of 8 (one share per XCD)
+inline int compute_units() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
+  return n & ~7;
+}
+
 // pit_build_route_index that also clears, in `zero_rows` (row pitch zero_ld_bytes, zero_row_bytes per row, both
 // multiples of 16), the rows of the tokens whose expert id is out of range (zero_rows == nullptr: nothing cleared).
 int launch_route_index(const int32_t* d_expert_id, int T, int E, const pit_index* out, int32_t* d_status,

@@ -49,12 +49,4 @@ int launch_zero_rows(void* C, int64_t ld_bytes, int M, int64_t row_bytes, hipStr
 // GATHER_M with several k-slabs per row (pit_slab.hip); fp32 results
 int launch_slab_strip(bool bf, const GemmArgs& g, hipStream_t st);
 
-// compute units of the current device rounded down to a multiple of 8 (one share per XCD)
-inline int compute_units() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 256;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8) n = 256;
-  return n & ~7;
-}
-
 }  // namespace pit

@@ -146,3 +146,34 @@ def test_mask_at_an_odd_address_takes_the_general_index_build(pit):
     torch.cuda.synchronize()
     assert_close(O_odd, orc.sparse_attn(w.Q, w.K, w.V, w.mask, w.scale), "sparse_attn, mask at an odd address")
     assert torch.equal(O_odd, O_al)
+
+
+# query blocks per compute unit on either side of each line between two and four waves per block, in heads of 8 blocks
+@pytest.mark.parametrize("per_cu,more", [(3, 0), (3, 1), (4, 0), (4, 1), (5, -1), (5, 0), (6, 0), (6, 1)])
+@pytest.mark.parametrize("in_dtype", [torch.bfloat16, torch.float16])
+def test_two_and_four_waves_per_query_block(pit, per_cu, more, in_dtype):
+    """Lists of no chunk, of fewer chunks than waves, and longer ones; all heads against the oracle (they repeat in eights), every
+    output type against the four-wave kernel, and the two-wave kernel's error no larger than the four-wave kernel's."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count & ~7
+    S, H = 256, per_cu * cus // 8 + more
+    w = wl.sparse_attn(H=8, S=S, window=16, density=0.05, seed=H)
+    m = w.mask.copy()
+    m[32:96] = 0                              # a block without keys
+    m[70, 5] = 1                              # .. and one with a single key
+    m[128:160, :200] = 1                      # seven chunks
+    q, k, v = (orc.bf16_bits_to_f64(x).astype(np.float16) if in_dtype == torch.float16 else x for x in (w.Q, w.K, w.V))
+    ref = orc.sparse_attn(q, k, v, m, w.scale)
+    Q, K, V = (to_dev(x).repeat(-(-H // 8), 1, 1)[:H].contiguous() for x in (q, k, v))
+    run = lambda n, dt: pit.pit_sparse_attn(Q[:n].contiguous(), K[:n].contiguous(), V[:n].contiguous(), to_dev(m), w.scale, o_dtype=dt)
+    O, few = run(H, torch.float32), run(8, torch.float32)                 # (8 heads: four waves)
+    assert_close(O, ref[np.arange(H) % 8], "all heads")
+    err = [np.linalg.norm(x.cpu().numpy().astype(np.float64) - ref) for x in (O[:8], few)]
+    assert err[0] <= 1.005 * err[1]
+    # the two kernels' P differ by the rounding of P (2^-17, 2^-11), their 16-bit outputs by one rounding more
+    p = 2.0 ** -15 if in_dtype == torch.bfloat16 else 2.0 ** -9
+    for dt, tol in ((torch.float32, p), (torch.bfloat16, p + 2.0 ** -7), (torch.float16, p + 2.0 ** -10)):
+        O, few = run(H, dt).float(), run(8, dt).float()
+        scale = torch.maximum(few.abs(), few.square().mean().sqrt())
+        for h0 in range(0, H, 8):
+            n = min(8, H - h0)
+            assert float(((O[h0:h0 + n] - few[:n]).abs() / scale[:n]).max()) <= tol
