@@ -1,5 +1,6 @@
 """The erf approximation of the GELU epilogue (paper_2301_10936_amd/csrc/pit_gemm_dev.hpp, gelu_erf_fast), evaluated
-here in numpy float32 with the constants of the kernel, against scipy's erf: the bound the kernel's comment states."""
+here in numpy float32 with the constants of the kernel, against scipy's erf: the bound the kernel's comment states.  The kernel
+evaluates x / 2 + |x| (1/2 - 2^-(q + 1)) with q as a polynomial in |x|; the first test pins q itself."""
 import numpy as np
 from scipy.special import erf
 
@@ -32,3 +33,36 @@ def test_erf_error_bound_and_tails():
     assert t[0] == np.float32(1e3) and t[1] == np.float32(1e6) and np.all(t[2:] == 0.0)
     _, n = gelu_kernel_formula(np.array([np.nan]))
     assert np.isnan(n[0])
+
+
+D = np.array([1.151091337, 0.4592546821, 0.05256123468, -0.007397509646, 0.0005204583285], dtype=np.float32)
+
+
+def _fma(a, b, c):
+    return (a.astype(np.float64) * np.float64(b) + np.float64(c)).astype(np.float32)
+
+
+def gelu_kernel(x):
+    x = x.astype(np.float32)
+    with np.errstate(over="ignore", invalid="ignore", under="ignore"):
+        a = np.abs(x)
+        p = np.full_like(a, D[4])
+        for c in (D[3], D[2], D[1], D[0], np.float32(1)):
+            p = _fma(p, a, c)
+        h = np.exp2(-p.astype(np.float64)).astype(np.float32)
+        h[h < 2.0 ** -126] = 0.0
+        return _fma(a, np.float32(0.5) - h, np.float32(0.5) * x)
+
+
+def test_gelu_in_the_form_of_the_kernel():
+    assert np.allclose(D, C.astype(np.float64) * 0.5 ** (np.arange(1, 6) / 2.0), rtol=1e-7)
+    g = np.random.default_rng(1)
+    for scale in (0.3, 1.0, 3.0, 10.0):
+        x = (g.standard_normal(1 << 18) * scale).astype(np.float32)
+        exact = 0.5 * x.astype(np.float64) * (1.0 + erf(x.astype(np.float64) / np.sqrt(2.0)))
+        now, before = gelu_kernel(x) - exact, gelu_kernel_formula(x)[1] - exact
+        assert np.abs(now).max() <= 3e-6
+        assert np.linalg.norm(now) <= np.linalg.norm(before)          # no larger than in the form it replaces
+    t = gelu_kernel(np.array([1e3, 1e6, np.inf, -9.0, -50.0, -1e4, -1e30, 0.0, -0.0]))
+    assert t[0] == np.float32(1e3) and t[1] == np.float32(1e6) and t[2] == np.inf and np.all(t[3:] == 0.0)
+    assert np.all(np.isnan(gelu_kernel(np.array([np.nan, -np.inf]))))  # (-inf: -inf * 0, as in x (1 + erf))
