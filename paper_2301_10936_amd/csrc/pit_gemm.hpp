@@ -39,12 +39,17 @@ struct GemmArgs {
   int zero_rest;     // GATHER_M, one segment: 1 = the rows of C that the list does not name are set to zero by the
                      // workgroups of the grid that have no tile
   int stream_c;      // GATHER_M, set by the launcher: 1 = C is written by streaming stores
+  // Mixture of experts without an index (both products: gather_m_routes): expert ids of the M <= 64 tokens; rows of A and C are
+  // tokens.  route_rest: count the tokens without an expert in *status (if given) and clear their rows of C.
+  const int32_t* route; int32_t* status; int route_rest;
 };
 
 // Host-side launchers shared by pit_sread_gemm and pit_moe_dispatch_gemm.
 // GATHER_M with operands staged through LDS by direct loads (pit_gemm_m.hip).  total_rows = upper bound of the
 // number of listed rows over all segments (the grid is sized for the worst case; the counts stay on the device).
 int launch_gather_m(bool bf, int epi, int c_is_in_type, const GemmArgs& g, int64_t total_rows, hipStream_t st);
+// Whether a product with a B per segment takes a kernel that can do without the index (then g.route may be set).
+bool gather_m_routes(const GemmArgs& g);
 int launch_zero_rows(void* C, int64_t ld_bytes, int M, int64_t row_bytes, hipStream_t st);
 // GATHER_M with several k-slabs per row (pit_slab.hip); fp32 results
 int launch_slab_strip(bool bf, const GemmArgs& g, hipStream_t st);

@@ -501,7 +501,14 @@ __device__ __forceinline__ f32x4_t mfma16x16(const u32x4_t& a, const u32x4_t& b,
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
 }
 
-template <bool BF, int EPI, int CT>
+// ROUTE (at most 64 tokens): no index.  A wave holds all expert ids, one per lane; ballots over their bits give every lane the
+// lanes with its expert, the first lane of each expert stands for it, and the scan of their numbers of row tiles says which
+// expert this tile belongs to (experts in the order of their first token: any order will do).  Hidden rows lie in token order.
+// What the index kernel does besides is done by the second product: tokens without an expert are counted and their rows of C
+// cleared, by the workgroups of row tile 0.  A call is two launches instead of three and a tile's rows are known after one
+// round trip instead of two.  Whole calls, us, with an index / this: 768 x 3072, 64 experts, 1 token 16.9 / 14.5, 48 tokens 37.5 /
+// 36.1; 512 x 2048, 128 experts (an index of two launches), 1 token 21.3 / 12.7.
+template <bool BF, int EPI, int CT, bool ROUTE>
 __global__ void __launch_bounds__(512, 4)
 k_gather_m_few(const GemmArgs g) {
   constexpr int CW = 4, NB = 1, DEPTH = 4;               // columns of a lane, blocks of 16 rows, slabs in flight
@@ -514,28 +521,67 @@ k_gather_m_few(const GemmArgs g) {
 
   // the tile: row tile blockIdx.y of all segments' row tiles (the grid holds the worst case), columns n0 ..
   int seg = -1, begin = 0, cnt = 0, base = 0;
+  int rows = 0;                                          // ROUTE: lane r holds the token of the tile's row r
   const int tile = blockIdx.y;
-  for (int s0 = 0; s0 < g.nseg; s0 += 64) {
-    const int s = s0 + lane;
-    int beg = 0, c = 0;
-    if (s < g.nseg) { beg = g.seg_ptr[s]; c = g.seg_ptr[s + 1] - beg; }
-    const int nt = (c + R - 1) / R;
+  if constexpr (ROUTE) {
+    const int e = lane < g.M ? g.route[lane] : -1;
+    const bool valid = e >= 0 && e < g.nseg;
+    unsigned long long same = __ballot(valid);
+    for (int bit = 0; (g.nseg - 1) >> bit; ++bit) {
+      const bool on = (e >> bit) & 1;
+      const unsigned long long b = __ballot(on);
+      same &= on ? b : ~b;
+    }
+    const int rank = __builtin_popcountll(same & ((1ull << lane) - 1ull));
+    const int nt = valid && rank == 0 ? (__builtin_popcountll(same) + R - 1) / R : 0;
     int inc = nt;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
       const int t = __shfl_up(inc, d);
       if (lane >= d) inc += t;
     }
-    const unsigned long long hit = __ballot(base + inc > tile);
+    if (g.route_rest && tile == 0) {
+      unsigned long long bad = __ballot(lane < g.M && !valid);
+      if (blockIdx.x == 0 && tid == 0 && g.status != nullptr) *g.status = __builtin_popcountll(bad);
+      for (int i = 0; bad != 0ull; ++i, bad &= bad - 1ull)
+        if ((i & (NW - 1)) == wv) {
+          char* p = reinterpret_cast<char*>(g.C) + ((int64_t)__builtin_ctzll(bad) * g.ldc + blockIdx.x * WC) * (CT ? 2 : 4);
+          if (lane < WC * (CT ? 2 : 4) / 16) *reinterpret_cast<u32x4_t*>(p + lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
+        }
+    }
+    const unsigned long long hit = __ballot(inc > tile);
     if (hit != 0ull) {
       const int l = __builtin_ctzll(hit);
-      const int in_seg = tile - (base + __shfl(inc, l) - __shfl(nt, l));
-      seg = s0 + l;
-      begin = __shfl(beg, l) + in_seg * R;
-      cnt = min(R, __shfl(c, l) - in_seg * R);
-      break;
+      const int first = (tile - (__shfl(inc, l) - __shfl(nt, l))) * R;      // rank of the tile's first row
+      seg = __shfl(e, l);
+      const bool mine = valid && e == seg;
+      cnt = min(R, __builtin_popcountll(__ballot(mine)) - first);
+      const int r = rank - first;
+      rows = __builtin_amdgcn_ds_permute((mine && r >= 0 && r < R ? r : 63) * 4, lane);   // (lane 63 is no row's)
     }
-    base += __shfl(inc, 63);
+  } else {
+    for (int s0 = 0; s0 < g.nseg; s0 += 64) {
+      const int s = s0 + lane;
+      int beg = 0, c = 0;
+      if (s < g.nseg) { beg = g.seg_ptr[s]; c = g.seg_ptr[s + 1] - beg; }
+      const int nt = (c + R - 1) / R;
+      int inc = nt;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(inc, d);
+        if (lane >= d) inc += t;
+      }
+      const unsigned long long hit = __ballot(base + inc > tile);
+      if (hit != 0ull) {
+        const int l = __builtin_ctzll(hit);
+        const int in_seg = tile - (base + __shfl(inc, l) - __shfl(nt, l));
+        seg = s0 + l;
+        begin = __shfl(beg, l) + in_seg * R;
+        cnt = min(R, __shfl(c, l) - in_seg * R);
+        break;
+      }
+      base += __shfl(inc, 63);
+    }
   }
   if (seg < 0) return;                                  // (uniform over the workgroup)
   seg = __builtin_amdgcn_readfirstlane(seg);
@@ -589,8 +635,11 @@ k_gather_m_few(const GemmArgs g) {
     PIT_SCHED_FENCE();
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      const int p = begin + min(16 * b + q, cnt - 1);   // rows past the end: the last listed row, never stored
-      a_off[b] = __umul24((uint32_t)(g.a_gather ? g.idx[p] : p), pitch_a) + 16u * (uint32_t)kb;
+      const int r = min(16 * b + q, cnt - 1);           // rows past the end: the last listed row, never stored
+      int row;
+      if constexpr (ROUTE) row = __shfl(rows, r);
+      else row = g.a_gather ? g.idx[begin + r] : begin + r;
+      a_off[b] = __umul24((uint32_t)row, pitch_a) + 16u * (uint32_t)kb;
     }
 #pragma unroll
     for (int u = 0; u < DEPTH; ++u) load_a(u, u);
@@ -627,7 +676,9 @@ k_gather_m_few(const GemmArgs g) {
     const int unit = v / H, h = v % H;
     const int row = 16 * (unit >> 2) + 4 * kb + (unit & 3);
     const bool live = row < cnt;
-    const int crow = live ? (g.c_scatter ? g.idx[begin + row] : begin + row) : 0;
+    int crow;
+    if constexpr (ROUTE) crow = __shfl(rows, live ? row : 0);
+    else crow = live ? (g.c_scatter ? g.idx[begin + row] : begin + row) : 0;
     float scale = 1.f;
     if constexpr (EPI == EPI_STORE) { if (g.gate && live) scale = g.gate[crow]; }
     f32x4_t s = *(PIT_LDS f32x4_t*)(red + v * 1024);
@@ -650,7 +701,9 @@ int launch_few(const GemmArgs& g, int64_t total_rows, hipStream_t st) {
   // sum over segments of ceil(count / 16): at most one tile per row, and one partly filled tile per segment
   const int64_t tiles = std::min<int64_t>(total_rows, total_rows / 16 + g.nseg);
   if (total_rows / 128 + g.nseg > 65520) return PIT_ESHAPE;     // (the limit of launch_cfg: tiles <= 65520 then, too)
-  hipLaunchKernelGGL((k_gather_m_few<BF, EPI, CT>), dim3((unsigned)(g.N / 64), (unsigned)tiles), dim3(512), 0, st, g);
+  const dim3 grid((unsigned)(g.N / 64), (unsigned)tiles);
+  if (g.route != nullptr) hipLaunchKernelGGL((k_gather_m_few<BF, EPI, CT, true>), grid, dim3(512), 0, st, g);
+  else                    hipLaunchKernelGGL((k_gather_m_few<BF, EPI, CT, false>), grid, dim3(512), 0, st, g);
   PIT_LAUNCH_CHECK();
   return PIT_OK;
 }
@@ -684,24 +737,34 @@ int launch_cfg(GemmArgs g, int64_t total_rows, hipStream_t st) {
   return PIT_OK;
 }
 
-// Whether k_gather_m_few is the faster kernel for segments with a B of their own: up to eight rows per segment on average (a
-// tile has 16 rows), and not much to read.  k_gather_m_lds takes at least the latency of its walk over k (0.3 us per 32
-// of K); with enough weights both run at the memory's rate, and this kernel at 5.0 TB/s a little below the other's
-// 5.3.  That point is at about 200 MB , or earlier where K is short: a workgroup's start (its segment, its rows, the
-// first loads) weighs as much as 64 x K elements of B then, and pays for up to 2.2 K workgroups.  The number of segments
-// that have a row at all is known on the device only; taken for it is what rows dealt at random would give (all rows
-// apart: at most 1.6 times as many, the loss then stays below 10 %; a few favoured segments: fewer).
+// Whether k_gather_m_few is the faster kernel for segments with a B of their own: where its workgroups for the tiles that
+// exist all run at once (two per compute unit), or there are up to eight rows per segment on average (a tile has 16 rows);
+// and not much to read.  k_gather_m_lds takes at least the latency of its walk over k (0.3 us per 32 of K), whatever the
+// number of rows; with enough weights both run at the memory's rate, and this kernel at 5.0 TB/s a little below the other's
+// 5.3.  That point is at about 200 MB, or, with more workgroups than run at once, earlier where K is short: a workgroup's
+// start (its segment, its rows, the first loads) weighs as much as 64 x K elements of B then, and pays for up to 2.2 K
+// workgroups.  The number of segments that have a row at all is known on the device only; taken for it is what rows dealt at
+// random would give (all rows apart: at most 1.6 times as many, the loss then stays below 10 %; a few favoured segments:
+// fewer).
 // Measured per product over 8 shapes of 256 - 1024 x 768 - 4096, 16 - 128 experts, 8 - 512 tokens, three ways of routing:
-// 0.783 of k_gather_m_lds' time in the geometric mean (the faster kernel every time: 0.776), 19 of 1008 calls slower by
-// more than 2 %.  (Up to 64 segments always and beyond only with a row each: 0.792, and 128 of them, by up to 19 %:
-// 512 x 2048, 64 experts, 64 tokens on one expert each 57.7 / 67.1; 1024 x 4096, 512 tokens 182 / 212.)
+// up to eight rows per segment 0.783 of k_gather_m_lds' time in the geometric mean (the faster kernel every time: 0.776), 19
+// of 1008 calls slower by more than 2 %.  (Up to 64 segments always and beyond only with a row each: 0.792, and 128 of them,
+// by up to 19 %: 512 x 2048, 64 experts, 64 tokens on one expert each 57.7 / 67.1; 1024 x 4096, 512 tokens 182 / 212.)
+// With more rows, whole calls over 6 shapes of 256 - 1024 x 512 - 4096, 1 - 128 experts, 65 - 2048 tokens, three ways of
+// routing: running at once as well, 0.861 of the time of eight rows alone (the faster kernel every time: 0.824), none of 846
+// more than 2.7 % slower; up to 768 workgroups 0.857 and 7.4 %, 1024 0.855 and 20 %.  768 x 3072, k_gather_m_lds / this, us:
+// 128 tokens, 8 experts 41.5 / 27.1; 192, 16 49.7 / 44.8; 512, 4 (the second product only) 43.7 / 36.8.
 // Beyond 512 segments k_gather_m_lds' search for a tile's segment decides, which visits all of them: 1024 tokens, 128 x
 // 256, 4096 experts 649 / 420.
+double hit_segments(const GemmArgs& g, int64_t rows) { return g.nseg * (1.0 - std::pow(1.0 - 1.0 / g.nseg, (double)rows)); }
+
 bool few_rows_pay(const GemmArgs& g, int64_t total_rows) {
-  if (g.b_seg_stride == 0 || total_rows > 8 * (int64_t)g.nseg) return false;
+  if (g.b_seg_stride == 0) return false;
   if (g.nseg > 512 && total_rows <= g.nseg) return true;
-  const double hit = g.nseg * (1.0 - std::pow(1.0 - 1.0 / g.nseg, (double)total_rows));
-  return hit * g.N * g.slab * 2.0 <= 200e6 && hit * g.N / 64.0 <= 2.2 * g.slab;
+  const double hit = hit_segments(g, total_rows), columns = g.N / 64.0;
+  if (hit * g.N * g.slab * 2.0 > 200e6) return false;
+  if (std::min((double)total_rows, hit + total_rows / 16) * columns <= 2.0 * compute_units()) return true;
+  return total_rows <= 8 * (int64_t)g.nseg && hit * columns <= 2.2 * g.slab;
 }
 
 // Tile shape by the shape of the product.  128 x 256 (a wave owns 64 x 128) where N allows: fewer bytes through
@@ -713,11 +776,9 @@ bool few_rows_pay(const GemmArgs& g, int64_t total_rows) {
 template <bool BF, int EPI, int CT>
 int launch_shape(const GemmArgs& g, int64_t total_rows, hipStream_t st) {
   // (a product too small to give every compute unit a 128 x 256 tile even in the worst case takes 128 x 128)
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
-  if (few_rows_pay(g, total_rows)) return launch_few<BF, EPI, CT>(g, total_rows, st);
+  if (g.route != nullptr || few_rows_pay(g, total_rows)) return launch_few<BF, EPI, CT>(g, total_rows, st);
   const int64_t wide_tiles = (total_rows / 128 + g.nseg) * (g.N / 256);
-  if (g.N % 256 == 0 && wide_tiles >= cus) return launch_cfg<BF, EPI, CT, 2, 4, 3>(g, total_rows, st);
+  if (g.N % 256 == 0 && wide_tiles >= compute_units()) return launch_cfg<BF, EPI, CT, 2, 4, 3>(g, total_rows, st);
   return launch_cfg<BF, EPI, CT, 2, 2, 4>(g, total_rows, st);
 }
 
@@ -731,6 +792,15 @@ int launch_bf(int epi, int ct, const GemmArgs& g, int64_t total_rows, hipStream_
 }
 
 }  // namespace
+
+// Up to 64 tokens: without an index k_gather_m_few is ahead of an index and k_gather_m_lds wherever the weights are not
+// expected to exceed 300 MB (whole calls, us, index and the faster kernel per product / without; 32 tokens, 1024 x 4096, 64
+// experts, tokens apart: 101 / 103, random by popularity: 78.6 / 70.9; 64 tokens: 179 / 199 and 98 / 101, left to the index).
+// Over 6 shapes of 256 - 1024 x 512 - 4096, 1 - 128 experts, 1 - 64 tokens, three ways of routing: 0.756 of the time with
+// an index and this kernel up to eight rows per segment only, 3 of 1134 more than 2 % slower (tokens apart, 300 MB and more: 8 %).
+bool gather_m_routes(const GemmArgs& g) {
+  return g.M <= 64 && g.b_seg_stride != 0 && (few_rows_pay(g, g.M) || hit_segments(g, g.M) * g.N * g.slab * 2.0 <= 300e6);
+}
 
 int launch_gather_m(bool bf, int epi, int c_is_in_type, const GemmArgs& g, int64_t total_rows, hipStream_t st) {
   if (total_rows <= 0 || g.N <= 0 || g.nseg <= 0) return PIT_OK;

@@ -1,5 +1,6 @@
 // pit_moe_dispatch_gemm: top-1 mixture-of-experts FFN (paper Section 5.1, Switch Transformer).
-//   route index (counting sort by expert, ascending tokens)            -- pit_build_route_index
+//   route index (counting sort by expert, ascending tokens)            -- pit_build_route_index; with at most 64 tokens
+//             and few rows per expert the matmuls find their rows from the expert ids, without an index
 //   matmul 1: SRead gathers each expert's token rows, GELU epilogue, hidden rows stored compactly
 //             in expert-sorted order
 //   matmul 2: reads the compact hidden rows, SWrite scatters every result row to its token's slot
@@ -56,13 +57,6 @@ extern "C" int pit_moe_dispatch_gemm(const void* d_X, const int32_t* d_expert_id
   if (!d_X || !d_expert_id || !d_W1 || !d_W2 || !d_Y) return PIT_EINVAL;
   if (!aligned(d_X, 16) || !aligned(d_W1, 16) || !aligned(d_W2, 16) || !aligned(d_Y, 16)) return PIT_EINVAL;
 
-  // tokens with an invalid expert id are listed nowhere; their rows of Y are cleared by the index build itself
-  // (every other row is written by the second matmul's SWrite)
-  const int y_esize = y_dt == PIT_F32 ? 4 : 2;
-  int rc = launch_route_index(d_expert_id, T, E, &ix, d_status, ws + L.route_off, L.total - L.route_off,
-                              d_Y, (int64_t)d_model * y_esize, d_model * y_esize, stream);
-  if (rc != PIT_OK) return rc;
-
   void* H = ws + L.h_off;
   const bool bf = in_dt == PIT_BF16;
 
@@ -71,13 +65,27 @@ extern "C" int pit_moe_dispatch_gemm(const void* d_X, const int32_t* d_expert_id
   g1.C = H; g1.ldc = d_ff; g1.seg_ptr = ix.seg_ptr; g1.idx = ix.idx; g1.gate = nullptr;
   g1.nseg = E; g1.M = T; g1.N = d_ff; g1.K = d_model;
   g1.slab = d_model; g1.a_gather = 1; g1.c_scatter = 0; g1.slab_per_seg = 0;
-  rc = launch_gather_m(bf, act == 0 ? EPI_GELU : EPI_STORE, 1, g1, T, st);
-  if (rc != PIT_OK) return rc;
-
   GemmArgs g2 = {};
   g2.A = H; g2.lda = d_ff; g2.B = d_W2; g2.ldb = d_model; g2.b_seg_stride = (int64_t)d_ff * d_model;
   g2.C = d_Y; g2.ldc = d_model; g2.seg_ptr = ix.seg_ptr; g2.idx = ix.idx; g2.gate = d_gate;
   g2.nseg = E; g2.M = T; g2.N = d_model; g2.K = d_ff;
   g2.slab = d_ff; g2.a_gather = 0; g2.c_scatter = 1; g2.slab_per_seg = 0;
+
+  int rc;
+  if (gather_m_routes(g1) && gather_m_routes(g2)) {
+    // a few tokens: both products find their rows from the expert ids themselves, and the second does what is to be done for
+    // tokens with an invalid id
+    g1.route = g2.route = d_expert_id;
+    g2.route_rest = 1; g2.status = d_status;
+  } else {
+    // tokens with an invalid expert id are listed nowhere; their rows of Y are cleared by the index build itself
+    // (every other row is written by the second matmul's SWrite)
+    const int y_esize = y_dt == PIT_F32 ? 4 : 2;
+    rc = launch_route_index(d_expert_id, T, E, &ix, d_status, ws + L.route_off, L.total - L.route_off,
+                            d_Y, (int64_t)d_model * y_esize, d_model * y_esize, stream);
+    if (rc != PIT_OK) return rc;
+  }
+  rc = launch_gather_m(bf, act == 0 ? EPI_GELU : EPI_STORE, 1, g1, T, st);
+  if (rc != PIT_OK) return rc;
   return launch_gather_m(bf, EPI_STORE, y_dt != PIT_F32, g2, T, st);
 }

@@ -92,6 +92,50 @@ def test_few_rows_invalid_expert_ids(pit, bad):
     assert np.array_equal(got[~lost], ref[~lost]) and np.all(got[lost] == 0)
 
 
+@pytest.mark.parametrize("T,E", [(1, 1), (2, 2), (15, 2), (16, 3), (17, 17), (33, 5), (63, 8), (64, 9), (64, 64), (64, 65), (64, 513), (65, 64)])
+@pytest.mark.parametrize("y_dtype", [torch.float32, torch.float16])
+def test_few_tokens_find_their_experts(pit, T, E, y_dtype):
+    """At most 64 tokens, no index: experts with one row, with 16, 17 and 64 (one tile, two, four), experts whose numbers differ
+    in one bit only, the last expert, ids out of range at either end, and gates of powers of two, which keep the results exact
+    on integers.  65 tokens: the index."""
+    rng = np.random.default_rng(100 * T + E)
+    w = wl.moe_ffn(T=T, d_model=128, d_ff=256, E=E, seed=T, integer=True, unit_gate=True)
+    half = (lambda a: torch.from_numpy(orc.bf16_bits_to_f64(a)).half().cuda())
+    X, W1, W2 = half(w.X), half(w.W1), half(w.W2)
+    gate = (2.0 ** rng.integers(-2, 3, size=T)).astype(np.float32)
+    near = np.array([(E - 1) ^ (1 << b) for b in range(11) if (E - 1) ^ (1 << b) < E] + [E - 1])
+    routes = [w.expert_id, np.zeros(T), np.full(T, E - 1), np.repeat(np.arange(T), 17)[:T] % E, near[rng.integers(len(near), size=T)],
+              rng.integers(-1, E + 1, size=T), np.where(np.arange(T) % 2 == 0, -2**31, 2**31 - 1)]
+    for eid in routes:
+        eid = np.asarray(eid).astype(np.int32)
+        lost = (eid < 0) | (eid >= E)
+        out = torch.full((T, 128), 9.0, dtype=y_dtype, device="cuda")
+        status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+        Y = pit.pit_moe_dispatch_gemm(X, to_dev(eid), to_dev(gate), W1, W2, out=out, y_dtype=y_dtype, act=1, status=status)
+        torch.cuda.synchronize()
+        assert int(status[0]) == lost.sum()
+        ref = orc.moe_ffn(w.X, np.where(lost, 0, eid), gate, w.W1, w.W2, activation="identity")
+        ref[lost] = 0.0
+        if y_dtype == torch.float16:           # one rounding of an exact result
+            ref = ref.astype(np.float16).astype(np.float64)
+        assert np.array_equal(Y.double().cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("T,d_model,d_ff,E", [(1984, 256, 256, 4), (2000, 256, 256, 4), (100, 128, 1024, 1), (1000, 128, 640, 3),
+                                              (70, 128, 128, 7), (400, 128, 256, 70)])
+@pytest.mark.parametrize("route", ["popular", "even", "one"])
+def test_many_rows_per_expert_in_tiles_of_few(pit, T, d_model, d_ff, E, route):
+    """With an index: experts of up to 2000 rows in tiles of 16, the last tile partly filled; 512 workgroups (the few-rows
+    kernel) and 516 (the general one); a product on either side of the rule in one call (1000 x 128 x 640)."""
+    w = wl.moe_ffn(T=T, d_model=d_model, d_ff=d_ff, E=E, seed=T, integer=True, unit_gate=True)
+    if route != "popular":
+        w.expert_id[:] = np.arange(T) % E if route == "even" else E - 1
+    Y, st = _run(pit, w, act=1, gate=False, sentinel=99.0)
+    ref = orc.moe_ffn(w.X, w.expert_id, None, w.W1, w.W2, activation="identity")
+    assert st == 0
+    assert np.array_equal(Y.double().cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("T,E", [(512, 8), (777, 3)])
 def test_gelu_and_gate(pit, T, E):
     w = wl.moe_ffn(T=T, d_model=256, d_ff=512, E=E, seed=E)
