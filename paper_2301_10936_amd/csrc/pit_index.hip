@@ -11,6 +11,7 @@
 // The tensor itself is never re-formatted.
 #include "pit_common.hpp"
 #include <algorithm>
+#include <type_traits>
 
 namespace pit {
 namespace {
@@ -434,38 +435,50 @@ k_bitmap_route(const int32_t* __restrict__ expert_id, int T, int E, int W, u64* 
 }
 
 // ----------------------------------------------------------------------------------------------
-// Routing decisions of up to 8192 tokens over up to 64 experts: the whole index in ONE launch by one workgroup
-// (a stable counting sort without atomics; the same lists as bitmap pass + ordered emit give).
-//   1. a wave takes 64 consecutive tokens; six ballots over the bits of the expert id give every lane the set
+// Routing decisions of up to 8192 tokens over up to 128 experts, 4096 over 256, 2048 over 512: the whole index in ONE
+// launch by one workgroup (a stable counting sort without atomics; the same lists as bitmap pass + ordered emit give).
+//   1. a wave takes 64 consecutive tokens; ballots over the bits of the expert id give every lane the set
 //      of lanes with its expert, hence its rank among them and, in the first of them, their number:
 //      tab[chunk][expert]
 //   2. exclusive prefix of tab over the chunks (16 runs of chunks per expert, then the runs), totals per expert,
-//      exclusive prefix over the experts = seg_ptr
+//      exclusive prefix over the experts = seg_ptr; a lane has EB neighbouring experts
 //   3. token t goes to seg_ptr[e] + (tokens of e in earlier chunks) + (rank in its chunk)
 // Tokens with an id outside [0, E) are listed nowhere, counted in *status, and their rows of zero_rows (if given)
 // are cleared, as in k_bitmap_route.
+// With few tokens it is bound by its chain of loads, barriers and a launch, with thousands by the vector instructions of one
+// compute unit, four per bit and chunk (as 64-bit selects they were twice as many: 64 experts, 4096 and 8192 tokens 6.1 and
+// 9.7 us, now 5.5 and 8.4).  Where the lines lie: the table has 32 KB; bitmap pass + ordered emit / this, us: 65 experts, 16 and
+// 8192 tokens 6.4 / 2.9 and 9.5 / 8.7; 128: 9.0 / 2.9 and 15.6 / 8.8; 256, 4096 tokens: 20.8 / 6.1; 512, 2048: 31.5 / 5.3.
+// (The list put together in LDS and written in order: 0.2 us more up to 2048 tokens, 0.1 less at 4096.)
 // ----------------------------------------------------------------------------------------------
-constexpr int ROUTE_ONE_MAX_T = 8192, ROUTE_ONE_CHUNKS = ROUTE_ONE_MAX_T / 64;
+template <int EB>                                 // experts per lane: E <= 64 EB
+struct RouteOne {
+  static constexpr int CHUNKS = EB <= 2 ? 128 : 256 / EB, PER_WAVE = CHUNKS / 16, MAX_T = 64 * CHUNKS, MAX_E = 64 * EB;
+};
+template <int EB>
 __global__ void __launch_bounds__(1024)
 k_route_index_one(const int32_t* __restrict__ expert_id, int T, int E, int32_t* __restrict__ seg_ptr,
                   int32_t* __restrict__ idx, int32_t* __restrict__ status,
                   char* __restrict__ zero_rows, int64_t zero_ld_bytes, int zero_row_bytes) {
-  __shared__ int tab[ROUTE_ONE_CHUNKS][64];
-  __shared__ int run_sum[16][64];
-  __shared__ int base[64];
+  using R = RouteOne<EB>;
+  constexpr int BITS = EB == 1 ? 6 : EB == 2 ? 7 : EB == 4 ? 8 : 9;
+  struct alignas(2 * EB) Row { uint16_t x[EB]; };  // a lane's experts (counts and positions: at most 8192)
+  __shared__ __attribute__((aligned(16))) uint16_t tab[R::CHUNKS][R::MAX_E];
+  __shared__ __attribute__((aligned(16))) uint16_t run_sum[16][R::MAX_E];
+  __shared__ int base[R::MAX_E];
   __shared__ int bad_s[16];
   const int tid = threadIdx.x, wv = tid >> 6, ln = tid & 63;
   const int C = (T + 63) >> 6;
   const int per = (C + 15) >> 4;                  // chunks per run; run g = chunks g * per .. g * per + per - 1
-  int my_e[ROUTE_ONE_CHUNKS / 16], my_rank[ROUTE_ONE_CHUNKS / 16];
+  int my_e[R::PER_WAVE], my_rank[R::PER_WAVE];
   int nbad = 0;
   // all of this wave's expert ids are requested before the first is used (unconditional loads at clamped
   // positions: one round trip to memory instead of one per chunk)
-  int raw[ROUTE_ONE_CHUNKS / 16];
+  int raw[R::PER_WAVE];
 #pragma unroll
-  for (int j = 0; j < ROUTE_ONE_CHUNKS / 16; ++j) raw[j] = expert_id[min((wv + 16 * j) * 64 + ln, T - 1)];
+  for (int j = 0; j < R::PER_WAVE; ++j) raw[j] = expert_id[min((wv + 16 * j) * 64 + ln, T - 1)];
 #pragma unroll
-  for (int j = 0; j < ROUTE_ONE_CHUNKS / 16; ++j) {
+  for (int j = 0; j < R::PER_WAVE; ++j) {
     const int c = wv + 16 * j;
     my_e[j] = -1; my_rank[j] = 0;
     if (c >= C) continue;                         // (uniform per wave)
@@ -482,51 +495,67 @@ k_route_index_one(const int32_t* __restrict__ expert_id, int T, int E, int32_t* 
         for (int b = ln * 16; b < zero_row_bytes; b += 64 * 16) *reinterpret_cast<uint4*>(row + b) = make_uint4(0, 0, 0, 0);
       }
     }
-    u64 same = __ballot(valid);
+    const u64 all = __ballot(valid);
+    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
 #pragma unroll
-    for (int bit = 0; bit < 6; ++bit) {
-      const bool on = (e >> bit) & 1;
-      const u64 b = __ballot(on);
-      same &= on ? b : ~b;
+    for (int bit = 0; bit < BITS; ++bit) {        // (keep the lanes whose bit is this lane's)
+      const uint32_t on = (uint32_t)((int32_t)((uint32_t)e << (31 - bit)) >> 31);
+      const u64 b = __ballot(on != 0u);
+      lo &= ~((uint32_t)b ^ on);
+      hi &= ~((uint32_t)(b >> 32) ^ on);
     }
+    const u64 same = (u64)hi << 32 | lo;
     const int rank = __builtin_popcountll(same & ((1ull << ln) - 1ull));
-    tab[c][ln] = 0;                               // (this wave owns row c of the table)
+    *reinterpret_cast<Row*>(&tab[c][ln * EB]) = Row{};      // (this wave owns row c of the table)
     __builtin_amdgcn_wave_barrier();
     if (valid) {
       my_e[j] = e; my_rank[j] = rank;
-      if (rank == 0) tab[c][e] = __builtin_popcountll(same);
+      if (rank == 0) tab[c][e] = (uint16_t)__builtin_popcountll(same);
     }
   }
   if (ln == 0) bad_s[wv] = nbad;
   __syncthreads();
   {
-    const int e = ln, g = wv;                     // 16 waves = 16 runs of chunks, lane = expert
-    int sum = 0;
+    const int g = wv;                             // 16 waves = 16 runs of chunks
+    Row sum{};
     for (int c = g * per; c < min(C, (g + 1) * per); ++c) {
-      const int x = tab[c][e];
-      tab[c][e] = sum;
-      sum += x;
+      Row* const p = reinterpret_cast<Row*>(&tab[c][ln * EB]);
+      const Row x = *p;
+      *p = sum;
+#pragma unroll
+      for (int i = 0; i < EB; ++i) sum.x[i] = (uint16_t)(sum.x[i] + x.x[i]);
     }
-    run_sum[g][e] = sum;
+    *reinterpret_cast<Row*>(&run_sum[g][ln * EB]) = sum;
   }
   __syncthreads();
   if (wv == 0) {
-    int total = 0;
+    Row total{};
 #pragma unroll
     for (int g = 0; g < 16; ++g) {
-      const int x = run_sum[g][ln];
-      run_sum[g][ln] = total;
-      total += x;
+      Row* const p = reinterpret_cast<Row*>(&run_sum[g][ln * EB]);
+      const Row x = *p;
+      *p = total;
+#pragma unroll
+      for (int i = 0; i < EB; ++i) total.x[i] = (uint16_t)(total.x[i] + x.x[i]);
     }
-    int inc = total;
+    int mine = 0;
+#pragma unroll
+    for (int i = 0; i < EB; ++i) mine += total.x[i];
+    int inc = mine;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
       const int x = __shfl_up(inc, d);
       if (ln >= d) inc += x;
     }
-    base[ln] = inc - total;
-    if (ln < E) seg_ptr[ln] = inc - total;
-    if (ln == E - 1) seg_ptr[E] = inc;           // (experts beyond E have no tokens: total = 0 there)
+    int at = inc - mine;
+#pragma unroll
+    for (int i = 0; i < EB; ++i) {
+      const int e = ln * EB + i;
+      base[e] = at;
+      if (e < E) seg_ptr[e] = at;
+      at += total.x[i];
+      if (e == E - 1) seg_ptr[E] = at;            // (experts beyond E have no tokens)
+    }
     if (ln == 0 && status != nullptr) {
       int nb = 0;
 #pragma unroll
@@ -536,7 +565,7 @@ k_route_index_one(const int32_t* __restrict__ expert_id, int T, int E, int32_t* 
   }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < ROUTE_ONE_CHUNKS / 16; ++j) {
+  for (int j = 0; j < R::PER_WAVE; ++j) {
     const int c = wv + 16 * j;
     const int e = my_e[j];
     if (c < C && e >= 0) idx[base[e] + run_sum[c / per][e] + tab[c][e] + my_rank[j]] = c * 64 + ln;
@@ -1179,9 +1208,15 @@ int pit::launch_route_index(const int32_t* d_expert_id, int T, int E, const pit_
   char* ws = reinterpret_cast<char*>(d_ws);
   u64* words = reinterpret_cast<u64*>(ws);
   int32_t* cnt = reinterpret_cast<int32_t*>(ws + L.words_bytes);
-  if (T <= ROUTE_ONE_MAX_T && E <= 64) {
-    hipLaunchKernelGGL(k_route_index_one, dim3(1), dim3(1024), 0, st, d_expert_id, T, E, out->seg_ptr, out->idx, d_status,
+  const auto one = [&](auto eb) -> bool {
+    constexpr int EB = decltype(eb)::value;
+    if (T > RouteOne<EB>::MAX_T || E > RouteOne<EB>::MAX_E) return false;
+    hipLaunchKernelGGL((k_route_index_one<EB>), dim3(1), dim3(1024), 0, st, d_expert_id, T, E, out->seg_ptr, out->idx, d_status,
                        reinterpret_cast<char*>(zero_rows), zero_ld_bytes, zero_row_bytes);
+    return true;
+  };
+  if (one(std::integral_constant<int, 1>()) || one(std::integral_constant<int, 2>()) || one(std::integral_constant<int, 4>()) ||
+      one(std::integral_constant<int, 8>())) {
     PIT_LAUNCH_CHECK();
     return PIT_OK;
   }

@@ -216,7 +216,7 @@ def test_repeatable(pit):
 
 # up to 8192 tokens and 64 experts the index is built by one workgroup in one launch; beyond, by the bitmap
 # pass and the ordered emit: (8192, 64) and (200, 64) are the largest and a small case of the first path,
-# (8200, 64), (9000, 16) and (300, 130) take the second
+# (8200, 64) and (9000, 16) take the second
 @pytest.mark.parametrize("T,E", [(4096, 64), (1000, 7), (63, 1), (300, 130), (1, 3), (8192, 64), (200, 64), (8200, 64), (9000, 16)])
 def test_route_index(pit, T, E):
     w = wl.moe_ffn(T=T, d_model=8, d_ff=8, E=E, seed=T + E)
@@ -255,6 +255,29 @@ def test_route_index_invalid_ids_on_both_paths(pit, T, E):
     rsp, ridx = orc.route_index(eid_np, E)
     assert np.array_equal(sp, rsp) and np.array_equal(idx, ridx)
     assert int(status[0]) == 37
+
+
+# several experts per lane: 65 - 128 experts up to 8192 tokens, - 256 up to 4096, - 512 up to 2048, and one more of either
+@pytest.mark.parametrize("T,E", [(1, 65), (8192, 65), (8193, 65), (64, 128), (8191, 128), (1025, 129), (4096, 129), (4097, 129),
+                                 (100, 256), (4095, 256), (2048, 257), (2049, 257), (1000, 512), (2048, 512), (70, 513)])
+@pytest.mark.parametrize("ids", ["valid", "some_invalid", "one_expert"])
+def test_route_index_more_than_64_experts(pit, T, E, ids):
+    rng = np.random.default_rng(T + E)
+    eid_np = rng.integers(0, E, size=T).astype(np.int32)
+    eid_np[rng.choice(T, size=min(T, 3), replace=False)] = [0, E - 1, 64][:min(T, 3)]
+    if ids == "one_expert":
+        eid_np[:] = E - 1
+    bad = 0
+    if ids == "some_invalid":
+        bad = max(1, T // 9)
+        eid_np[rng.choice(T, size=bad, replace=False)] = rng.choice(np.array([-1, -2**31, E, E + 512, 2**31 - 1], dtype=np.int32), size=bad)
+    status = torch.full((1,), -7, dtype=torch.int32, device=dev())
+    ix = pit.pit_build_route_index(to_dev(eid_np), E, status=status)
+    torch.cuda.synchronize()
+    sp, idx, _ = ix.to_host()
+    rsp, ridx = orc.route_index(eid_np, E)
+    assert np.array_equal(sp, rsp) and np.array_equal(idx, ridx)
+    assert int(status[0]) == bad
 
 
 def test_error_returns(pit):
