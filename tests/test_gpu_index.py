@@ -203,6 +203,17 @@ def test_many_segments_path(pit):
     _check(pit, h, 1, 1, 1)
 
 
+@pytest.mark.parametrize("nseg,W", [(1, 1024), (1, 1025), (2, 513), (4, 128), (5, 103), (17, 120), (16, 128), (20, 128), (33, 62), (65, 63), (65, 95),
+                                    (97, 127), (128, 128)])
+def test_words_counted_ahead_of_a_segment(pit, nseg, W):
+    """512, 2048, 2560, 4096 and more words ahead of the last segments and chunks, and one more or less: the batches in which the
+    emit kernels count them."""
+    g = np.random.default_rng(nseg * W)
+    src = (g.random((64 * W - 5, nseg)) < 0.3).astype(np.uint8)
+    src[:, nseg // 2] = 1
+    _check(pit, src, 1, 1, 0)
+
+
 def test_repeatable(pit):
     w = wl.relu_ffn(M=512, K=1024, N=8, seed=9)
     t = to_dev(w.Xt)
