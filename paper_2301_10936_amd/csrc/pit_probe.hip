@@ -20,10 +20,14 @@ __global__ void __launch_bounds__(256) k_rate_16x16x32(int iters, float* out) {
   f32x4_t acc[NACC];
 #pragma unroll
   for (int i = 0; i < NACC; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // Accumulators tied to their registers: left to itself the compiler gives each result the registers of the accumulator
+  // before it, which chains every instruction to the last and measures that (0.88 and 1.35 PFLOP/s from one and four waves).
+  asm volatile("s_nop 7");
   for (int t = 0; t < iters; ++t) {
 #pragma unroll
-    for (int i = 0; i < NACC; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[i], 0, 0, 0);
+    for (int i = 0; i < NACC; ++i) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i]) : "v"(a), "v"(b));
   }
+  asm volatile("s_nop 15\n\ts_nop 15");      // (the compiler does not know these for matrix instructions: results are read next)
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < NACC; ++i) s += acc[i][0] + acc[i][3];
