@@ -2,7 +2,7 @@
 //   route index (counting sort by expert, ascending tokens)            -- pit_build_route_index; with at most 64 tokens
 //             and few rows per expert the matmuls find their rows from the expert ids, without an index
 //   matmul 1: SRead gathers each expert's token rows, GELU epilogue, hidden rows stored compactly
-//             in expert-sorted order
+//             in expert-sorted order (without an index: in token order)
 //   matmul 2: reads the compact hidden rows, SWrite scatters every result row to its token's slot
 // Nothing is padded to a capacity: an expert with c tokens costs ceil(c / 128) row tiles.
 #include "pit_gemm.hpp"

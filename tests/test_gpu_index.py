@@ -225,7 +225,7 @@ def test_repeatable(pit):
     assert torch.equal(a.idx[:n], b.idx[:n])
 
 
-# up to 8192 tokens and 64 experts the index is built by one workgroup in one launch; beyond, by the bitmap
+# up to 8192 tokens (and 128 experts) the index is built by one workgroup in one launch; beyond, by the bitmap
 # pass and the ordered emit: (8192, 64) and (200, 64) are the largest and a small case of the first path,
 # (8200, 64) and (9000, 16) take the second
 @pytest.mark.parametrize("T,E", [(4096, 64), (1000, 7), (63, 1), (300, 130), (1, 3), (8192, 64), (200, 64), (8200, 64), (9000, 16)])

@@ -28,8 +28,8 @@ def _run(pit, w, act=0, gate=True, y_dtype=torch.float32, sentinel=None):
     return Y, int(status[0])
 
 
-# (2000, .., 100): more than 64 experts -- the tile lookup of the product kernel scans the segments in two passes and
-# the route index takes the bitmap + emit path; (9000, .., 70): more tokens than the one-launch route index takes;
+# (2000, .., 100): more than 64 experts -- the tile lookup of the product kernel scans the segments in two passes; (9000, .., 70):
+# more tokens than the one-launch route index takes (bitmap + emit);
 # (20000, 128, 256, 100): enough row tiles for the 128 x 256 tile of the product kernel with more than 64 segments
 @pytest.mark.parametrize("T,d_model,d_ff,E", [(64, 128, 128, 2), (300, 128, 256, 5), (1000, 256, 384, 16), (129, 128, 128, 1),
                                               (2000, 128, 256, 100), (9000, 128, 128, 70), (20000, 128, 256, 100)])
