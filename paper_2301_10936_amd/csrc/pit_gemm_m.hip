@@ -502,12 +502,13 @@ __device__ __forceinline__ f32x4_t mfma16x16(const u32x4_t& a, const u32x4_t& b,
 }
 
 // ROUTE (at most 64 tokens): no index.  A wave holds all expert ids, one per lane; ballots over their bits give every lane the
-// lanes with its expert, the first lane of each expert stands for it, and the scan of their numbers of row tiles says which
-// expert this tile belongs to (experts in the order of their first token: any order will do).  Hidden rows lie in token order.
+// lanes with its expert, the first lane of each expert stands for it, and ballots over their numbers of row tiles (at most four
+// each) say which expert this tile belongs to (experts in the order of their first token: any order will do).  Hidden rows lie in token order.
 // What the index kernel does besides is done by the second product: tokens without an expert are counted and their rows of C
 // cleared, by the workgroups of row tile 0.  A call is two launches instead of three and a tile's rows are known after one
 // round trip instead of two.  Whole calls, us, with an index / this: 768 x 3072, 64 experts, 1 token 16.9 / 14.5, 48 tokens 37.5 /
-// 36.1; 512 x 2048, 128 experts (an index of two launches), 1 token 21.3 / 12.7.
+// 36.1; 512 x 2048, 128 experts (an index of two launches), 1 token 21.3 / 12.7.  (Those with a scan over shuffles and 64-bit selects
+// for the lanes, 55 vector instructions: 2.7 % more over 630 calls; 48 tokens 46.6 against 45.9.)
 template <bool BF, int EPI, int CT, bool ROUTE>
 __global__ void __launch_bounds__(512, 4)
 k_gather_m_few(const GemmArgs g) {
@@ -526,19 +527,22 @@ k_gather_m_few(const GemmArgs g) {
   if constexpr (ROUTE) {
     const int e = lane < g.M ? g.route[lane] : -1;
     const bool valid = e >= 0 && e < g.nseg;
-    unsigned long long same = __ballot(valid);
-    for (int bit = 0; (g.nseg - 1) >> bit; ++bit) {
-      const bool on = (e >> bit) & 1;
-      const unsigned long long b = __ballot(on);
-      same &= on ? b : ~b;
+    const unsigned long long all = __ballot(valid);
+    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
+    for (int bit = 0; (g.nseg - 1) >> bit; ++bit) {      // (keep the lanes whose bit is this lane's)
+      const uint32_t on = 0u - (((uint32_t)e >> bit) & 1u);
+      const unsigned long long b = __ballot(on != 0u);
+      lo &= ~((uint32_t)b ^ on);
+      hi &= ~((uint32_t)(b >> 32) ^ on);
     }
-    const int rank = __builtin_popcountll(same & ((1ull << lane) - 1ull));
-    const int nt = valid && rank == 0 ? (__builtin_popcountll(same) + R - 1) / R : 0;
-    int inc = nt;
+    const int size = __builtin_popcount(lo) + __builtin_popcount(hi);
+    const int rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+    const int nt = valid && rank == 0 ? (size + R - 1) / R : 0;
+    int ahead = 0;                                       // row tiles of the experts before this lane's (at most 64 / R each)
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int t = __shfl_up(inc, d);
-      if (lane >= d) inc += t;
+    for (int n = 1; n <= 64 / R; ++n) {
+      const unsigned long long b = __ballot(nt >= n);
+      ahead = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, ahead));
     }
     if (g.route_rest && tile == 0) {
       unsigned long long bad = __ballot(lane < g.M && !valid);
@@ -549,13 +553,13 @@ k_gather_m_few(const GemmArgs g) {
           if (lane < WC * (CT ? 2 : 4) / 16) *reinterpret_cast<u32x4_t*>(p + lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
         }
     }
-    const unsigned long long hit = __ballot(inc > tile);
+    const unsigned long long hit = __ballot(tile >= ahead && tile < ahead + nt);      // (one lane at most)
     if (hit != 0ull) {
       const int l = __builtin_ctzll(hit);
-      const int first = (tile - (__shfl(inc, l) - __shfl(nt, l))) * R;      // rank of the tile's first row
-      seg = __shfl(e, l);
+      const int first = (tile - __builtin_amdgcn_readlane(ahead, l)) * R;     // rank of the tile's first row
+      seg = __builtin_amdgcn_readlane(e, l);
       const bool mine = valid && e == seg;
-      cnt = min(R, __builtin_popcountll(__ballot(mine)) - first);
+      cnt = min(R, __builtin_amdgcn_readlane(size, l) - first);
       const int r = rank - first;
       rows = __builtin_amdgcn_ds_permute((mine && r >= 0 && r < R ? r : 63) * 4, lane);   // (lane 63 is no row's)
     }
