@@ -7,7 +7,7 @@
 //      (k_mask_index_q32: the lists sit at fixed places, one workgroup per query block), or by
 //      pit_build_index when the mask cannot be read 16 bytes at a time.
 //   2. One workgroup per (query block, head); its 4 (or 2) wavefronts take the key list in chunks of 32
-//      keys, round-robin, each with its own running softmax state, merged at the end.  A wave's
+//      keys, round-robin over four chains with a running softmax state each, merged at the end.  A wave's
 //      loop has no workgroup barrier and keeps the loads of its next chunk (and the list entries
 //      of the one after) in flight while it computes.
 //      Per chunk (everything is laid out so that lane % 32 == query):
@@ -27,11 +27,14 @@
 // and P enters as the sum of two bf16 terms, P = hi + lo with hi = P rounded to bf16 and lo = the
 // exact fp32 remainder rounded to bf16 (relative error of the pair below 2^-17), in 8 MFMAs per chunk
 // that share their V operands.
-// The error of P is smallest where P is exactly 1: at the largest score of each chain of chunks, i.e. once per wave and query.
-// With two waves instead of four that alone makes the result's error 5 % larger; there one in eight keys of a chunk takes the
-// next term of its P as well (2 more MFMAs per chunk), and the error is 1 - 2 % below that of four waves (12 x 4096, window
-// 256: 1.900e-6 with four, 2.007e-6 with two, 1.875e-6 with the term; fp16 inputs, 10 heads, window 512: 1.693e-4, 1.663e-4).
+// Chunk c belongs to chain c % 4, whatever the number of waves: a chain has a running maximum, sum and output of its own, and the
+// four are merged in their order.  Four waves have a chain each, two waves two, one after the other, so a result's bits
+// depend neither on the number of waves nor on what chooses it.  (P is exact where it is 1, at the largest score of each
+// chain.  With one chain per wave for two waves as well the result's error is 5 % larger.  A further term of P for some places
+// of a chunk makes up for that in the mean only -- every eighth key allowed, 14 x 2048: 5 % less at half of the queries, 9 %
+// more at the others -- and turns an infinity in V into NaN with fp16 inputs, as 0 x inf.)
 #include "pit_common.hpp"
+#include <type_traits>
 
 namespace pit {
 namespace {
@@ -68,15 +71,6 @@ __device__ __forceinline__ void split_bf16x2(float a, float b, uint32_t& hi2, ui
   hi2 = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
   const f32x2_t r = {a - __builtin_bit_cast(float, hi2 << 16), b - __builtin_bit_cast(float, hi2 & 0xFFFF0000u)};
   lo2 = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2_t));
-}
-// what the pair's 16-bit terms leave of {a, b} (exact in fp32), rounded to the same type
-__device__ __forceinline__ uint32_t rest_bf16x2(float a, float b, uint32_t hi2, uint32_t lo2) {
-  const f32x2_t r = {(a - __builtin_bit_cast(float, hi2 << 16)) - __builtin_bit_cast(float, lo2 << 16),
-                     (b - __builtin_bit_cast(float, hi2 & 0xFFFF0000u)) - __builtin_bit_cast(float, lo2 & 0xFFFF0000u)};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2_t));
-}
-__device__ __forceinline__ uint32_t rest_f16x2(float a, float b, uint32_t h2) {
-  return pack_f16x2(a - (float)__builtin_bit_cast(_Float16, (uint16_t)h2), b - (float)__builtin_bit_cast(_Float16, (uint16_t)(h2 >> 16)));
 }
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   uint32_t u = __builtin_bit_cast(uint32_t, f);
@@ -119,12 +113,11 @@ __global__ void __launch_bounds__(64 * NW, 3)
 k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
               const int32_t* __restrict__ seg_ptr, const int32_t* __restrict__ idx, const uint32_t* __restrict__ bits,
               int list_stride, void* __restrict__ O, int S, float scale_log2e) {
-  // per wave (private): two V tiles and one K tile of 4 KiB; after the loop the first 8 KiB carry the
-  // wave's partial output to wave 0 (32 floats per lane, laid out [value][lane])
+  // per wave (private): two V tiles and one K tile of 4 KiB; after the loop the first 8 KiB carry partial outputs to another
+  // wave (32 floats per lane, laid out [value][lane]) and the next 512 bytes per chain its maxima and sums
   __shared__ __attribute__((aligned(1024))) char s_kv[NW][3 * V_TILE_BYTES];
   // per wave, for two chunks: the 32 listed keys, then their 32 occupancy words
   __shared__ __attribute__((aligned(256))) uint32_t s_list[NW][2][2 * KC];
-  __shared__ float s_ml[NW - 1][2][64];
 
   // Consecutive workgroup ids go to different XCDs (8, each with its own L2): renumber so that an XCD
   // works on a contiguous run of (head, query block) pairs, i.e. on the K and V of one or two heads
@@ -138,7 +131,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
     head = lp / nqb;
     qb = lp - head * nqb;
   }
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, ql = lane & 31;
   // list_stride > 0: the list of query block qb starts at qb * list_stride and seg_ptr[qb] is its length
   // (k_mask_index_q32 below); else seg_ptr is the exclusive prefix pit_build_index writes
@@ -165,10 +158,13 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   const char* k_head = reinterpret_cast<const char*>(K + head_off);
   const char* v_head = reinterpret_cast<const char*>(V + head_off);
 
-  // This wave's chunks are wv, wv + NW, ...  The tiles and the mask words in LDS are private to the wave, so
-  // the loop needs no workgroup barrier, and it is software-pipelined: while chunk i is computed, the list
-  // entries of chunk i + 2 and the K and V rows of chunk i + 1 are under way.
-  const int my_chunks = nchunks > wv ? (nchunks - wv + NW - 1) / NW : 0;
+  // This wave's chunks: those of chain wv, then (two waves) those of chain wv + 2; a chain has every fourth.  The tiles
+  // and the mask words in LDS are private to the wave, so the loop needs no workgroup barrier, and it is
+  // software-pipelined: while chunk i is computed, the list entries of chunk i + 2 and the K and V rows of chunk i + 1
+  // are under way.
+  const int n_first = nchunks > wv ? (nchunks - wv + 3) >> 2 : 0;
+  const int my_chunks = n_first + (NW == 2 && nchunks > wv + 2 ? (nchunks - wv + 1) >> 2 : 0);
+  auto first_key = [&](int i) { return (wv + 4 * i + (NW == 2 && i >= n_first ? 2 - 4 * n_first : 0)) * KC; };
   // SRead.  The K and V rows of a chunk (32 x 128 B each) travel global -> LDS directly, 8 lanes x 16 B per
   // row, so that every 128-byte line is requested once; the place of a 16-byte piece inside its row of the
   // tile (the bank swizzle) is expressed by which piece of the source row a lane asks for.
@@ -178,7 +174,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   // nothing.  (The loop only runs when the list is not empty.)
   const uint32_t my_row = (uint32_t)(lane >> 3), my_slot = (uint32_t)(lane & 7);
   auto key_request = [&](int i, int slot) {                          // issue only
-    const int kk = (wv + NW * i) * KC + ql;
+    const int kk = first_key(i) + ql;
     const uint32_t pos = (uint32_t)(list_begin + min(kk, list_len - 1)) * 4u;
     const uint32_t at = (uint32_t)(uintptr_t)(PIT_LDS char*)&s_list[wv][slot][0];
     if (lane < KC) {
@@ -188,7 +184,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   };
   // (after the entries have landed) positions past the end of the list get an occupancy word of zero
   auto key_finish = [&](int i, int slot) {
-    if (!(i < my_chunks && (wv + NW * i) * KC + ql < list_len)) s_list[wv][slot][KC + ql] = 0u;
+    if (!(i < my_chunks && first_key(i) + ql < list_len)) s_list[wv][slot][KC + ql] = 0u;
     __builtin_amdgcn_wave_barrier();
   };
   // byte offset of this lane's row of the key tile, instruction `it` (tile rows 8 it + lane / 8)
@@ -227,7 +223,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   }
   // one chunk; vb = i % 2.  On entry the rows of chunk i (V in tile vb, K) and the list entries of chunk i + 1
   // (in slot vb ^ 1) were requested during the previous chunk.
-  auto step = [&](int i, int vb) {
+  auto step = [&](int i, int vb) __attribute__((always_inline)) {
     const uint32_t v_lds = v_lds0 + (uint32_t)vb * V_TILE_BYTES;
     wait_loads();                            // everything requested so far has landed
     key_finish(i + 1, vb ^ 1);
@@ -289,25 +285,18 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
       // O^T += V'^T . P^T ; k-step t covers chunk keys 16t .. 16t+15 in the order the accumulator holds them
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        uint4 pb, pl = make_uint4(0, 0, 0, 0), px = make_uint4(0, 0, 0, 0);
-        constexpr bool MORE = NW == 2;
+        uint4 pb, pl = make_uint4(0, 0, 0, 0);
         if constexpr (BF) {
           uint32_t hi2[4], lo2[4];
 #pragma unroll
           for (int x = 0; x < 4; ++x) split_bf16x2(st[8 * t + 2 * x], st[8 * t + 2 * x + 1], hi2[x], lo2[x]);
           pb = make_uint4(hi2[0], hi2[1], hi2[2], hi2[3]);
           pl = make_uint4(lo2[0], lo2[1], lo2[2], lo2[3]);
-          if constexpr (MORE) {
-            if (t == 0) px.x = rest_bf16x2(st[0], st[1], hi2[0], lo2[0]);
-          }
         } else {
           pb.x = pack_f16x2(st[8 * t + 0], st[8 * t + 1]);
           pb.y = pack_f16x2(st[8 * t + 2], st[8 * t + 3]);
           pb.z = pack_f16x2(st[8 * t + 4], st[8 * t + 5]);
           pb.w = pack_f16x2(st[8 * t + 6], st[8 * t + 7]);
-          if constexpr (MORE) {
-            if (t == 0) px.x = rest_f16x2(st[0], st[1], pb.x);
-          }
         }
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt) {
@@ -321,77 +310,104 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
           const uint4 vt = make_uint4(lo.x, lo.y, hi.x, hi.y);
           o[dt] = mfma_in<BF>(vt, pb, o[dt]);
           if constexpr (BF) o[dt] = mfma_in<BF>(vt, pl, o[dt]);
-          if constexpr (MORE) {
-            if (t == 0) o[dt] = mfma_in<BF>(vt, px, o[dt]);
-          }
         }
       }
     }
   };
-  for (int i = 0; i < my_chunks; i += 2) {      // the two V tiles alternate
+  // (a loop for each chain: with one loop for both, o_first is moved on in every turn, 32 - 60 instructions; 12 heads, S =
+  // 4096, window 256 and 5 %, us: 29.3, now 28.5.  The second loop is not unrolled: with the first chain's output kept that
+  // takes more registers than three waves per SIMD have.)
+  float m_first = -INFINITY, l_first = 0.f;
+  f32x16_t o_first[2];
+  int i = 0;
+  for (; i < n_first; i += 2) {                 // the two V tiles alternate
     step(i, 0);
-    if (i + 1 < my_chunks) step(i + 1, 1);
+    if (i + 1 < n_first) step(i + 1, 1);
+  }
+  if (NW == 2) {
+    m_first = m_run; l_first = l_run;
+    m_run = -INFINITY; l_run = 0.f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) { o_first[t][e] = o[t][e]; o[t][e] = 0.f; }
+#pragma nounroll
+    for (i = n_first; i < my_chunks; ++i) step(i, i & 1);
   }
   // the rows requested beyond the last chunk are still arriving in this wave's tiles, which now carry its
-  // partial result to wave 0
+  // partial result to the others
   wait_loads();
   wait_lds();
 
-  // merge the wavefronts' partial (m, l, O) per lane; wave 0 finishes
-  if (wv > 0) {
-    float* dst = reinterpret_cast<float*>(s_kv[wv]);      // this wave's own tiles: nobody else reads them
-    s_ml[wv - 1][0][lane] = m_run;
-    s_ml[wv - 1][1][lane] = l_run;
+  // merge the chains' partial (m, l, O) per lane in their order.  Four waves: wave 0 finishes.  Two waves: wave w finishes the
+  // 32 columns d = 32 w .. of O, each with the other's partial results for them.
+  auto part = [&](int w) { return reinterpret_cast<float*>(s_kv[w]); };      // (a wave's own tiles: nobody else reads them)
+  auto ml = [&](int w, int i) { return reinterpret_cast<float*>(s_kv[w] + 2 * V_TILE_BYTES) + i * 128; };
+  auto finish = [&](auto wave) {
+    constexpr int W = decltype(wave)::value, NT = NW == 2 ? 1 : 2, NC = 4 / NW;      // NT: blocks of 32 columns, NC: chains per wave
+    f32x16_t r[NT];
+    float m_c[4], l_c[4], a_c[4];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) dst[(t * 16 + e) * 64 + lane] = o[t][e];
-  }
-  __syncthreads();
-  if (wv != 0) return;
-  float m_all = m_run;
-#pragma unroll
-  for (int w = 0; w < NW - 1; ++w) m_all = fmaxf(m_all, s_ml[w][0][lane]);
-  const float m_safe = m_all == -INFINITY ? 0.f : m_all;
-  float a = exp2f(m_run - m_safe);
-  float l_all = l_run * a;
-#pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) o[t][e] *= a;
-#pragma unroll
-  for (int w = 0; w < NW - 1; ++w) {
-    const float* src = reinterpret_cast<const float*>(s_kv[w + 1]);
-    a = exp2f(s_ml[w][0][lane] - m_safe);
-    l_all += s_ml[w][1][lane] * a;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) o[t][e] += src[(t * 16 + e) * 64 + lane] * a;
-  }
-  const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
-  // o[dt][4*g + e] = O[query ql][d = 32*dt + 8*g + 4*h + e]
-  const int64_t row = head_off + (int64_t)(qb * QB + ql) * HD;
-#pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int d = dt * 32 + g * 8 + h * 4;
-      const float v0 = o[dt][4 * g] * inv, v1 = o[dt][4 * g + 1] * inv, v2 = o[dt][4 * g + 2] * inv, v3 = o[dt][4 * g + 3] * inv;
-      if constexpr (OT == 0) {
-        *reinterpret_cast<float4*>(reinterpret_cast<float*>(O) + row + d) = make_float4(v0, v1, v2, v3);
-      } else if constexpr (OT == 1) {
-        uint2 pk;
-        pk.x = (uint32_t)f32_to_bf16_rne(v0) | ((uint32_t)f32_to_bf16_rne(v1) << 16);
-        pk.y = (uint32_t)f32_to_bf16_rne(v2) | ((uint32_t)f32_to_bf16_rne(v3) << 16);
-        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(O) + row + d) = pk;
-      } else {
-        uint2 pk;
-        pk.x = pack_f16x2(v0, v1);
-        pk.y = pack_f16x2(v2, v3);
-        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(O) + row + d) = pk;
-      }
+    for (int c = 0; c < 4; ++c) {
+      const bool first = NW == 2 && c < 2;
+      m_c[c] = c % NW == W ? (first ? m_first : m_run) : ml(c % NW, c / NW)[lane];
+      l_c[c] = c % NW == W ? (first ? l_first : l_run) : ml(c % NW, c / NW)[64 + lane];
     }
+    const float m_all = fmaxf(fmaxf(m_c[0], m_c[1]), fmaxf(m_c[2], m_c[3]));
+    const float m_safe = m_all == -INFINITY ? 0.f : m_all;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) a_c[c] = exp2f(m_c[c] - m_safe);
+    // (fmaf: the same roundings whatever the compiler would contract)
+    const float l_all = fmaf(l_c[3], a_c[3], fmaf(l_c[2], a_c[2], fmaf(l_c[0], a_c[0], l_c[1] * a_c[1])));
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const f32x16_t* own = NW == 2 && c < 2 ? o_first : o;
+          const float x = c % NW == W ? own[NW == 2 ? W : t][e] : part(c % NW)[(16 * (NC == 2 ? c / NW : t) + e) * 64 + lane];
+          r[t][e] = c == 0 ? x * a_c[c] : fmaf(x, a_c[c], r[t][e]);
+        }
+    const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
+    // r[t][4*g + e] = O[query ql][d = 32*dt + 8*g + 4*h + e]
+    const int64_t row = head_off + (int64_t)(qb * QB + ql) * HD;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int d = (NW == 2 ? W : t) * 32 + g * 8 + h * 4;
+        const float v0 = r[t][4 * g] * inv, v1 = r[t][4 * g + 1] * inv, v2 = r[t][4 * g + 2] * inv, v3 = r[t][4 * g + 3] * inv;
+        if constexpr (OT == 0) {
+          *reinterpret_cast<float4*>(reinterpret_cast<float*>(O) + row + d) = make_float4(v0, v1, v2, v3);
+        } else if constexpr (OT == 1) {
+          uint2 pk;
+          pk.x = (uint32_t)f32_to_bf16_rne(v0) | ((uint32_t)f32_to_bf16_rne(v1) << 16);
+          pk.y = (uint32_t)f32_to_bf16_rne(v2) | ((uint32_t)f32_to_bf16_rne(v3) << 16);
+          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(O) + row + d) = pk;
+        } else {
+          uint2 pk;
+          pk.x = pack_f16x2(v0, v1);
+          pk.y = pack_f16x2(v2, v3);
+          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(O) + row + d) = pk;
+        }
+      }
+  };
+  auto give = [&](auto wave) {
+    constexpr int W = decltype(wave)::value;
+    if constexpr (NW == 2) { ml(wv, 0)[lane] = m_first; ml(wv, 0)[64 + lane] = l_first; }
+    ml(wv, 4 / NW - 1)[lane] = m_run; ml(wv, 4 / NW - 1)[64 + lane] = l_run;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) part(wv)[(t * 16 + e) * 64 + lane] = NW == 4 ? o[t][e] : t == 0 ? o_first[1 - W][e] : o[1 - W][e];
+  };
+  if (NW == 4 && wv > 0) give(std::integral_constant<int, 0>());
+  if (NW == 2 && wv == 0) give(std::integral_constant<int, 0>());
+  if (NW == 2 && wv == 1) give(std::integral_constant<int, 1>());
+  __syncthreads();
+  if (wv == 0) finish(std::integral_constant<int, 0>());
+  else if (NW == 2) finish(std::integral_constant<int, NW == 2 ? 1 : 0>());
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -556,12 +572,13 @@ extern "C" int pit_sparse_attn(const void* d_Q, const void* d_K, const void* d_V
   const uint16_t* v = reinterpret_cast<const uint16_t*>(d_V);
   dim3 grid((unsigned)L.nseg, (unsigned)H);
   // Waves per query block.  12 waves of this kernel fit a compute unit: three blocks of four waves, six of two.  Two where
-  // that makes one round of what four make two: each wave then has twice the chunks behind its start, and half as many
-  // partial results are merged.  us a call, four / two waves: 12 heads, S = 4096, window 256 and 5 % of the columns (1536 blocks
-  // on 256 compute units) 30.9 / 29.1; 7 heads, window 64 and 2 %, 19.0 / 15.7; 16 heads, S = 1600, window 64, 14.5 / 12.0.
-  // With fewer blocks four waves are faster (768: 19.4 / 21.1; 512: 16.7 / 20.6), and with more than one round of two-wave
-  // blocks (14 heads, window 512 and 10 %: 48.8 / 53.4).  Between four and five blocks per compute unit the four-wave
-  // blocks' second round is the emptier one, and long lists are faster that way (9 heads, window 512 and 10 %: 37.6 / 39.0).
+  // that makes one round of what four make two: each wave then has twice the chunks behind its start.  us a call, four / two
+  // waves: 12 heads, S = 4096, window 256 and 5 % of the columns (1536 blocks on 256 compute units) 28.8 / 28.5, no columns
+  // 24.1 / 22.2; 7 heads, window 64 and 2 %, 18.7 / 16.4; 16 heads, S = 1600, window 64, 14.0 / 12.7.
+  // With fewer blocks four waves are faster (768: 19.5 / 21.8; 512: 16.8 / 20.8), and with more than one round of two-wave
+  // blocks (14 heads, window 512 and 10 %: 48.5 / 55.6).  Between four and five blocks per compute unit the four-wave blocks'
+  // second round is the emptier one, and which is faster depends on the lists, whose lengths are on the device only: 9
+  // heads, window 512 and 10 %, 36.1 / 38.1; window 64, 16.9 / 15.7.
   const int64_t blocks = (int64_t)L.nseg * H, cus = compute_units();
   const bool two = (blocks > 3 * cus && blocks <= 4 * cus) || (blocks >= 5 * cus && blocks <= 6 * cus);
 #define PIT_ATTN_LAUNCH(BF, OT) do { \

@@ -177,3 +177,39 @@ def test_two_and_four_waves_per_query_block(pit, per_cu, more, in_dtype):
         for h0 in range(0, H, 8):
             n = min(8, H - h0)
             assert float(((O[h0:h0 + n] - few[:n]).abs() / scale[:n]).max()) <= tol
+
+
+def _masks(S):
+    """Masks under which a query's keys take every place in a chunk of 32, or only some of them."""
+    g = np.random.default_rng(S)
+    i, j = np.arange(S)[:, None], np.arange(S)[None, :]
+    band = (np.abs(i - j) <= 32) | np.repeat(g.random((S // 32, S)) < 0.1, 32, axis=0)
+    return {"band": band, "full": np.ones((S, S), bool), "random": g.random((S, S)) < 0.2, "stride": (j - i) % 8 == 0,
+            "residue": (j % 8 == 2) | ((j % 8 == 6) & (i % 2 == 0))}
+
+
+@pytest.mark.parametrize("kind", ["band", "full", "random", "stride", "residue"])
+@pytest.mark.parametrize("in_dtype", [torch.bfloat16, torch.float16])
+def test_a_head_does_not_depend_on_the_others(pit, kind, in_dtype):
+    """Two waves per query block or four, chosen by the number of heads: the same bits, whatever the mask, the output type and
+    the values (an infinity in V, which must not turn into NaN at the queries that see no more than it and finite ones)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count & ~7
+    S, H = 256, 4 * cus // 8                                              # (four blocks per compute unit: two waves)
+    w = wl.sparse_attn(H=4, S=S, seed=H)
+    m = _masks(S)[kind].astype(np.uint8)
+    q, k, v = (orc.bf16_bits_to_f64(x).astype(np.float16) if in_dtype == torch.float16 else x for x in (w.Q, w.K, w.V))
+    Q, K, V = (to_dev(x) for x in (q, k, v))
+    run = lambda n, V, dt: pit.pit_sparse_attn(*(x.repeat(-(-n // 4), 1, 1)[:n].contiguous() for x in (Q, K, V)), to_dev(m), w.scale, o_dtype=dt)
+    V_inf = V.clone()
+    V_inf[1, 10, 3], V_inf[2, 12, 40] = float("inf"), float("-inf")
+    for values in (V, V_inf):
+        for dt in (torch.float32, torch.bfloat16, torch.float16):
+            O, few = run(H, values, dt), run(4, values, dt)
+            same = O.view(-1, 4, S, 64).view(torch.uint8) == few.view(torch.uint8)
+            assert bool(same.all())
+    err = np.abs(run(H, V, torch.float32)[:4].cpu().numpy() - orc.sparse_attn(q, k, v, m, w.scale)).max()
+    # P to 2^-17 or 2^-11 of itself, |V| < 6, and fp32 sums of up to S terms
+    assert err <= 6.0 * ((2.0 ** -17 if in_dtype == torch.bfloat16 else 2.0 ** -11) + S * 2.0 ** -24)
+    if in_dtype == torch.float16 and kind == "full":
+        O = run(H, V_inf, torch.float32)[:4].cpu().numpy()
+        assert np.all(O[1, :, 3] == np.inf) and np.all(O[2, :, 40] == -np.inf)
