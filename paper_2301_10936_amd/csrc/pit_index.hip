@@ -443,8 +443,11 @@ k_bitmap_route(const int32_t* __restrict__ expert_id, int T, int E, int W, u64* 
 //   2. exclusive prefix of tab over the chunks (16 runs of chunks per expert, then the runs), totals per expert,
 //      exclusive prefix over the experts = seg_ptr; a lane has EB neighbouring experts
 //   3. token t goes to seg_ptr[e] + (tokens of e in earlier chunks) + (rank in its chunk)
-// Tokens with an id outside [0, E) are listed nowhere, counted in *status, and their rows of zero_rows (if given)
-// are cleared, as in k_bitmap_route.
+// Tokens with an id outside [0, E) are listed nowhere, counted in *status, and their rows of zero_rows (if given) are
+// cleared, as in k_bitmap_route -- by further workgroups, one per 64 tokens, which do nothing else: one compute unit does not
+// write more than 0.15 TB/s.  Whole mixture-of-experts calls, cleared by the index's own workgroup / by these, us: 8192 tokens,
+// 768 x 1536, 128 experts, no token without one 163 / 163, half of them 234 / 147, all 195 / 16.5; 2048 x 256, 8 experts, half
+// 288 / 49.
 // With few tokens it is bound by its chain of loads, barriers and a launch, with thousands by the vector instructions of one
 // compute unit, four per bit and chunk (as 64-bit selects they were twice as many: 64 experts, 4096 and 8192 tokens 6.1 and
 // 9.7 us, now 5.5 and 8.4).  Where the lines lie: the table has 32 KB; bitmap pass + ordered emit / this, us: 65 experts, 16 and
@@ -468,6 +471,17 @@ k_route_index_one(const int32_t* __restrict__ expert_id, int T, int E, int32_t* 
   __shared__ int base[R::MAX_E];
   __shared__ int bad_s[16];
   const int tid = threadIdx.x, wv = tid >> 6, ln = tid & 63;
+  if (blockIdx.x > 0) {                           // (tokens t0 .. t0 + 63; every wave holds their ids and clears each 16th)
+    const int t0 = (blockIdx.x - 1) * 64;
+    const int e = t0 + ln < T ? expert_id[t0 + ln] : 0;
+    u64 bad = __ballot(e < 0 || e >= E);
+    for (int i = 0; bad; ++i, bad &= bad - 1) {
+      if ((i & 15) != wv) continue;
+      char* row = zero_rows + (int64_t)(t0 + __builtin_ctzll(bad)) * zero_ld_bytes;
+      for (int b = ln * 16; b < zero_row_bytes; b += 64 * 16) *reinterpret_cast<uint4*>(row + b) = make_uint4(0, 0, 0, 0);
+    }
+    return;
+  }
   const int C = (T + 63) >> 6;
   const int per = (C + 15) >> 4;                  // chunks per run; run g = chunks g * per .. g * per + per - 1
   int my_e[R::PER_WAVE], my_rank[R::PER_WAVE];
@@ -485,16 +499,7 @@ k_route_index_one(const int32_t* __restrict__ expert_id, int T, int E, int32_t* 
     const int t = c * 64 + ln;
     const int e = t < T ? raw[j] : -1;
     const bool valid = e >= 0 && e < E;
-    u64 bad = __ballot(t < T && !valid);
-    nbad += __builtin_popcountll(bad);
-    if (zero_rows != nullptr) {
-      while (bad) {
-        const int l = __builtin_ctzll(bad);
-        bad &= bad - 1;
-        char* row = zero_rows + (int64_t)(c * 64 + l) * zero_ld_bytes;
-        for (int b = ln * 16; b < zero_row_bytes; b += 64 * 16) *reinterpret_cast<uint4*>(row + b) = make_uint4(0, 0, 0, 0);
-      }
-    }
+    nbad += __builtin_popcountll(__ballot(t < T && !valid));
     const u64 all = __ballot(valid);
     uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
 #pragma unroll
@@ -1221,7 +1226,7 @@ int pit::launch_route_index(const int32_t* d_expert_id, int T, int E, const pit_
   const auto one = [&](auto eb) -> bool {
     constexpr int EB = decltype(eb)::value;
     if (T > RouteOne<EB>::MAX_T || E > RouteOne<EB>::MAX_E) return false;
-    hipLaunchKernelGGL((k_route_index_one<EB>), dim3(1), dim3(1024), 0, st, d_expert_id, T, E, out->seg_ptr, out->idx, d_status,
+    hipLaunchKernelGGL((k_route_index_one<EB>), dim3(zero_rows ? 1 + (T + 63) / 64 : 1), dim3(1024), 0, st, d_expert_id, T, E, out->seg_ptr, out->idx, d_status,
                        reinterpret_cast<char*>(zero_rows), zero_ld_bytes, zero_row_bytes);
     return true;
   };

@@ -172,6 +172,47 @@ def test_invalid_expert_ids_are_reported_and_zeroed(pit):
     assert np.array_equal(got[ok], ref[ok]) and np.all(got[~ok] == 0)
 
 
+@pytest.mark.parametrize("T,E", [(65, 8), (128, 64), (8192, 64), (8191, 128), (4096, 200), (2048, 512), (8193, 64)])
+@pytest.mark.parametrize("share", [0.03, 0.5, 1.0])
+def test_rows_of_tokens_without_an_expert(pit, T, E, share):
+    """One-launch index (all but the last) and bitmap pass: exactly the rows of the tokens without an expert come out zero."""
+    rng = np.random.default_rng(T + E)
+    w = wl.moe_ffn(T=T, d_model=128, d_ff=128, E=E, seed=T, integer=True, unit_gate=True)
+    lost = rng.random(T) < share
+    lost[-1] = True
+    w.expert_id[lost] = rng.choice(np.array([-1, E, -2**31, 2**31 - 1], dtype=np.int32), size=lost.sum())
+    Y, st = _run(pit, w, act=1, gate=False, sentinel=5.0)
+    assert st == lost.sum()
+    ref = orc.moe_ffn(w.X, np.where(lost, 0, w.expert_id), None, w.W1, w.W2, activation="identity")
+    got = Y.double().cpu().numpy()
+    assert np.array_equal(got[~lost], ref[~lost]) and np.all(got[lost] == 0)
+
+
+@pytest.mark.parametrize("T,d_model,E", [(8192, 768, 128), (4096, 1024, 64)])
+def test_clearing_rows_is_not_left_to_one_workgroup(pit, T, d_model, E):
+    """A batch that is all padding costs less than one without any: 16 and 13 us against 78 and 64 (193 and 128 where the one
+    workgroup that makes the index clears the rows as well)."""
+    X = torch.randn((T, d_model), device="cuda").bfloat16()
+    W = torch.zeros((E, d_model, d_model), dtype=torch.bfloat16, device="cuda")
+    Y = torch.empty((T, d_model), device="cuda")
+    ws = torch.empty(pit.pit_moe_workspace(T, d_model, d_model, E), dtype=torch.uint8, device="cuda")
+    none = torch.arange(T, dtype=torch.int32, device="cuda") % E
+
+    def us(eid):
+        best = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                pit.pit_moe_dispatch_gemm(X, eid, None, W, W, out=Y, ws=ws)
+            b.record()
+            b.synchronize()
+            best.append(a.elapsed_time(b) * 100)
+        return min(best)
+
+    assert us(torch.full_like(none, -1)) <= 0.75 * us(none)
+
+
 def test_empty_batch(pit):
     w = wl.moe_ffn(T=1, d_model=128, d_ff=128, E=4, seed=5)
     X = to_dev(w.X)[:0]
