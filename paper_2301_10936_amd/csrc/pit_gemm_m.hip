@@ -741,33 +741,40 @@ int launch_cfg(GemmArgs g, int64_t total_rows, hipStream_t st) {
   return PIT_OK;
 }
 
-// Whether k_gather_m_few is the faster kernel for segments with a B of their own: where its workgroups for the tiles that
-// exist all run at once (two per compute unit), or there are up to eight rows per segment on average (a tile has 16 rows);
-// and not much to read.  k_gather_m_lds takes at least the latency of its walk over k (0.3 us per 32 of K), whatever the
-// number of rows; with enough weights both run at the memory's rate, and this kernel at 5.0 TB/s a little below the other's
-// 5.3.  That point is at about 200 MB, or, with more workgroups than run at once, earlier where K is short: a workgroup's
-// start (its segment, its rows, the first loads) weighs as much as 64 x K elements of B then, and pays for up to 2.2 K
-// workgroups.  The number of segments that have a row at all is known on the device only; taken for it is what rows dealt at
-// random would give (all rows apart: at most 1.6 times as many, the loss then stays below 10 %; a few favoured segments:
-// fewer).
-// Measured per product over 8 shapes of 256 - 1024 x 768 - 4096, 16 - 128 experts, 8 - 512 tokens, three ways of routing:
-// up to eight rows per segment 0.783 of k_gather_m_lds' time in the geometric mean (the faster kernel every time: 0.776), 19
-// of 1008 calls slower by more than 2 %.  (Up to 64 segments always and beyond only with a row each: 0.792, and 128 of them,
-// by up to 19 %: 512 x 2048, 64 experts, 64 tokens on one expert each 57.7 / 67.1; 1024 x 4096, 512 tokens 182 / 212.)
-// With more rows, whole calls over 6 shapes of 256 - 1024 x 512 - 4096, 1 - 128 experts, 65 - 2048 tokens, three ways of
-// routing: running at once as well, 0.861 of the time of eight rows alone (the faster kernel every time: 0.824), none of 846
-// more than 2.7 % slower; up to 768 workgroups 0.857 and 7.4 %, 1024 0.855 and 20 %.  768 x 3072, k_gather_m_lds / this, us:
-// 128 tokens, 8 experts 41.5 / 27.1; 192, 16 49.7 / 44.8; 512, 4 (the second product only) 43.7 / 36.8.
-// Beyond 512 segments k_gather_m_lds' search for a tile's segment decides, which visits all of them: 1024 tokens, 128 x
-// 256, 4096 experts 649 / 420.
+// Whether k_gather_m_few is the faster kernel for segments with a B of their own.  k_gather_m_lds takes at least the latency of
+// its walk over k (0.3 us per 32 of K), whatever the number of rows; with enough weights both run at the memory's rate, and
+// this kernel at 5.0 TB/s a little below the other's 5.3.  That point is at about 200 MB.  The number of segments that have a
+// row at all is known on the device only; taken for it (hit) is what rows dealt at random would give.  In this order:
+//   more than 512 segments, at most a row each: k_gather_m_lds' search for a tile's segment visits all of them (1024
+//     tokens, 128 x 256, 4096 experts 649 / 420 us).
+//   one workgroup per compute unit or fewer for the tiles to be expected (half a tile per segment is empty): always.
+//   two at most for the most tiles there can be: not where the walk is short and a segment has many rows (K < 512, but for K
+//     <= 128), nor where many workgroups read the same columns of B again for every 16 rows (N < 512): each XCD sees all of B
+//     then unless the columns divide evenly over the eight, and with K > 1024 a wave's slabs are no longer all under way at
+//     once.
+//   up to eight rows per segment on average: a workgroup's start (its segment, its rows, the first loads) weighs as much as
+//     64 x K elements of B, and pays for up to 2.2 K workgroups.
+// Measured, up to eight rows per segment, per product over 8 shapes of 256 - 1024 x 768 - 4096, 16 - 128 experts, 8 - 512
+// tokens, three ways of routing: 0.783 of k_gather_m_lds' time in the geometric mean (the faster kernel every time: 0.776), 19
+// of 1008 calls slower by more than 2 %.
+// With more rows, 4380 whole calls, 65 - 4096 tokens, 128 - 1024 x 128 - 4096, 1 - 256 experts, three ways of routing: 0.835 of
+// the time of the rule of eight rows alone (the faster kernel every time: 0.824), 17 of them more than 2 % slower and one more
+// than 5 %.  (Two workgroups per compute unit whatever the shape: 0.835 as well, but 216 and 149, by up to 21 %: 1136 tokens,
+// 256 x 256, 2 experts 18.7 / 20.8; 754, 384 x 3968, 16 44.4 / 52.6; one per compute unit alone: 0.848.)  768 x 3072,
+// k_gather_m_lds / this, us: 128 tokens, 8 experts 41.5 / 27.1; 192, 16 49.7 / 44.8.
 double hit_segments(const GemmArgs& g, int64_t rows) { return g.nseg * (1.0 - std::pow(1.0 - 1.0 / g.nseg, (double)rows)); }
 
 bool few_rows_pay(const GemmArgs& g, int64_t total_rows) {
   if (g.b_seg_stride == 0) return false;
   if (g.nseg > 512 && total_rows <= g.nseg) return true;
-  const double hit = hit_segments(g, total_rows), columns = g.N / 64.0;
+  const double rows = (double)total_rows, hit = hit_segments(g, total_rows), columns = g.N / 64.0, cus = compute_units();
   if (hit * g.N * g.slab * 2.0 > 200e6) return false;
-  if (std::min((double)total_rows, hit + total_rows / 16) * columns <= 2.0 * compute_units()) return true;
+  if (std::max(hit, 0.5 * hit + rows / 16) * columns <= cus) return true;
+  if (std::min(rows, hit + total_rows / 16) * columns <= 2 * cus) {
+    if (g.slab <= 128) return true;
+    if (g.slab < 512 && g.N >= 512 && rows <= 32 * hit) return true;
+    if (g.slab >= 512 && (g.N >= 512 || rows <= 16 * hit || (g.slab <= 1024 && (g.N == 128 || g.N == 256)))) return true;
+  }
   return total_rows <= 8 * (int64_t)g.nseg && hit * columns <= 2.2 * g.slab;
 }
 

@@ -36,3 +36,12 @@ def assert_close(got: torch.Tensor, ref: np.ndarray, what=""):
     mx, fro = orc.rel_errors(g, ref)
     assert mx <= MAX_REL_TOL and fro <= FRO_TOL, f"{what}: max_rel={mx:.3e} fro={fro:.3e}"
     return mx, fro
+
+
+def kernels(fn):
+    """Names of the kernels that fn() runs, in order (empty where the profiler records none)."""
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
+        fn()
+        torch.cuda.synchronize()
+    return [e.name for e in sorted(p.events(), key=lambda e: e.time_range.start) if "k_" in e.name]

@@ -5,7 +5,7 @@ import torch
 
 from oracle import pit_oracle as orc
 from paper_2301_10936_amd import workloads as wl
-from tests.gpu_util import assert_close, dev, to_dev
+from tests.gpu_util import assert_close, dev, kernels, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -121,12 +121,39 @@ def test_few_tokens_find_their_experts(pit, T, E, y_dtype):
         assert np.array_equal(Y.double().cpu().numpy(), ref)
 
 
-@pytest.mark.parametrize("T,d_model,d_ff,E", [(1984, 256, 256, 4), (2000, 256, 256, 4), (100, 128, 1024, 1), (1000, 128, 640, 3),
-                                              (70, 128, 128, 7), (400, 128, 256, 70)])
+# Which kernel the two products of a call take at 256 compute units, F: the few-rows kernel, G: the general one with 128 x 128
+# tiles, W: with 128 x 256; f: the few-rows kernel without an index.  In pairs on either side of the lines: one workgroup of
+# the few-rows kernel per compute unit; two where K <= 128; 32 rows per expert where 128 < K < 512; two per compute unit where
+# K >= 512 and N >= 512; K <= 1024 with N = 256; 16 rows per expert with N = 384; eight rows per expert; 64 tokens.
+PRODUCTS = [(992, 256, 256, 4, "FF"), (1008, 256, 256, 4, "GG"), (1984, 128, 256, 4, "FF"), (2000, 128, 256, 4, "GF"),
+            (511, 256, 512, 16, "FF"), (512, 256, 512, 16, "GF"), (1007, 512, 512, 2, "FF"), (1008, 512, 512, 2, "GG"),
+            (1500, 256, 1024, 2, "GF"), (1500, 256, 1152, 2, "GG"), (500, 384, 512, 32, "FF"), (512, 384, 512, 32, "FG"),
+            (100, 128, 1024, 1, "FF"), (1000, 128, 640, 3, "GF"), (70, 128, 128, 7, "FF"), (400, 128, 256, 70, "FF"),
+            (70, 256, 1024, 64, "WF"), (100, 640, 256, 128, "FG"), (64, 256, 1024, 64, "ff"), (65, 256, 256, 64, "FF"),
+            (1984, 256, 256, 4, "GG"), (2000, 256, 256, 4, "GG"), (512, 256, 512, 8, "GF"), (4096, 256, 2048, 16, "WG"),
+            (40, 128, 128, 600, "ff"), (600, 128, 128, 600, "FF")]
+
+
+@pytest.mark.parametrize("T,d_model,d_ff,E,expected", PRODUCTS)
+def test_which_kernel_a_product_takes(pit, T, d_model, d_ff, E, expected):
+    """So that a new rule does not quietly take the tests of a kernel to another one."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the lines are those of 256 compute units")
+    X = torch.zeros((T, d_model), dtype=torch.bfloat16, device="cuda")
+    W1, W2 = (torch.zeros((E, a, b), dtype=torch.bfloat16, device="cuda") for a, b in ((d_model, d_ff), (d_ff, d_model)))
+    eid = torch.arange(T, dtype=torch.int32, device="cuda") % E
+    names = [n for n in kernels(lambda: pit.pit_moe_dispatch_gemm(X, eid, None, W1, W2)) if "k_gather_m" in n]
+    if not names:
+        pytest.skip("no kernel names from the profiler")
+    letter = lambda n: ("f" if "true>" in n else "F") if "k_gather_m_few" in n else "W" if ", 2, 4, 3" in n else "G"
+    assert "".join(letter(n) for n in names) == expected, names
+
+
+@pytest.mark.parametrize("T,d_model,d_ff,E", [p[:4] for p in PRODUCTS[:17] + PRODUCTS[20:22]])
 @pytest.mark.parametrize("route", ["popular", "even", "one"])
 def test_many_rows_per_expert_in_tiles_of_few(pit, T, d_model, d_ff, E, route):
-    """With an index: experts of up to 2000 rows in tiles of 16, the last tile partly filled; 512 workgroups (the few-rows
-    kernel) and 516 (the general one); a product on either side of the rule in one call (1000 x 128 x 640)."""
+    """With an index: experts of up to 2000 rows in tiles of 16, the last tile partly filled; either side of every line; both
+    kernels in one call in either order."""
     w = wl.moe_ffn(T=T, d_model=d_model, d_ff=d_ff, E=E, seed=T, integer=True, unit_gate=True)
     if route != "popular":
         w.expert_id[:] = np.arange(T) % E if route == "even" else E - 1
