@@ -48,8 +48,8 @@ def test_exact_on_integers_identity_activation(pit, T, d_model, d_ff, E):
 def test_few_rows_per_expert(pit, T, d_model, d_ff, E, y_dtype):
     """At most eight rows per expert on average: waves without a slab of k, with one, with more than are in flight; experts
     without a row, with one, with more than a tile of 16; one product by the few-rows kernel and the other by the general one
-    (100 x 640 x 256: the first; 64 x 256 x 1024: the second); more than 512 experts.  Exact on integers (bf16: the rounded
-    exact sum)."""
+    (100 x 640 x 256: the first; the second alone: 70 x 256 x 1024 below); more than 512 experts.  Exact on integers (bf16: the
+    rounded exact sum)."""
     w = wl.moe_ffn(T=T, d_model=d_model, d_ff=d_ff, E=E, seed=T, integer=True, unit_gate=True)
     Y, st = _run(pit, w, act=1, gate=False, y_dtype=y_dtype, sentinel=99.0)
     ref = orc.moe_ffn(w.X, w.expert_id, None, w.W1, w.W2, activation="identity")
@@ -134,6 +134,10 @@ PRODUCTS = [(992, 256, 256, 4, "FF"), (1008, 256, 256, 4, "GG"), (1984, 128, 256
             (40, 128, 128, 600, "ff"), (600, 128, 128, 600, "FF")]
 
 
+def letter(name):
+    return ("f" if "true>" in name else "F") if "k_gather_m_few" in name else "W" if ", 2, 4, 3" in name else "G"
+
+
 @pytest.mark.parametrize("T,d_model,d_ff,E,expected", PRODUCTS)
 def test_which_kernel_a_product_takes(pit, T, d_model, d_ff, E, expected):
     """So that a new rule does not quietly take the tests of a kernel to another one."""
@@ -145,7 +149,6 @@ def test_which_kernel_a_product_takes(pit, T, d_model, d_ff, E, expected):
     names = [n for n in kernels(lambda: pit.pit_moe_dispatch_gemm(X, eid, None, W1, W2)) if "k_gather_m" in n]
     if not names:
         pytest.skip("no kernel names from the profiler")
-    letter = lambda n: ("f" if "true>" in n else "F") if "k_gather_m_few" in n else "W" if ", 2, 4, 3" in n else "G"
     assert "".join(letter(n) for n in names) == expected, names
 
 
@@ -161,6 +164,52 @@ def test_many_rows_per_expert_in_tiles_of_few(pit, T, d_model, d_ff, E, route):
     ref = orc.moe_ffn(w.X, w.expert_id, None, w.W1, w.W2, activation="identity")
     assert st == 0
     assert np.array_equal(Y.double().cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("T,d_model,d_ff,E", [(2000, 256, 256, 4), (4096, 256, 2048, 16)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_general_kernel_gelu_and_gate(pit, T, d_model, d_ff, E, dtype):
+    """GELU, gate, both input types and both kinds of result in the general kernel: 128 x 128 tiles for both products, and
+    128 x 256 for the first; every token's row against the oracle."""
+    w = wl.moe_ffn(T=T, d_model=d_model, d_ff=d_ff, E=E, seed=T)
+    X, W1, W2 = (orc.bf16_bits_to_f64(a).astype(np.float16 if dtype == torch.float16 else np.float32) for a in (w.X, w.W1, w.W2))
+    tX, tW1, tW2 = (to_dev(a).to(dtype) for a in (X, W1, W2))
+    gate = np.random.default_rng(T).uniform(0.1, 2.0, size=T).astype(np.float32)
+    ref = orc.moe_ffn(X, w.expert_id, gate, W1, W2, round_hidden=False)
+    for y_dtype in (torch.float32, dtype):
+        out = torch.full((T, d_model), 7.0, dtype=y_dtype, device=dev())
+        Y = pit.pit_moe_dispatch_gemm(tX, to_dev(w.expert_id), to_dev(gate), tW1, tW2, out=out)
+        err = np.linalg.norm(Y.double().cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
+        # (two roundings to `dtype` at most, as in test_few_rows_gelu_and_gate)
+        assert float(err.max()) <= 2 * 0.42 * 2 ** 0.5 * (2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -11), float(err.max())
+
+
+# 40.6 experts of 64 to be expected: 341 MB of weights per product, beyond the 300 MB up to which 64 tokens take no index, and 298
+@pytest.mark.parametrize("d_ff,expected", [(4096, "WW"), (3584, "ff")])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_few_tokens_with_much_to_read(pit, d_ff, expected, dtype):
+    T, d_model, E = 64, 1024, 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d_ff)
+    draw = lambda *shape: torch.randint(-1, 2, shape, generator=g, device="cuda", dtype=torch.int8)
+    X = (draw(T, d_model) * (torch.rand((T, d_model), generator=g, device="cuda") < 0.02)).to(dtype)     # |hidden| <= 60: exact
+    W1, W2 = draw(E, d_model, d_ff).to(dtype), draw(E, d_ff, d_model).to(dtype)
+    eid = torch.arange(T, dtype=torch.int32, device="cuda") * 5 % 48
+    eid[[0, 17, 63]] = torch.tensor([-1, E, 2**31 - 1], dtype=torch.int32, device="cuda")
+    status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    Y = torch.full((T, d_model), 5.0, device="cuda")
+    call = lambda: pit.pit_moe_dispatch_gemm(X, eid, None, W1, W2, out=Y, act=1, status=status)
+    names = [n for n in kernels(call) if "k_gather_m" in n]
+    assert int(status[0]) == 3
+    ref = torch.zeros((T, d_model), dtype=torch.float64, device="cuda")
+    for t, e in enumerate(eid.tolist()):
+        if 0 <= e < E:
+            hidden = X[t:t + 1].double() @ W1[e].double()
+            assert float(hidden.abs().max()) <= 256
+            ref[t:t + 1] = hidden @ W2[e].double()
+    assert torch.equal(Y.double(), ref)
+    if names and torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert "".join(letter(n) for n in names) == expected, names
 
 
 @pytest.mark.parametrize("T,E", [(512, 8), (777, 3)])
