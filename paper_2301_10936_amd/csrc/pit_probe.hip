@@ -22,12 +22,17 @@ __global__ void __launch_bounds__(256) k_rate_16x16x32(int iters, float* out) {
   for (int i = 0; i < NACC; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   // Accumulators tied to their registers: left to itself the compiler gives each result the registers of the accumulator
   // before it, which chains every instruction to the last and measures that (0.88 and 1.35 PFLOP/s from one and four waves).
-  asm volatile("s_nop 7");
+  // The compiler does not know these for matrix instructions and would neither wait between its writes of the accumulators and
+  // the first, nor between the last and its reads: the waits below do, and are tied to the accumulators so that writes
+  // stay before them and reads behind (a s_nop without operands does not hold them).
+#pragma unroll
+  for (int i = 0; i < NACC; ++i) asm volatile("s_nop 1" : "+a"(acc[i]) : "v"(a), "v"(b));
   for (int t = 0; t < iters; ++t) {
 #pragma unroll
     for (int i = 0; i < NACC; ++i) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i]) : "v"(a), "v"(b));
   }
-  asm volatile("s_nop 15\n\ts_nop 15");      // (the compiler does not know these for matrix instructions: results are read next)
+#pragma unroll
+  for (int i = 0; i < NACC; ++i) asm volatile("s_nop 15" : "+a"(acc[i]));
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < NACC; ++i) s += acc[i][0] + acc[i][3];
