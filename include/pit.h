@@ -336,7 +336,8 @@ size_t pit_sparse_attn_workspace(int H, int S, int D);
  * (every finite bf16 / fp16 value as it is: no range restriction; K and V must be finite in the rows of
  * listed keys -- a key that some query of a block attends to meets the other 31 queries with a
  * probability of exactly zero, and 0 x Inf is not 0); the softmax numerators enter it as a two-term
- * bf16 sum (relative error < 2^-15) for bf16 inputs and rounded to fp16 for fp16 inputs.
+ * bf16 sum (relative error < 2^-15) for bf16 inputs and rounded to fp16 for fp16 inputs.  The bits of a head's result do not
+ * depend on the other heads of the call.
  * Shape rules: D == 64, S % 32 == 0.
  */
 int pit_sparse_attn(const void* d_Q, const void* d_K, const void* d_V, const uint8_t* d_mask,

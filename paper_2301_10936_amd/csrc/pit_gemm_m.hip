@@ -476,10 +476,11 @@ k_gather_m_lds(const GemmArgs g) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Segments of few rows with a B of their own (a decode step of a mixture of experts: a handful of tokens, most experts
-// with one or two of them).
+// Segments with a B of their own and few rows (a decode step of a mixture of experts: a handful of tokens, most experts
+// with one or two of them), or with more where few row tiles and columns leave k_gather_m_lds only a few workgroups (one
+// expert of 2000 rows x 128 columns: 16 workgroups there, 250 here).
 //
-// k_gather_m_lds gives such a segment 128 x 256 or 128 x 128 tiles: 12 or 6 workgroups per expert, each walking all of
+// k_gather_m_lds gives a segment of few rows 128 x 256 or 128 x 128 tiles: 12 or 6 workgroups per expert, each walking all of
 // k behind a barrier per 32 -- latency from end to end.  The bound is the memory's rate for the listed experts' weights,
 // so here a workgroup takes 64 columns of one expert and its eight waves split k (slabs of 32, wave w takes w, w + 8,
 // ..), each with four slabs of B on their way in registers: 256 KB in flight per compute unit.  A tile is 16 rows;
@@ -757,7 +758,7 @@ int launch_cfg(GemmArgs g, int64_t total_rows, hipStream_t st) {
 // Measured, up to eight rows per segment, per product over 8 shapes of 256 - 1024 x 768 - 4096, 16 - 128 experts, 8 - 512
 // tokens, three ways of routing: 0.783 of k_gather_m_lds' time in the geometric mean (the faster kernel every time: 0.776), 19
 // of 1008 calls slower by more than 2 %.
-// With more rows, 4380 whole calls, 65 - 4096 tokens, 128 - 1024 x 128 - 4096, 1 - 256 experts, three ways of routing: 0.835 of
+// With more rows, 4380 whole calls, 65 - 4096 tokens, 128 - 1024 x 128 - 4096, 1 - 256 experts, three ways of routing: 0.834 of
 // the time of the rule of eight rows alone (the faster kernel every time: 0.824), 17 of them more than 2 % slower and one more
 // than 5 %.  (Two workgroups per compute unit whatever the shape: 0.835 as well, but 216 and 149, by up to 21 %: 1136 tokens,
 // 256 x 256, 2 experts 18.7 / 20.8; 754, 384 x 3968, 16 44.4 / 52.6; one per compute unit alone: 0.848.)  768 x 3072,

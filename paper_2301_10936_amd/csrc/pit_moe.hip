@@ -1,10 +1,12 @@
 // pit_moe_dispatch_gemm: top-1 mixture-of-experts FFN (paper Section 5.1, Switch Transformer).
 //   route index (counting sort by expert, ascending tokens)            -- pit_build_route_index; with at most 64 tokens
-//             and few rows per expert the matmuls find their rows from the expert ids, without an index
+//             whose experts are expected to hold at most 300 MB of weights per matmul, the matmuls find their rows from
+//             the expert ids, without an index (gather_m_routes)
 //   matmul 1: SRead gathers each expert's token rows, GELU epilogue, hidden rows stored compactly
 //             in expert-sorted order (without an index: in token order)
 //   matmul 2: reads the compact hidden rows, SWrite scatters every result row to its token's slot
-// Nothing is padded to a capacity: an expert with c tokens costs ceil(c / 128) row tiles.
+// Nothing is padded to a capacity: an expert with c tokens costs ceil(c / 128) row tiles, or ceil(c / 16) of the few-rows
+// kernel (few_rows_pay says which a matmul takes).
 #include "pit_gemm.hpp"
 
 namespace pit {

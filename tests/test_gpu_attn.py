@@ -192,7 +192,8 @@ def _masks(S):
 @pytest.mark.parametrize("in_dtype", [torch.bfloat16, torch.float16])
 def test_a_head_does_not_depend_on_the_others(pit, kind, in_dtype):
     """Two waves per query block or four, chosen by the number of heads: the same bits, whatever the mask, the output type and
-    the values (an infinity in V, which must not turn into NaN at the queries that see no more than it and finite ones)."""
+    the values (with an infinity in V, too, for which the header promises nothing: with fp16 inputs it stays one at queries
+    that see every key of their block)."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count & ~7
     S, H = 256, 4 * cus // 8                                              # (four blocks per compute unit: two waves)
     w = wl.sparse_attn(H=4, S=S, seed=H)
