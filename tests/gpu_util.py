@@ -38,10 +38,15 @@ def assert_close(got: torch.Tensor, ref: np.ndarray, what=""):
     return mx, fro
 
 
-def kernels(fn):
-    """Names of the kernels that fn() runs, in order (empty where the profiler records none)."""
+def kernels(fn, part, count):
+    """Names of the `count` kernels with `part` in their name that fn() runs, in order; None where the profiler does not see
+    that many in three tries."""
     from torch.profiler import ProfilerActivity, profile
-    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
-        fn()
-        torch.cuda.synchronize()
-    return [e.name for e in sorted(p.events(), key=lambda e: e.time_range.start) if "k_" in e.name]
+    for _ in range(3):
+        with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as p:
+            fn()
+            torch.cuda.synchronize()
+        names = [e.name for e in sorted(p.events(), key=lambda e: e.time_range.start) if part in e.name]
+        if len(names) == count:
+            return names
+    return None
