@@ -7,6 +7,7 @@
 //             and are transposed inside each lane; the waves of a workgroup split the k-list and
 //             reduce their partial tiles through LDS at the end (details above the kernel).
 //             Tiles of 128, 64 or 32 rows x 128 columns (at most the height of the micro-tile).
+//   k_gather_k_ring (pit_gemm_ring.hip)  the same product with few tiles: up to 64 x 64, eight waves, rings in LDS.
 //   k_slab_strip, k_slab_strip_tall (pit_slab.hip)  GATHER_M with several k-slabs per row (1 x mt micro-tiles of a
 //             row-major A): a strip of C stays in LDS while the listed rows of every slab are added to it.
 //   k_gather_m_lds (pit_gemm_m.hip)  GATHER_M with whole-row micro-tiles (padded batches, MoE): the
@@ -535,10 +536,9 @@ static int launch_gather_k_tile(const GemmArgs& g, int resident, hipStream_t st)
 
 // Tile height and waves per tile by the number of tiles the product has at each height (128 columns wide; cus compute
 // units).  A tile may be lower than the micro-tile: the tiles of a micro-tile row share its list.
-//   32-row tiles <= cus: those, four waves each.  The taller tile leaves compute units idle, or alone with the latency of
-//     one long tile: 128 rows and four waves / 32 rows and four waves, full lists, us: 256 x 512 x 256 10.8 / 7.2,
-//     512 x 4096 x 512 31.6 / 21.8, 1024 x 2048 x 1024 19.2 / 12.4, 1024 x 8192 x 1024 49.8 / 35.4; lists of micro-tiles
-//     of 64 or 32 rows, two waves before: 32.4 / 22.2 and 31.6 / 22.0 at 512 x 4096 x 512.
+//   few tiles: k_gather_k_ring (the rule is at ring_tile); what is left of the next two lines is products it does not take.
+//   32-row tiles <= cus (lists of micro-tiles of 32 rows): those, four waves each.  The taller tile leaves compute units
+//     idle, or alone with the latency of one long tile; with two waves 512 x 4096 x 512 was 31.6 for 22.0 us.
 //   64-row tiles <= cus: those, four waves each: 2048 x 2048 x 1024 19.4 / 14.8 (at 512 tiles of 64 rows, 2048 x 4096 x
 //     2048, 128-row tiles are better: 32.6 / 43.6).
 //   otherwise the micro-tile's own height.  128 rows: four waves up to two tiles per compute unit, two beyond.  Lower
@@ -550,6 +550,8 @@ static int launch_gather_k_tile(const GemmArgs& g, int resident, hipStream_t st)
 template <bool BF, int CT>
 static int launch_gather_k(const GemmArgs& g, int tm_tiles, hipStream_t st) {
   const int64_t cus = compute_units(), tn = g.N / TN;
+  const RingTile ring = ring_tile(g);
+  if (ring != RING_NONE) return launch_gather_k_ring(BF, CT, g, ring, st);
   if (g.M / 32 * tn <= cus) return launch_gather_k_tile<BF, CT, 4, 2>(g, 2, st);
   if (g.slab >= 64 && g.M / 64 * tn <= cus) return launch_gather_k_tile<BF, CT, 4, 4>(g, 1, st);
   const int64_t total = tm_tiles * tn;

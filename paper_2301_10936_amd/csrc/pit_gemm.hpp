@@ -1,6 +1,7 @@
 // Types, tile constants and host-side launchers shared by the SRead -> dense MFMA tile -> SWrite
 // kernels for gfx950 (paper Section 3.1, sparse kernel template).  The kernels themselves:
 //   pit_gemm.hip    GATHER_K (k is the PIT-axis, operands register-direct)
+//   pit_gemm_ring.hip  GATHER_K for products with few tiles (operands through rings in LDS)
 //   pit_slab.hip    GATHER_M with several k-slabs per row (strips of C in LDS)
 //   pit_gemm_m.hip  GATHER_M with whole-row micro-tiles (operands staged through LDS by direct loads)
 // Their device-side helpers are in pit_gemm_dev.hpp.
@@ -51,6 +52,10 @@ int launch_gather_m(bool bf, int epi, int c_is_in_type, const GemmArgs& g, int64
 // Whether a product with a B per segment takes a kernel that can do without the index (then g.route may be set).
 bool gather_m_routes(const GemmArgs& g);
 int launch_zero_rows(void* C, int64_t ld_bytes, int M, int64_t row_bytes, hipStream_t st);
+// GATHER_K for few tiles (pit_gemm_ring.hip): the tile it has for a product, or none
+enum RingTile { RING_NONE, RING_32x32, RING_32x64, RING_64x64, RING_64x64_SHORT };
+RingTile ring_tile(const GemmArgs& g);
+int launch_gather_k_ring(bool bf, int c_is_in_type, const GemmArgs& g, RingTile tile, hipStream_t st);
 // GATHER_M with several k-slabs per row (pit_slab.hip); fp32 results
 int launch_slab_strip(bool bf, const GemmArgs& g, hipStream_t st);
 

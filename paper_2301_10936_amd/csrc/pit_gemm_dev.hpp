@@ -111,6 +111,29 @@ __device__ __forceinline__ ACols<JA> load_cols(const char* base, uint32_t byte_o
   return r;
 }
 
+// Direct global -> LDS load of 16 bytes per lane: lane i's bytes land at lds_wave_base + 16 i.
+// `base` and `lds_wave_base` are wave-uniform.
+__device__ __forceinline__ void dma16(const char* base, uint32_t byte_off, uint32_t lds_wave_base) {
+  const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_wave_base);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(m0v), "v"(byte_off), "s"(reinterpret_cast<uint64_t>(base)) : "memory", "m0");
+}
+// the same with 4 bytes per lane
+__device__ __forceinline__ void dma4(const char* base, uint32_t byte_off, uint32_t lds_wave_base) {
+  const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_wave_base);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+               :: "s"(m0v), "v"(byte_off), "s"(reinterpret_cast<uint64_t>(base)) : "memory", "m0");
+}
+// transposing LDS read (ds_read_b64_tr_b16): in each group of 16 lanes, lane i receives column i of the four rows addressed by
+// lanes 4 j .. 4 j + 3
+__device__ __forceinline__ uint2 lds_tr(uint32_t addr) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((PIT_LDS v4i16_t*)(uintptr_t)addr));
+}
+// wait until at most n vector-memory operations of this wavefront are outstanding (gfx9 encoding:
+// vmcnt in bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at "no wait"); LDS accesses that
+// follow in program order stay behind it
+#define PIT_WAIT_VMCNT(n) do { __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14)); \
+                               asm volatile("" ::: "memory"); } while (0)
 // nothing may be scheduled across this point
 #define PIT_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 

@@ -39,21 +39,6 @@
 namespace pit {
 namespace {
 
-// Direct global -> LDS load of 16 bytes per lane: lane i's bytes land at lds_wave_base + 16 i.
-// `base` and `lds_wave_base` are wave-uniform.
-__device__ __forceinline__ void dma16(const char* base, uint32_t byte_off, uint32_t lds_wave_base) {
-  const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_wave_base);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(m0v), "v"(byte_off), "s"(reinterpret_cast<uint64_t>(base)) : "memory", "m0");
-}
-__device__ __forceinline__ uint2 lds_tr(uint32_t addr) {
-  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((PIT_LDS v4i16_t*)(uintptr_t)addr));
-}
-// wait until at most n vector-memory operations of this wavefront are outstanding (gfx9 encoding:
-// vmcnt in bits 3:0 and 15:14, expcnt 6:4 and lgkmcnt 11:8 left at "no wait"); LDS accesses that
-// follow in program order stay behind it
-#define PIT_WAIT_VMCNT(n) do { __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14)); \
-                               asm volatile("" ::: "memory"); } while (0)
 // workgroup barrier that waits for this wave's LDS operations only (not for vector-memory operations:
 // the younger stages' loads stay in flight across it)
 #define PIT_LDS_BARRIER() do { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); __builtin_amdgcn_s_barrier(); \

@@ -5,7 +5,7 @@ import torch
 
 from oracle import pit_oracle as orc
 from paper_2301_10936_amd import workloads as wl
-from tests.gpu_util import assert_close, assert_index_equal, bf16_bits, dev, to_dev
+from tests.gpu_util import assert_close, assert_index_equal, bf16_bits, dev, kernels, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -222,6 +222,73 @@ def test_gather_k_every_form_large_last_row(pit, form):
     ix = pit.pit_build_index(X, 1, mt, 0)
     C = pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_K, X, W, ix, mt, M, N, K)
     assert torch.equal(C, X[K - 1].float()[:, None].expand(M, N))          # the other rows' sums are far below half a unit
+
+
+# the products with few tiles: (M, K, N, mt) on either side of every line of the rule (on 256 compute units) and the kernel they take
+FEW_TILES = {(256, 1500, 768, 128): "<%s, 32, 32, 8", (192, 1100, 1024, 64): "<%s, 32, 32, 8", (512, 700, 512, 32): "<%s, 32, 64, 8",
+             (256, 1300, 2048, 32): "<%s, 32, 64, 8", (512, 1024, 2048, 128): "<%s, 64, 64, 4", (1088, 300, 1920, 64): "<%s, 64, 64, 4",
+             (1024, 2100, 1024, 64): "<%s, 64, 64, 8", (640, 1100, 1024, 128): "<%s, 64, 64, 8", (1152, 1100, 1024, 64): "direct<%s, 4, 4",
+             (1024, 1100, 1024, 32): "direct<%s, 4, 2"}
+
+
+def _few_tiles_operands(M, K, N, mt, in_dtype):
+    lengths = [0, 1, 31, 32, 33, 255, 256, 257, 300, 511, 513, 767, 769, 1000, 1023, 1024, 1025, 1056, 1100, 1300, 2047, 2100]
+    lengths = [n for n in lengths if n <= K] + [K]
+    g = np.random.default_rng(M + N + mt)
+    Xt = np.zeros((K, M), dtype=np.float32)
+    for s in range(M // mt):
+        rows = g.choice(K, size=lengths[(5 * s + 3) % len(lengths)], replace=False)
+        Xt[rows, mt * s:mt * (s + 1)] = g.integers(-2, 3, size=(len(rows), mt))
+        Xt[rows, mt * s] = 1.0                                            # keep the listed rows non-zero
+    W = g.integers(-2, 3, size=(K, N)).astype(np.float32)
+    bigX, bigW = (torch.full((K, n), float("nan"), dtype=in_dtype, device=dev()) for n in (M + 64, N + 128))
+    bigX[:, :M] = torch.from_numpy(Xt).to(in_dtype)
+    bigW[:, :N] = torch.from_numpy(W).to(in_dtype)
+    return Xt, W, bigX[:, :M], bigW[:, :N]
+
+
+@pytest.mark.parametrize("in_dtype,c_dtype", [(torch.bfloat16, torch.float32), (torch.bfloat16, torch.bfloat16),
+                                              (torch.float16, torch.float32), (torch.float16, torch.float16)])
+@pytest.mark.parametrize("shape", FEW_TILES)
+def test_gather_k_few_tiles(pit, shape, in_dtype, c_dtype):
+    """Each tile of the kernel for few tiles: waves without work, with a partial last slab, with fewer and more slabs than
+    the loop without conditions takes; row pitches beyond the rows (NaN there), a sentinel beyond the result.  Exact on
+    integers (16-bit results: the rounded exact sum).  The dense mode on the same operands, too."""
+    M, K, N, mt = shape
+    Xt, W, X, B = _few_tiles_operands(M, K, N, mt, in_dtype)
+    ref = torch.from_numpy(Xt.T.astype(np.float64) @ W.astype(np.float64)).to(c_dtype)
+    ix = pit.pit_build_index(X, 1, mt, 0)
+    for mode, index in ((pit.PIT_GEMM_GATHER_K, ix), (pit.PIT_GEMM_DENSE_K, None)):
+        C = torch.full((M, N + 32), 9.0, dtype=c_dtype, device=dev())
+        pit.pit_sread_gemm(mode, X, B, index, mt, M, N, K, out=C[:, :N])
+        torch.cuda.synchronize()
+        assert torch.equal(C[:, :N].cpu(), ref), mode
+        assert bool((C[:, N:] == 9.0).all())
+    if (in_dtype, c_dtype) == (torch.bfloat16, torch.float32):
+        names = kernels(lambda: pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_K, X, B, ix, mt, M, N, K), "k_gather_k", 1)
+        assert names is None or FEW_TILES[shape] % "true, 0" in names[0], names
+
+
+@pytest.mark.parametrize("shape", [s for s in FEW_TILES if "direct" not in FEW_TILES[s]])
+def test_gather_k_few_tiles_large_last_row_and_rounding(pit, shape):
+    """The last listed row holds the largest finite values, or an infinity: positions past the end of a list re-read it and
+    must add nothing.  And the error of sums of floats against 64 bits: chains of at most a quarter of the list, so no more
+    than 1.1e-7 of the result on full lists of up to 2100 (four chains over 2048: 0.8e-7)."""
+    M, K, N, mt = shape
+    g = torch.Generator(device="cuda").manual_seed(M)
+    for last in (3.0e38, float("inf")):
+        X = torch.randint(-2, 3, (K, M), generator=g, device="cuda").float() * (torch.rand((K, M), generator=g, device="cuda") < 0.3)
+        X[K - 1] = last
+        W = torch.randint(-2, 3, (K, N), generator=g, device="cuda").float()
+        W[K - 1] = 1.0
+        X, W = X.to(torch.bfloat16), W.to(torch.bfloat16)
+        ix = pit.pit_build_index(X, 1, mt, 0)
+        C = pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_K, X, W, ix, mt, M, N, K)
+        assert torch.equal(C, X[K - 1].float()[:, None].expand(M, N))      # the other rows' sums are far below half a unit
+    X, W = (torch.randn(n, generator=g, device="cuda").to(torch.bfloat16) for n in ((K, M), (K, N)))
+    C = pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_K, X, W, pit.pit_build_index(X, 1, mt, 0), mt, M, N, K)
+    ref = X.double().t().contiguous() @ W.double()
+    assert float((C - ref).norm() / ref.norm()) <= 1.1e-7
 
 
 @pytest.mark.parametrize("M,K,mt", [(4224, 1300, 32), (8448, 1300, 64)])
