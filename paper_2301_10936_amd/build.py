@@ -25,6 +25,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wno-inline-asm
 OPTIONAL = {"pit_slab.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
+BINDING = os.path.join(HERE, "_pit_native.so")        # pit.py's way into the library for the calls of every step (host code)
 PROBE_LIB = os.path.join(HERE, "libpit_probe.so")     # measurement probes (bench_micro.py --probe), not the product
 
 
@@ -56,9 +57,22 @@ def _library(srcs, lib, verbose):
         raise RuntimeError("hipcc failed:\n" + out)
 
 
+def _binding(lib, verbose):
+    import sysconfig
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    rc, out = _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                    "-I" + sysconfig.get_paths()["include"], "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+                    os.path.join(CSRC, "pit_binding.cpp"), "-o", BINDING, "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"),
+                    "-ltorch_python", "-ltorch_cpu", "-lc10", "-L" + HERE, "-l:" + os.path.basename(lib), "-Wl,-rpath,$ORIGIN"], verbose)
+    if rc != 0:
+        raise RuntimeError("building the binding failed:\n" + out)
+
+
 def build(verbose: bool = False) -> str:
     srcs = [os.path.join(CSRC, s) for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
     _library(srcs, LIB, verbose)
+    _binding(LIB, verbose)
     _library([os.path.join(CSRC, "pit_probe.hip")], PROBE_LIB, verbose)
     return LIB
 

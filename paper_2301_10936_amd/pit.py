@@ -1,8 +1,13 @@
-"""Thin ctypes binding of the C-ABI library declared in include/pit.h.
+"""Thin binding of the C-ABI library declared in include/pit.h.
 
 Argument marshalling only: every step of the hot path (index build, SRead gather, MFMA tiles,
 SWrite scatter) runs inside libpit_hip.so.  PyTorch supplies device memory and the current stream.
 Importing this module raises if the library has not been built -- there is no fallback path.
+
+The calls that a layer makes on every step go through the module _pit_native (csrc/pit_binding.cpp), which reads the tensors
+natively; it answers None for arguments out of the ordinary (subclasses of Tensor, other types, ...), and those take the
+general path through ctypes below it, which accepts or refuses them.  ctypes costs 3 - 4.5 us a call on the host, as much as two
+kernel launches; _pit_native 0.3.
 """
 from __future__ import annotations
 
@@ -17,6 +22,10 @@ LIB_PATH = os.path.join(_HERE, "libpit_hip.so")
 if not os.path.exists(LIB_PATH):
     raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2301_10936_amd.build`")
 _lib = ctypes.CDLL(LIB_PATH)
+try:
+    from . import _pit_native as _native
+except ImportError as e:
+    raise ImportError("the native binding is missing: build it with `python -m paper_2301_10936_amd.build`") from e
 
 PIT_OK, PIT_EINVAL, PIT_ESHAPE, PIT_ECAPACITY, PIT_EHIP = 0, -1, -2, -3, -4
 PIT_U8, PIT_F16, PIT_BF16, PIT_F32 = 0, 1, 2, 3
@@ -163,6 +172,12 @@ def pit_build_index_workspace(rows, cols, mt_rows, mt_cols, pit_dim, want_bits=F
 def pit_build_index(src: torch.Tensor, mt_rows: int, mt_cols: int, pit_dim: int, want_bits: bool = False,
                     out: PitIndex | None = None, ws: torch.Tensor | None = None) -> PitIndex:
     """Online sparsity detection on a 2-D tensor (last dim contiguous).  See include/pit.h."""
+    if out is not None and ws is not None:
+        rc = _native.build_index(src, mt_rows, mt_cols, pit_dim, out.seg_ptr, out.idx, out.bits, out.nseg, out.cap, ws, _stream())
+        if rc == PIT_OK:
+            return out
+        if rc is not None:
+            raise PitError(rc, "pit_build_index")
     assert src.dim() == 2 and src.stride(1) == 1
     (rows, cols), ld = src.shape, src.stride(0)
     if out is None:
@@ -231,6 +246,12 @@ def pit_relu_channel_major_index(H: torch.Tensor, out_xt: torch.Tensor | None = 
     """Xt = ReLU(H)^T ([channels, tokens]) and its index at 1 x 128 micro-tiles in one pass over H
     ([tokens, channels], last dim contiguous).  Returns (Xt, index); with index=False no index is
     written and (Xt, None) is returned.  See include/pit.h."""
+    if index and out_xt is not None and out is not None and ws is not None:
+        rc = _native.relu_channel_major_index(H, out_xt, out.seg_ptr, out.idx, out.bits, out.nseg, out.cap, ws, _stream())
+        if rc == PIT_OK:
+            return out_xt, out
+        if rc is not None:
+            raise PitError(rc, "pit_relu_channel_major_index")
     assert H.dim() == 2 and H.stride(1) == 1
     tokens, channels = H.shape
     if out_xt is None:
@@ -292,6 +313,15 @@ def pit_sread_gemm(mode: int, A: torch.Tensor, B: torch.Tensor, ix: PitIndex | N
                    out: torch.Tensor | None = None, c_dtype=torch.float32, zero_uncovered: bool = True) -> torch.Tensor:
     """C = A.B over the listed micro-tiles.  GATHER_M: A is [M,K]; GATHER_K and DENSE_K (ix = None): A is At [K,M].
     B is [K,N]."""
+    if out is not None:
+        if ix is None:
+            rc = _native.sread_gemm(mode, A, B, None, None, None, 0, 0, mt, M, N, K, out, zero_uncovered, _stream())
+        else:
+            rc = _native.sread_gemm(mode, A, B, ix.seg_ptr, ix.idx, ix.bits, ix.nseg, ix.cap, mt, M, N, K, out, zero_uncovered, _stream())
+        if rc == PIT_OK:
+            return out
+        if rc is not None:
+            raise PitError(rc, "pit_sread_gemm")
     _check_operands(A, B, "pit_sread_gemm")
     if out is None:
         out = torch.empty((M, N), dtype=c_dtype, device=B.device)
@@ -322,6 +352,12 @@ def pit_select_and_run_gemm(candidates, num_tiles, grid_tiles, At: torch.Tensor,
                             out: torch.Tensor | None = None, c_dtype=torch.float32, ws: torch.Tensor | None = None):
     """Algorithm 1 over `candidates` (as for pit_select_kernel) and the winner's kernel on At [K,M], B [K,N].
     Returns (C, index of the chosen candidate).  See include/pit.h."""
+    if out is not None and ws is not None:
+        got = _native.select_and_run_gemm(candidates, num_tiles, grid_tiles, At, B, M, N, K, out, ws, _stream())
+        if got is not None:
+            rc, best = got
+            _check(rc, "pit_select_and_run_gemm")
+            return out, best
     _check_operands(At, B, "pit_select_and_run_gemm")
     if out is None:
         out = torch.empty((M, N), dtype=c_dtype, device=B.device)
@@ -342,6 +378,12 @@ def pit_moe_workspace(T, d_model, d_ff, E) -> int:
 
 def pit_moe_dispatch_gemm(X, expert_id, gate, W1, W2, out=None, y_dtype=torch.float32, act: int = 0,
                           status=None, ws=None) -> torch.Tensor:
+    if out is not None and ws is not None:
+        rc = _native.moe_dispatch_gemm(X, expert_id, gate, W1, W2, out, act, status, ws, _stream())
+        if rc == PIT_OK:
+            return out
+        if rc is not None:
+            raise PitError(rc, "pit_moe_dispatch_gemm")
     T, d_model = X.shape
     E, _, d_ff = W1.shape
     if not (X.dtype == W1.dtype == W2.dtype and X.is_contiguous() and W1.is_contiguous() and W2.is_contiguous()
@@ -363,6 +405,12 @@ def pit_sparse_attn_workspace(H, S, D) -> int:
 
 
 def pit_sparse_attn(Q, K, V, mask, scale: float, out=None, o_dtype=torch.float32, ws=None) -> torch.Tensor:
+    if out is not None and ws is not None:
+        rc = _native.sparse_attn(Q, K, V, mask, scale, out, ws, _stream())
+        if rc == PIT_OK:
+            return out
+        if rc is not None:
+            raise PitError(rc, "pit_sparse_attn")
     H, S, D = Q.shape
     if not (Q.dtype == K.dtype == V.dtype and Q.is_contiguous() and K.is_contiguous() and V.is_contiguous()
             and K.shape == Q.shape and V.shape == Q.shape and mask.dtype in (torch.uint8, torch.bool)
