@@ -14,7 +14,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpit_hip.so")
-SOURCES = ["pit_api.hip", "pit_index.hip", "pit_gemm.hip", "pit_gemm_m.hip", "pit_gemm_ring.hip", "pit_slab.hip", "pit_moe.hip", "pit_attn.hip"]
+SOURCES = ["pit_api.hip", "pit_index.hip", "pit_gemm.hip", "pit_gemm_m.hip", "pit_gemm_ring.hip", "pit_gemm_m_ring.hip", "pit_slab.hip", "pit_moe.hip", "pit_attn.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wno-inline-asm", "-Wno-pass-failed",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 # Options of one source, left out where the compiler does not know them.

@@ -4,6 +4,7 @@
 //   pit_gemm_ring.hip  GATHER_K for products with few tiles (operands through rings in LDS)
 //   pit_slab.hip    GATHER_M with several k-slabs per row (strips of C in LDS)
 //   pit_gemm_m.hip  GATHER_M with whole-row micro-tiles (operands staged through LDS by direct loads)
+//   pit_gemm_m_ring.hip  the same with few tiles or few rows per segment
 // Their device-side helpers are in pit_gemm_dev.hpp.
 #pragma once
 #include "pit_common.hpp"
@@ -56,6 +57,11 @@ int launch_zero_rows(void* C, int64_t ld_bytes, int M, int64_t row_bytes, hipStr
 enum RingTile { RING_NONE, RING_32x32, RING_32x64, RING_64x64, RING_64x64_SHORT };
 RingTile ring_tile(const GemmArgs& g);
 int launch_gather_k_ring(bool bf, int c_is_in_type, const GemmArgs& g, RingTile tile, hipStream_t st);
+// GATHER_M for few tiles or few rows per segment (pit_gemm_m_ring.hip): the tile it has for a product (rows x columns; _8: eight waves
+// instead of four; 16 x 32 and 32 x 32 have eight), or none
+enum RingMTile { RINGM_NONE, RINGM_16x32, RINGM_16x64, RINGM_16x64_8, RINGM_32x32, RINGM_32x64, RINGM_32x64_8, RINGM_64x64, RINGM_64x64_8 };
+RingMTile ring_m_tile(int epi, const GemmArgs& g, int64_t total_rows);
+int launch_gather_m_ring(bool bf, int epi, int c_is_in_type, const GemmArgs& g, int64_t total_rows, RingMTile tile, hipStream_t st);
 // GATHER_M with several k-slabs per row (pit_slab.hip); fp32 results
 int launch_slab_strip(bool bf, const GemmArgs& g, hipStream_t st);
 

@@ -30,10 +30,9 @@
 // and four consecutive columns per register quad: one row number (and gate) per lane, 16-byte stores to
 // the row the index names (or to compact rows), optionally GELU + rounding to the input type.
 #include "pit_gemm.hpp"
-#include "pit_gemm_dev.hpp"
+#include "pit_gather_m.hpp"
 #include <algorithm>
 #include <climits>
-#include <cmath>
 #include <type_traits>
 
 namespace pit {
@@ -43,57 +42,6 @@ namespace {
 // the younger stages' loads stay in flight across it)
 #define PIT_LDS_BARRIER() do { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); __builtin_amdgcn_s_barrier(); \
                                asm volatile("" ::: "memory"); } while (0)
-
-// f(store), where store(value, address) is an ordinary or a streaming store of 16 bytes of C (the rule is at launch_cfg).
-// (The marks keep the compiler from merging the two paths, which would make all stores ordinary ones.)
-template <bool CHOICE = true, typename F>
-__device__ __forceinline__ void with_stores_of(const GemmArgs& g, F&& f) {
-  if (CHOICE && g.stream_c) {
-    asm volatile("; streaming stores");
-    f([](const u32x4_t& v, void* at) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(at)); });
-    asm volatile("; end of streaming stores");
-  } else {
-    f([](const u32x4_t& v, void* at) { *reinterpret_cast<u32x4_t*>(at) = v; });
-  }
-}
-
-// Zero the rows of C that an ascending list does not name, for the rows [r_begin, r_end): the share of one
-// workgroup without a tile (all of these shares together cover [0, M)).  One 64-ary search finds the list
-// position of the first row (three or four dependent loads for a list of thousands); from there the list is
-// read 64 entries at a time: the entries below the end of a chunk of 64 rows mark its covered rows in a 64-bit
-// mask, and as many entries as the mask has bits are consumed.  Wave w clears rows w, w + 4, ... of the chunk,
-// 16 bytes per lane.
-template <int ESIZE>
-__device__ __forceinline__ void zero_unlisted_rows(const GemmArgs& g, int r_begin, int r_end, int wv, int lane) {
-  const int n = g.seg_ptr[1] - g.seg_ptr[0];
-  const int32_t* list = g.idx + g.seg_ptr[0];
-  int lo = 0, hi = n;                      // smallest j with list[j] >= r_begin (n if none)
-  while (lo < hi) {
-    const int step = (hi - lo + 63) >> 6;
-    const int p = lo + lane * step;
-    const int v = p < hi ? list[p] : INT_MAX;
-    const int k = __builtin_popcountll(__ballot(v < r_begin));   // the probes ascend: the first k are below
-    if (k == 0) { hi = lo; break; }
-    const int below = lo + (k - 1) * step;
-    hi = min(hi, below + step);
-    lo = below + 1;
-  }
-  const int64_t nbytes = (int64_t)g.N * ESIZE;
-  for (int r0 = r_begin; r0 < r_end; r0 += 64) {
-    const int v = lo + lane < n ? list[lo + lane] : INT_MAX;     // strictly ascending: entry j is >= r0 + j
-    uint64_t m = (v < r0 + 64) ? (1ull << (v - r0)) : 0ull;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) m |= __shfl_xor(m, d);
-    lo += __builtin_popcountll(m);
-    for (int r = r0 + wv; r < min(r0 + 64, r_end); r += 4) {
-      if ((m >> (r - r0)) & 1) continue;
-      char* p = reinterpret_cast<char*>(g.C) + (int64_t)r * g.ldc * ESIZE;
-      with_stores_of(g, [&](auto store) {
-        for (int64_t b = (int64_t)lane * 16; b < nbytes; b += 64 * 16) store(u32x4_t{0u, 0u, 0u, 0u}, p + b);
-      });
-    }
-  }
-}
 
 // GM x GN = arrangement of the four waves over the tile (2 x 2 or 1 x 4); a wave owns WM x WN blocks of 32 x 32.
 template <int WM, int WN, int NST, int GN> struct MTile {
@@ -181,7 +129,7 @@ k_gather_m_lds(const GemmArgs g) {
         const int idle = (int)(gridDim.x * gridDim.y / 8) - mine;
         const int d = (slot - mine) * 8 + xcd, per = (g.M + 8 * idle - 1) / (8 * idle);
         const int rb = min(g.M, d * per), re = min(g.M, rb + per);
-        if (rb < re) zero_unlisted_rows<CT ? 2 : 4>(g, rb, re, wv, lane);
+        if (rb < re) zero_unlisted_rows<CT ? 2 : 4, 4>(g, rb, re, wv, lane);
       }
       return;
     }
@@ -460,244 +408,6 @@ k_gather_m_lds(const GemmArgs g) {
   }
 }
 
-// ------------------------------------------------------------------------------------------------
-// Segments with a B of their own and few rows (a decode step of a mixture of experts: a handful of tokens, most experts
-// with one or two of them), or with more where few row tiles and columns leave k_gather_m_lds only a few workgroups (one
-// expert of 2000 rows x 128 columns: 16 workgroups there, 250 here).
-//
-// k_gather_m_lds gives a segment of few rows 128 x 256 or 128 x 128 tiles: 12 or 6 workgroups per expert, each walking all of
-// k behind a barrier per 32 -- latency from end to end.  The bound is the memory's rate for the listed experts' weights,
-// so here a workgroup takes 64 columns of one expert and its eight waves split k (slabs of 32, wave w takes w, w + 8,
-// ..), each with four slabs of B on their way in registers: 256 KB in flight per compute unit.  A tile is 16 rows;
-// an expert with more reads its weights again, mostly from L2.
-//   B operand: 8 k-rows x 4 columns per lane (16 lanes side by side fill a 128-byte line), transposed inside the lane.
-//   A operand: 16 bytes (8 k) of a listed row per lane -- already the operand layout.
-//   The waves' partial tiles meet in LDS and are added in the order of the waves.
-// Whole mixture-of-experts calls, k_gather_m_lds / this, us (tokens, d_model x d_ff, experts, tokens on few experts):
-//   1 and 48, 768 x 3072, 64: 45 / 17.6 and 62.8 / 50.9 (200 MB of weights: 4.6 TB/s);  16, 1024 x 2048, 128: 58 / 31;
-//   64, 512 x 2048, 8: 32 / 20.  When it is taken: few_rows_pay, below.
-// Tried: 32 rows per tile with three or four slabs in flight: 57 at 48 tokens; 128 columns, 16-byte loads: 55 - 68.
-// ------------------------------------------------------------------------------------------------
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-template <bool BF>
-__device__ __forceinline__ f32x4_t mfma16x16(const u32x4_t& a, const u32x4_t& b, const f32x4_t& c) {
-  if constexpr (BF)
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
-}
-
-// ROUTE (at most 64 tokens): no index.  A wave holds all expert ids, one per lane; ballots over their bits give every lane the
-// lanes with its expert, the first lane of each expert stands for it, and ballots over their numbers of row tiles (at most four
-// each) say which expert this tile belongs to (experts in the order of their first token: any order will do).  Hidden rows lie in token order.
-// What the index kernel does besides is done by the second product: tokens without an expert are counted and their rows of C
-// cleared, by the workgroups of row tile 0.  A call is two launches instead of three and a tile's rows are known after one
-// round trip instead of two.  Whole calls, us, with an index / this: 768 x 3072, 64 experts, 1 token 16.9 / 14.5, 48 tokens 37.5 /
-// 36.1; 512 x 2048, 128 experts (an index of two launches), 1 token 21.3 / 12.7.  (Those with a scan over shuffles and 64-bit selects
-// for the lanes, 55 vector instructions: 2.7 % more over 630 calls; 48 tokens 46.6 against 45.9.)
-template <bool BF, int EPI, int CT, bool ROUTE>
-__global__ void __launch_bounds__(512, 4)
-k_gather_m_few(const GemmArgs g) {
-  constexpr int CW = 4, NB = 1, DEPTH = 4;               // columns of a lane, blocks of 16 rows, slabs in flight
-  constexpr int WC = 16 * CW, NW = 8, R = 16 * NB, KS = 32;
-  constexpr int H = CW / 4, VEC = NB * 4 * H;          // 16-byte vectors of a lane's share of a partial tile
-  __shared__ __attribute__((aligned(16))) char s_red[NW * VEC * 1024];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int q = lane & 15, kb = lane >> 4;
-
-  // the tile: row tile blockIdx.y of all segments' row tiles (the grid holds the worst case), columns n0 ..
-  int seg = -1, begin = 0, cnt = 0, base = 0;
-  int rows = 0;                                          // ROUTE: lane r holds the token of the tile's row r
-  const int tile = blockIdx.y;
-  if constexpr (ROUTE) {
-    const int e = lane < g.M ? g.route[lane] : -1;
-    const bool valid = e >= 0 && e < g.nseg;
-    const unsigned long long all = __ballot(valid);
-    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
-    for (int bit = 0; (g.nseg - 1) >> bit; ++bit) {      // (keep the lanes whose bit is this lane's)
-      const uint32_t on = 0u - (((uint32_t)e >> bit) & 1u);
-      const unsigned long long b = __ballot(on != 0u);
-      lo &= ~((uint32_t)b ^ on);
-      hi &= ~((uint32_t)(b >> 32) ^ on);
-    }
-    const int size = __builtin_popcount(lo) + __builtin_popcount(hi);
-    const int rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
-    const int nt = valid && rank == 0 ? (size + R - 1) / R : 0;
-    int ahead = 0;                                       // row tiles of the experts before this lane's (at most 64 / R each)
-#pragma unroll
-    for (int n = 1; n <= 64 / R; ++n) {
-      const unsigned long long b = __ballot(nt >= n);
-      ahead = __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, ahead));
-    }
-    if (g.route_rest && tile == 0) {
-      unsigned long long bad = __ballot(lane < g.M && !valid);
-      if (blockIdx.x == 0 && tid == 0 && g.status != nullptr) *g.status = __builtin_popcountll(bad);
-      for (int i = 0; bad != 0ull; ++i, bad &= bad - 1ull)
-        if ((i & (NW - 1)) == wv) {
-          char* p = reinterpret_cast<char*>(g.C) + ((int64_t)__builtin_ctzll(bad) * g.ldc + blockIdx.x * WC) * (CT ? 2 : 4);
-          if (lane < WC * (CT ? 2 : 4) / 16) *reinterpret_cast<u32x4_t*>(p + lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
-        }
-    }
-    const unsigned long long hit = __ballot(tile >= ahead && tile < ahead + nt);      // (one lane at most)
-    if (hit != 0ull) {
-      const int l = __builtin_ctzll(hit);
-      const int first = (tile - __builtin_amdgcn_readlane(ahead, l)) * R;     // rank of the tile's first row
-      seg = __builtin_amdgcn_readlane(e, l);
-      const bool mine = valid && e == seg;
-      cnt = min(R, __builtin_amdgcn_readlane(size, l) - first);
-      const int r = rank - first;
-      rows = __builtin_amdgcn_ds_permute((mine && r >= 0 && r < R ? r : 63) * 4, lane);   // (lane 63 is no row's)
-    }
-  } else {
-    for (int s0 = 0; s0 < g.nseg; s0 += 64) {
-      const int s = s0 + lane;
-      int beg = 0, c = 0;
-      if (s < g.nseg) { beg = g.seg_ptr[s]; c = g.seg_ptr[s + 1] - beg; }
-      const int nt = (c + R - 1) / R;
-      int inc = nt;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const int t = __shfl_up(inc, d);
-        if (lane >= d) inc += t;
-      }
-      const unsigned long long hit = __ballot(base + inc > tile);
-      if (hit != 0ull) {
-        const int l = __builtin_ctzll(hit);
-        const int in_seg = tile - (base + __shfl(inc, l) - __shfl(nt, l));
-        seg = s0 + l;
-        begin = __shfl(beg, l) + in_seg * R;
-        cnt = min(R, __shfl(c, l) - in_seg * R);
-        break;
-      }
-      base += __shfl(inc, 63);
-    }
-  }
-  if (seg < 0) return;                                  // (uniform over the workgroup)
-  seg = __builtin_amdgcn_readfirstlane(seg);
-  begin = __builtin_amdgcn_readfirstlane(begin);
-  cnt = __builtin_amdgcn_readfirstlane(cnt);
-
-  const int n0 = blockIdx.x * WC;
-  const char* a_src = uniform_ptr(g.A);
-  const char* b_src = uniform_ptr(reinterpret_cast<const char*>(g.B) + (int64_t)seg * g.b_seg_stride * 2);
-  const uint32_t pitch_a = (uint32_t)(g.lda * 2), pitch_b = (uint32_t)(g.ldb * 2);
-  const int nslab = g.slab / KS;
-  const int n_w = nslab > wv ? (nslab - wv + NW - 1) / NW : 0;   // this wave's slabs: wv, wv + NW, ...
-
-  f32x4_t acc[NB][CW];
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int x = 0; x < CW; ++x) acc[b][x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  if (n_w > 0) {
-    uint32_t b_off[8], a_off[NB];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) b_off[i] = __umul24((uint32_t)(8 * kb + i), pitch_b) + (uint32_t)(n0 + CW * q) * 2u;
-    ACols<CW> rb[DEPTH][8];
-    uint4 ra[DEPTH][NB];
-    // (slabs past this wave's last: the last once more, never multiplied)
-    auto load_b = [&](int t, int u) {
-      const uint32_t k = (uint32_t)(KS * (wv + NW * min(t, n_w - 1)));
-      const char* p = b_src + (uint64_t)k * pitch_b;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) rb[u][i] = load_cols<CW>(p, b_off[i]);
-    };
-    auto load_a = [&](int t, int u) {
-      const char* p = a_src + 2u * (uint32_t)(KS * (wv + NW * min(t, n_w - 1)));
-#pragma unroll
-      for (int b = 0; b < NB; ++b) ra[u][b] = load16(p, a_off[b]);
-    };
-    auto process = [&](int u) {
-#pragma unroll
-      for (int x = 0; x < CW; ++x) {
-        u32x4_t bop;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) bop[jj] = transpose_cols_dword<CW>(rb[u], x, jj);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[b][x] = mfma16x16<BF>(__builtin_bit_cast(u32x4_t, ra[u][b]), bop, acc[b][x]);
-      }
-    };
-    // the weights do not depend on the row numbers: they are requested first
-#pragma unroll
-    for (int u = 0; u < DEPTH; ++u) load_b(u, u);
-    PIT_SCHED_FENCE();
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int r = min(16 * b + q, cnt - 1);           // rows past the end: the last listed row, never stored
-      int row;
-      if constexpr (ROUTE) row = __shfl(rows, r);
-      else row = g.a_gather ? g.idx[begin + r] : begin + r;
-      a_off[b] = __umul24((uint32_t)row, pitch_a) + 16u * (uint32_t)kb;
-    }
-#pragma unroll
-    for (int u = 0; u < DEPTH; ++u) load_a(u, u);
-    PIT_SCHED_FENCE();
-    int t = 0;
-    for (; t + DEPTH < n_w; t += DEPTH) {
-#pragma unroll
-      for (int u = 0; u < DEPTH; ++u) {
-        process(u);
-        PIT_SCHED_FENCE();
-        load_a(t + u + DEPTH, u);
-        load_b(t + u + DEPTH, u);
-        PIT_SCHED_FENCE();
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < DEPTH; ++u)
-      if (t + u < n_w) process(u);
-  }
-
-  // vector (b * 4 + e) * H + h of a wave's slot = columns CW q + 4 h .. + 3 of row 16 b + 4 kb + e
-  PIT_LDS char* red = (PIT_LDS char*)s_red + lane * 16;
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-      for (int h = 0; h < H; ++h)
-        *(PIT_LDS f32x4_t*)(red + (wv * VEC + (b * 4 + e) * H + h) * 1024) =
-            f32x4_t{acc[b][4 * h][e], acc[b][4 * h + 1][e], acc[b][4 * h + 2][e], acc[b][4 * h + 3][e]};
-  __syncthreads();
-#pragma unroll
-  for (int v = wv; v < VEC; v += NW) {                   // wave w adds up and stores the vectors w, w + NW, ..
-    const int unit = v / H, h = v % H;
-    const int row = 16 * (unit >> 2) + 4 * kb + (unit & 3);
-    const bool live = row < cnt;
-    int crow;
-    if constexpr (ROUTE) crow = __shfl(rows, live ? row : 0);
-    else crow = live ? (g.c_scatter ? g.idx[begin + row] : begin + row) : 0;
-    float scale = 1.f;
-    if constexpr (EPI == EPI_STORE) { if (g.gate && live) scale = g.gate[crow]; }
-    f32x4_t s = *(PIT_LDS f32x4_t*)(red + v * 1024);
-#pragma unroll
-    for (int w = 1; w < NW; ++w) s += *(PIT_LDS f32x4_t*)(red + (w * VEC + v) * 1024);
-    if (!live) continue;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      if constexpr (EPI == EPI_GELU) s[x] = gelu_erf_fast(s[x]);
-      if constexpr (EPI == EPI_STORE) s[x] *= scale;
-    }
-    const int64_t at = (int64_t)crow * g.ldc + n0 + CW * q + 4 * h;
-    if constexpr (CT == 0) *reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(g.C) + at) = s;
-    else *reinterpret_cast<u32x2_t*>(reinterpret_cast<uint16_t*>(g.C) + at) = u32x2_t{pack2_in<BF>(s[0], s[1]), pack2_in<BF>(s[2], s[3])};
-  }
-}
-
-template <bool BF, int EPI, int CT>
-int launch_few(const GemmArgs& g, int64_t total_rows, hipStream_t st) {
-  // sum over segments of ceil(count / 16): at most one tile per row, and one partly filled tile per segment
-  const int64_t tiles = std::min<int64_t>(total_rows, total_rows / 16 + g.nseg);
-  if (total_rows / 128 + g.nseg > 65520) return PIT_ESHAPE;     // (the limit of launch_cfg: tiles <= 65520 then, too)
-  const dim3 grid((unsigned)(g.N / 64), (unsigned)tiles);
-  if (g.route != nullptr) hipLaunchKernelGGL((k_gather_m_few<BF, EPI, CT, true>), grid, dim3(512), 0, st, g);
-  else                    hipLaunchKernelGGL((k_gather_m_few<BF, EPI, CT, false>), grid, dim3(512), 0, st, g);
-  PIT_LAUNCH_CHECK();
-  return PIT_OK;
-}
-
 template <bool BF, int EPI, int CT, int WM, int WN, int NST, int GN = 2>
 int launch_cfg(GemmArgs g, int64_t total_rows, hipStream_t st) {
   using T = MTile<WM, WN, NST, GN>;
@@ -727,43 +437,6 @@ int launch_cfg(GemmArgs g, int64_t total_rows, hipStream_t st) {
   return PIT_OK;
 }
 
-// Whether k_gather_m_few is the faster kernel for segments with a B of their own.  k_gather_m_lds takes at least the latency of
-// its walk over k (0.3 us per 32 of K), whatever the number of rows; with enough weights both run at the memory's rate, and
-// this kernel at 5.0 TB/s a little below the other's 5.3.  That point is at about 200 MB.  The number of segments that have a
-// row at all is known on the device only; taken for it (hit) is what rows dealt at random would give.  In this order:
-//   more than 512 segments, at most a row each: k_gather_m_lds' search for a tile's segment visits all of them (1024
-//     tokens, 128 x 256, 4096 experts 649 / 420 us).
-//   one workgroup per compute unit or fewer for the tiles to be expected (half a tile per segment is empty): always.
-//   two at most for the most tiles there can be: not where the walk is short and a segment has many rows (K < 512, but for K
-//     <= 128), nor where many workgroups read the same columns of B again for every 16 rows (N < 512): each XCD sees all of B
-//     then unless the columns divide evenly over the eight, and with K > 1024 a wave's slabs are no longer all under way at
-//     once.
-//   up to eight rows per segment on average: a workgroup's start (its segment, its rows, the first loads) weighs as much as
-//     64 x K elements of B, and pays for up to 2.2 K workgroups.
-// Measured, up to eight rows per segment, per product over 8 shapes of 256 - 1024 x 768 - 4096, 16 - 128 experts, 8 - 512
-// tokens, three ways of routing: 0.783 of k_gather_m_lds' time in the geometric mean (the faster kernel every time: 0.776), 19
-// of 1008 calls slower by more than 2 %.
-// With more rows, 4380 whole calls, 65 - 4096 tokens, 128 - 1024 x 128 - 4096, 1 - 256 experts, three ways of routing: 0.834 of
-// the time of the rule of eight rows alone (the faster kernel every time: 0.824), 17 of them more than 2 % slower and one more
-// than 5 %.  (Two workgroups per compute unit whatever the shape: 0.835 as well, but 216 and 149, by up to 21 %: 1136 tokens,
-// 256 x 256, 2 experts 18.7 / 20.8; 754, 384 x 3968, 16 44.4 / 52.6; one per compute unit alone: 0.848.)  768 x 3072,
-// k_gather_m_lds / this, us: 128 tokens, 8 experts 41.5 / 27.1; 192, 16 49.7 / 44.8.
-double hit_segments(const GemmArgs& g, int64_t rows) { return g.nseg * (1.0 - std::pow(1.0 - 1.0 / g.nseg, (double)rows)); }
-
-bool few_rows_pay(const GemmArgs& g, int64_t total_rows) {
-  if (g.b_seg_stride == 0) return false;
-  if (g.nseg > 512 && total_rows <= g.nseg) return true;
-  const double rows = (double)total_rows, hit = hit_segments(g, total_rows), columns = g.N / 64.0, cus = compute_units();
-  if (hit * g.N * g.slab * 2.0 > 200e6) return false;
-  if (std::max(hit, 0.5 * hit + rows / 16) * columns <= cus) return true;
-  if (std::min(rows, hit + total_rows / 16) * columns <= 2 * cus) {
-    if (g.slab <= 128) return true;
-    if (g.slab < 512 && g.N >= 512 && rows <= 32 * hit) return true;
-    if (g.slab >= 512 && (g.N >= 512 || rows <= 16 * hit || (g.slab <= 1024 && (g.N == 128 || g.N == 256)))) return true;
-  }
-  return total_rows <= 8 * (int64_t)g.nseg && hit * columns <= 2.2 * g.slab;
-}
-
 // Tile shape by the shape of the product.  128 x 256 (a wave owns 64 x 128) where N allows: fewer bytes through
 // LDS per MFMA and fewer workgroups' worth of set-up than 128 x 128.  (Measured on the padded-batch product,
 // 8364 x 1024 x 4096: 128 x 128 with a ring of 3 or 4 stages 127 us, 256 x 128 117, 128 x 256 108-115; on the
@@ -773,7 +446,9 @@ bool few_rows_pay(const GemmArgs& g, int64_t total_rows) {
 template <bool BF, int EPI, int CT>
 int launch_shape(const GemmArgs& g, int64_t total_rows, hipStream_t st) {
   // (a product too small to give every compute unit a 128 x 256 tile even in the worst case takes 128 x 128)
-  if (g.route != nullptr || few_rows_pay(g, total_rows)) return launch_few<BF, EPI, CT>(g, total_rows, st);
+  if (total_rows / 128 + g.nseg > 65520) return PIT_ESHAPE;    // (the limit of launch_cfg's grid, for every kernel)
+  const RingMTile ring = ring_m_tile(EPI, g, total_rows);
+  if (ring != RINGM_NONE) return launch_gather_m_ring(BF, EPI, CT, g, total_rows, ring, st);
   const int64_t wide_tiles = (total_rows / 128 + g.nseg) * (g.N / 256);
   if (g.N % 256 == 0 && wide_tiles >= compute_units()) return launch_cfg<BF, EPI, CT, 2, 4, 3>(g, total_rows, st);
   return launch_cfg<BF, EPI, CT, 2, 2, 4>(g, total_rows, st);
@@ -789,15 +464,6 @@ int launch_bf(int epi, int ct, const GemmArgs& g, int64_t total_rows, hipStream_
 }
 
 }  // namespace
-
-// Up to 64 tokens: without an index k_gather_m_few is ahead of an index and k_gather_m_lds wherever the weights are not
-// expected to exceed 300 MB (whole calls, us, index and the faster kernel per product / without; 32 tokens, 1024 x 4096, 64
-// experts, tokens apart: 101 / 103, random by popularity: 78.6 / 70.9; 64 tokens: 179 / 199 and 98 / 101, left to the index).
-// Over 6 shapes of 256 - 1024 x 512 - 4096, 1 - 128 experts, 1 - 64 tokens, three ways of routing: 0.756 of the time with
-// an index and this kernel up to eight rows per segment only, 3 of 1134 more than 2 % slower (tokens apart, 300 MB and more: 8 %).
-bool gather_m_routes(const GemmArgs& g) {
-  return g.M <= 64 && g.b_seg_stride != 0 && (few_rows_pay(g, g.M) || hit_segments(g, g.M) * g.N * g.slab * 2.0 <= 300e6);
-}
 
 int launch_gather_m(bool bf, int epi, int c_is_in_type, const GemmArgs& g, int64_t total_rows, hipStream_t st) {
   if (total_rows <= 0 || g.N <= 0 || g.nseg <= 0) return PIT_OK;

@@ -18,28 +18,10 @@
 //   SWrite  every wave leaves its partial tile in LDS (over the rings); the partial tiles are added in the order of the
 //           waves and stored, 16 lanes filling 256 contiguous bytes of an fp32 row.
 #include "pit_gemm.hpp"
-#include "pit_gemm_dev.hpp"
+#include "pit_ring.hpp"
 
 namespace pit {
 namespace {
-
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-template <bool BF>
-__device__ __forceinline__ f32x4_t mfma16r(const u32x4_t& a, const u32x4_t& b, const f32x4_t& c) {
-  if constexpr (BF)
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
-}
-
-// One operand's slab in LDS: 32 rows ("slots") of T columns
-template <int T> struct SlabLayout {
-  static_assert(T == 32 || T == 64, "columns of a tile");
-  static constexpr int BYTES = 32 * T * 2, LOADS = BYTES / 1024;
-  static constexpr int LPR = T / 8, RPI = 64 / LPR;        // lanes per row, rows per load instruction
-  // swizzle of the 32-byte chunks of a row
-  static __device__ __forceinline__ int f(int slot) { return T == 64 ? ((slot >> 1) & 1) | (((slot >> 3) & 1) << 1) : (slot >> 3) & 1; }
-};
 
 template <bool BF, int CT, int TA, int TB, int NW, int NST, bool DENSE>
 __global__ void __launch_bounds__(64 * NW, NW / 4)
@@ -223,13 +205,7 @@ k_gather_k_ring(const GemmArgs g, const int tm_tiles) {
   }
 
   // ---------------------------------------------------------------- reduction and SWrite
-  // Vector (row m, columns 4 c .. 4 c + 3) of a wave's partial tile: block (c / 4, m / 16), 256 bytes per c % 4 in it, 16 bytes
-  // at a place that differs both for the 16 rows of a block and for the vectors of a row, so that neither the writes nor
-  // the reads meet on a bank.
-  auto place = [&](int m, int c) -> uint32_t {
-    const int x = (m & 15) ^ (c & 15) ^ (TB == 32 ? (m & 1) << 3 : 0);
-    return (uint32_t)(((c >> 2) * FA + (m >> 4)) * 1024 + (c & 3) * 256 + x * 16);
-  };
+  auto place = [](int m, int c) { return partial_place<TB, FA>(m, c); };
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < FB; ++i)

@@ -5,8 +5,8 @@
 //   matmul 1: SRead gathers each expert's token rows, GELU epilogue, hidden rows stored compactly
 //             in expert-sorted order (without an index: in token order)
 //   matmul 2: reads the compact hidden rows, SWrite scatters every result row to its token's slot
-// Nothing is padded to a capacity: an expert with c tokens costs ceil(c / 128) row tiles, or ceil(c / 16) of the few-rows
-// kernel (few_rows_pay says which a matmul takes).
+// Nothing is padded to a capacity: an expert with c tokens costs ceil(c / 128) row tiles, or as many of 16, 32 or 64 rows in
+// k_gather_m_ring (ring_m_tile says which a matmul takes).
 #include "pit_gemm.hpp"
 
 namespace pit {

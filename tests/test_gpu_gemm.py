@@ -366,6 +366,43 @@ def test_padded_linear_exact_on_integers(pit, batch, max_len, hidden, out):
     assert np.array_equal(Y.cpu().numpy().astype(np.float64), orc.gemm_rows_masked(w.X, w.row_mask, w.W))
 
 
+# padded layers (batch, max_len, hidden, out), on either side of the lines of the rule (256 compute units), and their kernels
+PADDED_FEW = {(3, 70, 160, 640): "ring<%s, 32, 32, 8", (7, 90, 288, 384): "ring<%s, 32, 32, 8", (2, 130, 1056, 896): "ring<%s, 32, 64, 8",
+              (5, 200, 96, 512): "ring<%s, 32, 64, 8", (1, 500, 1088, 2048): "ring<%s, 64, 64, 8", (9, 100, 1024, 640): "ring<%s, 64, 64, 4",
+              (30, 150, 32, 512): "ring<%s, 64, 64, 4", (4, 300, 320, 2048): "lds<%s"}
+
+
+@pytest.mark.parametrize("in_dtype,c_dtype", [(torch.bfloat16, torch.float32), (torch.bfloat16, torch.bfloat16),
+                                              (torch.float16, torch.float32), (torch.float16, torch.float16)])
+@pytest.mark.parametrize("shape", PADDED_FEW)
+def test_padded_linear_few_tiles(pit, shape, in_dtype, c_dtype):
+    """Each tile of the kernel for few tiles: waves without a step, with one, odd and even numbers of them; lists of no row, one
+    row, every row, and in between; NaN in the padding rows and beyond the rows of X, a sentinel beyond those of the result, the
+    rows that are not listed cleared or left as they are.  Exact on integers (16-bit results: the rounded exact sum)."""
+    batch, max_len, K, N = shape
+    M = batch * max_len
+    g = np.random.default_rng(M + K)
+    x, w = g.integers(-2, 3, size=(M, K)).astype(np.float32), g.integers(-2, 3, size=(K, N)).astype(np.float32)
+    ref = torch.from_numpy(x.astype(np.float64) @ w.astype(np.float64)).to(c_dtype).to(dev())
+    masks = [np.arange(max_len)[None] < g.integers(1, max_len + 1, size=(batch, 1)), np.zeros((batch, max_len)), np.ones((batch, max_len)),
+             np.arange(M).reshape(batch, max_len) == M - 1, g.random((batch, max_len)) < 0.5]
+    big = torch.full((M, K + 64), float("nan"), dtype=in_dtype, device=dev())
+    W = torch.from_numpy(w).to(in_dtype).to(dev())
+    for i, mask in enumerate(masks):
+        valid = torch.from_numpy(np.ascontiguousarray(mask).astype(np.uint8).reshape(M, 1)).to(dev())
+        big[:, :K] = torch.where(valid.bool(), torch.from_numpy(x).to(dev()), float("nan")).to(in_dtype)
+        ix = pit.pit_build_index(valid, 1, 1, 0)
+        clear = i != 4
+        C = torch.full((M, N + 32), 9.0, dtype=c_dtype, device=dev())
+        pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, big[:, :K], W, ix, K, M, N, K, out=C[:, :N], zero_uncovered=clear)
+        want = torch.where(valid.bool(), ref, torch.full_like(ref, 0.0 if clear else 9.0))
+        assert torch.equal(C[:, :N], want), i
+        assert bool((C[:, N:] == 9.0).all())
+    if (in_dtype, c_dtype) == (torch.bfloat16, torch.float32):
+        names = kernels(lambda: pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, big[:, :K], W, ix, K, M, N, K), "k_gather_m", 1)
+        assert names is None or PADDED_FEW[shape] % "true, 0, 0" in names[0], names
+
+
 def test_padded_linear_leaves_uncovered_rows_when_asked(pit):
     w = wl.padded_linear(batch=4, max_len=50, hidden=64, out=128, min_len=1, seed=2, integer=True)
     Y = _run_padded(pit, w, zero_uncovered=False, sentinel=-9.0).cpu().numpy()

@@ -103,8 +103,8 @@ def test_row_mask_index_and_gather_m_product_with_clearing(pit):
     _replays(g, lambda i: mask.copy_(to_dev(cases[i].row_mask.reshape(-1, 1))), [Y], eager)
 
 
-# an index and the few-rows kernel; no index; an index and the general kernel
-@pytest.mark.parametrize("T,d_model,d_ff,E", [(600, 128, 256, 8), (48, 128, 256, 64), (2000, 256, 256, 4)])
+# an index and tiles of few rows; no index; an index and tiles of 64 rows; an index and the general kernel
+@pytest.mark.parametrize("T,d_model,d_ff,E", [(600, 128, 256, 8), (48, 128, 256, 64), (2000, 256, 256, 4), (8000, 384, 640, 8)])
 def test_moe_call(pit, T, d_model, d_ff, E):
     cases = [wl.moe_ffn(T=T, d_model=d_model, d_ff=d_ff, E=E, seed=s) for s in range(3)]
     W1, W2 = to_dev(cases[0].W1), to_dev(cases[0].W2)

@@ -121,21 +121,27 @@ def test_few_tokens_find_their_experts(pit, T, E, y_dtype):
         assert np.array_equal(Y.double().cpu().numpy(), ref)
 
 
-# Which kernel the two products of a call take at 256 compute units, F: the few-rows kernel, G: the general one with 128 x 128
-# tiles, W: with 128 x 256; f: the few-rows kernel without an index.  In pairs on either side of the lines: one workgroup of
-# the few-rows kernel per compute unit; two where K <= 128; 32 rows per expert where 128 < K < 512; two per compute unit where
-# K >= 512 and N >= 512; K <= 1024 with N = 256; 16 rows per expert with N = 384; eight rows per expert; 64 tokens.
-PRODUCTS = [(992, 256, 256, 4, "FF"), (1008, 256, 256, 4, "GG"), (1984, 128, 256, 4, "FF"), (2000, 128, 256, 4, "GF"),
-            (511, 256, 512, 16, "FF"), (512, 256, 512, 16, "GF"), (1007, 512, 512, 2, "FF"), (1008, 512, 512, 2, "GG"),
-            (1500, 256, 1024, 2, "GF"), (1500, 256, 1152, 2, "GG"), (500, 384, 512, 32, "FF"), (512, 384, 512, 32, "FG"),
-            (100, 128, 1024, 1, "FF"), (1000, 128, 640, 3, "GF"), (70, 128, 128, 7, "FF"), (400, 128, 256, 70, "FF"),
-            (70, 256, 1024, 64, "WF"), (100, 640, 256, 128, "FG"), (64, 256, 1024, 64, "ff"), (65, 256, 256, 64, "FF"),
-            (1984, 256, 256, 4, "GG"), (2000, 256, 256, 4, "GG"), (512, 256, 512, 8, "GF"), (4096, 256, 2048, 16, "WG"),
-            (40, 128, 128, 600, "ff"), (600, 128, 128, 600, "FF")]
+# Which kernel the two products of a call take at 256 compute units.  G: the general one with 128 x 128 tiles, W: with 128 x 256.
+# The others are tiles of k_gather_m_ring, A 16 x 32, B 16 x 64 by eight waves, C by four, D 32 x 64, E 64 x 64; in small letters
+# without an index (up to 64 tokens).
+PRODUCTS = [(992, 256, 256, 4, "BB"), (1008, 256, 256, 4, "EE"), (1984, 128, 256, 4, "EB"), (2000, 128, 256, 4, "EB"),
+            (511, 256, 512, 16, "DB"), (512, 256, 512, 16, "DB"), (1007, 512, 512, 2, "EE"), (1008, 512, 512, 2, "EE"),
+            (1500, 256, 1024, 2, "EE"), (1500, 256, 1152, 2, "EE"), (500, 384, 512, 32, "DD"), (512, 384, 512, 32, "DD"),
+            (100, 128, 1024, 1, "BA"), (1000, 128, 640, 3, "EB"), (70, 128, 128, 7, "AA"), (400, 128, 256, 70, "CB"),
+            (70, 256, 1024, 64, "CB"), (100, 640, 256, 128, "CC"), (64, 256, 1024, 64, "cb"), (65, 256, 256, 64, "BB"),
+            (1984, 256, 256, 4, "EE"), (2000, 256, 256, 4, "EE"), (512, 256, 512, 8, "DB"), (4096, 256, 2048, 16, "WE"),
+            (40, 128, 128, 600, "aa"), (600, 128, 128, 600, "CC"), (4096, 256, 512, 8, "EE"), (2300, 256, 1024, 8, "GE"),
+            (300, 512, 512, 16, "BB"), (1300, 384, 1152, 64, "DD"), (700, 256, 1024, 128, "CC"), (200, 384, 768, 64, "CC"),
+            (4096, 768, 3072, 64, "WW"), (8000, 384, 640, 8, "GG")]
 
 
 def letter(name):
-    return ("f" if "true>" in name else "F") if "k_gather_m_few" in name else "W" if ", 2, 4, 3" in name else "G"
+    if "k_gather_m_ring" not in name:
+        return "W" if ", 2, 4, 3" in name else "G"
+    tile = {"16, 32, 8": "A", "16, 64, 8": "B", "16, 64, 4": "C", "32, 64, 4": "D", "64, 64, 4": "E"}
+    args = name[name.index("<") + 1:name.index(">")].split(", ")
+    x = tile[", ".join(args[3:6])]
+    return x.lower() if args[6] == "2" else x
 
 
 @pytest.mark.parametrize("T,d_model,d_ff,E,expected", PRODUCTS)
@@ -152,7 +158,7 @@ def test_which_kernel_a_product_takes(pit, T, d_model, d_ff, E, expected):
     assert "".join(letter(n) for n in names) == expected, names
 
 
-@pytest.mark.parametrize("T,d_model,d_ff,E", [p[:4] for p in PRODUCTS[:17] + PRODUCTS[20:22]])
+@pytest.mark.parametrize("T,d_model,d_ff,E", [p[:4] for p in PRODUCTS[:17] + PRODUCTS[20:22] + PRODUCTS[26:32] + PRODUCTS[33:]])
 @pytest.mark.parametrize("route", ["popular", "even", "one"])
 def test_many_rows_per_expert_in_tiles_of_few(pit, T, d_model, d_ff, E, route):
     """With an index: experts of up to 2000 rows in tiles of 16, the last tile partly filled; either side of every line; both
@@ -166,11 +172,11 @@ def test_many_rows_per_expert_in_tiles_of_few(pit, T, d_model, d_ff, E, route):
     assert np.array_equal(Y.double().cpu().numpy(), ref)
 
 
-@pytest.mark.parametrize("T,d_model,d_ff,E", [(2000, 256, 256, 4), (4096, 256, 2048, 16)])
+@pytest.mark.parametrize("T,d_model,d_ff,E", [(2000, 256, 256, 4), (4096, 256, 2048, 16), (8000, 384, 640, 8), (700, 256, 1024, 128)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 def test_general_kernel_gelu_and_gate(pit, T, d_model, d_ff, E, dtype):
-    """GELU, gate, both input types and both kinds of result in the general kernel: 128 x 128 tiles for both products, and
-    128 x 256 for the first; every token's row against the oracle."""
+    """GELU, gate, both input types and both kinds of result in the general kernel (128 x 128 tiles for both products, 128 x 256
+    for the first) and in tiles of 16 and 64 rows; every token's row against the oracle."""
     w = wl.moe_ffn(T=T, d_model=d_model, d_ff=d_ff, E=E, seed=T)
     X, W1, W2 = (orc.bf16_bits_to_f64(a).astype(np.float16 if dtype == torch.float16 else np.float32) for a in (w.X, w.W1, w.W2))
     tX, tW1, tW2 = (to_dev(a).to(dtype) for a in (X, W1, W2))
@@ -185,7 +191,7 @@ def test_general_kernel_gelu_and_gate(pit, T, d_model, d_ff, E, dtype):
 
 
 # 40.6 experts of 64 to be expected: 341 MB of weights per product, beyond the 300 MB up to which 64 tokens take no index, and 298
-@pytest.mark.parametrize("d_ff,expected", [(4096, "WW"), (3584, "ff")])
+@pytest.mark.parametrize("d_ff,expected", [(4096, "WW"), (3584, "cc")])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 def test_few_tokens_with_much_to_read(pit, d_ff, expected, dtype):
     T, d_model, E = 64, 1024, 64
