@@ -62,6 +62,9 @@ int launch_gather_k_ring(bool bf, int c_is_in_type, const GemmArgs& g, RingTile 
 enum RingMTile { RINGM_NONE, RINGM_16x32, RINGM_16x64, RINGM_16x64_8, RINGM_32x32, RINGM_32x64, RINGM_32x64_8, RINGM_64x64, RINGM_64x64_8 };
 RingMTile ring_m_tile(int epi, const GemmArgs& g, int64_t total_rows);
 int launch_gather_m_ring(bool bf, int epi, int c_is_in_type, const GemmArgs& g, int64_t total_rows, RingMTile tile, hipStream_t st);
+// the same for several k-slabs per row (micro-tiles along k), fp32 results
+RingMTile ring_slab_tile(const GemmArgs& g);
+int launch_slab_ring(bool bf, const GemmArgs& g, RingMTile tile, hipStream_t st);
 // GATHER_M with several k-slabs per row (pit_slab.hip); fp32 results
 int launch_slab_strip(bool bf, const GemmArgs& g, hipStream_t st);
 

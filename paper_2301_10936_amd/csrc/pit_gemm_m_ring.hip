@@ -11,20 +11,24 @@
 //           operands read with the transposing LDS read.
 //   SWrite  partial tiles added in the order of the waves; rows go where the index says, 16 lanes filling 256 contiguous bytes of
 //           an fp32 row.  The rows that a list does not name are cleared by the workgroups without a tile, when asked for.
+//   SLABS   micro-tiles along k: the tile's rows are those of C; which of them a slab lists comes as bits in LDS
+//           (build_slab_masks, while the first operands travel), and the A operands of the others are set to zero in registers.
 // Product alone, k_gather_m_lds / here, us: 186 rows (140 listed) x 1408 x 384 14.6 / 4.0, 732 (308) x 1920 x 1792 19.0 / 7.8, 2911 x
 // 1408 x 512 14.2 / 7.8.  Whole mixture-of-experts calls, us, before (segments of few rows went to a kernel with the weights in
 // registers) / here: 1 token, 896 x 1792, 8 experts 11.6 / 8.0; 48, 768 x 3072, 64 43.4 / 40; 515, 640 x 1920, 8 31.6 / 21.5.
 // Tried: four steps per ring (fewer workgroups per compute unit: up to 1.7 times the time), three with 16 x 64 and eight waves (the same).
 #include "pit_ring.hpp"
 #include "pit_gather_m.hpp"
+#include "pit_slab_masks.hpp"
 #include <algorithm>
 #include <cmath>
 
 namespace pit {
 namespace {
 
-// where the rows of the tiles come from: one list; a list per segment, each with a B of its own; the expert ids of up to 64 tokens
-enum { ONE, SEGMENTS, ROUTE };
+// where the rows of the tiles come from: one list; a list per segment, each with a B of its own; the expert ids of up to 64 tokens;
+// all rows, with a list per k-slab of those that count
+enum { ONE, SEGMENTS, ROUTE, SLABS };
 
 template <bool BF, int EPI, int CT, int TR, int TC, int NW, int MODE>
 __global__ void __launch_bounds__(64 * NW, 2)
@@ -35,6 +39,8 @@ k_gather_m_ring(const GemmArgs g) {
   constexpr int FA = TR / 16, FB = TC / 16;
   constexpr int RING = NW * NST * STAGE, PART = TR * TC * 4;
   __shared__ __attribute__((aligned(1024))) char smem[RING > NW * PART ? RING : NW * PART];
+  constexpr int MW = (TR + 31) / 32;                       // SLABS: words of the rows listed for a slab
+  __shared__ uint32_t s_mask[MODE == SLABS ? SLABS_MAX * MW : 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(PIT_LDS char*)smem, ring = lds0 + (uint32_t)(wv * NST * STAGE);
@@ -45,7 +51,15 @@ k_gather_m_ring(const GemmArgs g) {
   const int lin = blockIdx.x, xcd = lin & 7, slot = lin >> 3;
   int n0, begin = 0, cnt, seg = 0;
   int rows = 0;                                            // ROUTE: lane r holds the token of the tile's row r
-  if constexpr (MODE == ONE) {
+  if constexpr (MODE == SLABS) {
+    const int rt = (g.M + TR - 1) / TR, total = rt * tn;
+    const int lp = xcd * (total >> 3) + min(xcd, total & 7) + slot;
+    const bool down = rt <= tn;
+    const int outer = lp / (down ? rt : tn), inner = lp - outer * (down ? rt : tn);
+    n0 = (down ? outer : inner) * TC;
+    begin = (down ? inner : outer) * TR;
+    cnt = min(TR, g.M - begin);
+  } else if constexpr (MODE == ONE) {
     const int begin0 = g.seg_ptr[0], cnt0 = g.seg_ptr[1] - begin0;
     const int rt = (cnt0 + TR - 1) / TR, total = rt * tn;
     const int share = (total >> 3) + (xcd < (total & 7) ? 1 : 0);
@@ -171,7 +185,7 @@ k_gather_m_ring(const GemmArgs g) {
   const char* a_src = uniform_ptr(g.A);
   const char* b_src = uniform_ptr(reinterpret_cast<const char*>(g.B) + (int64_t)seg * g.b_seg_stride * 2);
   const uint32_t pitch_a = (uint32_t)(g.lda * 2), pitch_b = (uint32_t)(g.ldb * 2);
-  const int nsteps = g.slab / KS;
+  const int nsteps = (MODE == SLABS ? g.K : g.slab) / KS;
   const int n_w = nsteps > wv ? (nsteps - wv + NW - 1) / NW : 0;
   uint32_t b_off[NB];
 #pragma unroll
@@ -192,7 +206,7 @@ k_gather_m_ring(const GemmArgs g) {
 #pragma unroll
   for (int j = 0; j < NA; ++j) {
     const int r = 16 * j + (lane >> 2), p = begin + min(r, cnt - 1);       // rows past the end: the last one, never stored
-    a_off[j] = __umul24((uint32_t)(MODE == ROUTE ? __shfl(rows, min(r, cnt - 1)) : g.a_gather ? g.idx[p] : p), pitch_a) + (uint32_t)(((lane & 3) ^ ((r >> 2) & 3)) * 16);
+    a_off[j] = __umul24((uint32_t)(MODE == ROUTE ? __shfl(rows, min(r, cnt - 1)) : MODE != SLABS && g.a_gather ? g.idx[p] : p), pitch_a) + (uint32_t)(((lane & 3) ^ ((r >> 2) & 3)) * 16);
   }
   auto issue_a = [&](int t, int u) {
     const uint32_t at = ring + (uint32_t)(u * STAGE), k = (uint32_t)(KS * (wv + NW * t)) * 2u;
@@ -231,6 +245,25 @@ k_gather_m_ring(const GemmArgs g) {
 #pragma unroll
     for (int u = 0; u < NST; ++u)
       if (u < n_w) issue_a(u, u);
+  }
+  // SLABS: which rows of the tile each slab lists, as bits (the first operands are on their way meanwhile)
+  if constexpr (MODE == SLABS) {
+    build_slab_masks<(TR < 32 ? 32 : TR), NW>(g, begin, s_mask, tid);
+  }
+  const uint32_t per_k = 0xffffffffu / (uint32_t)g.slab + 1u;      // k / slab by its reciprocal: exact below 2^32 / slab
+  auto slab_of = [&](int t) { return (int)__umulhi((uint32_t)(KS * (wv + NW * t)), per_k); };
+  auto listed = [&](int t, int c) -> bool {                // is this lane's row of block c listed for step t?
+    return (s_mask[slab_of(t) * MW + (c >> 1)] >> ((c & 1) * 16 + (lane & 15))) & 1u;
+  };
+  auto mask_rows = [&](int t, Frags& fr) {
+    if constexpr (MODE == SLABS) {
+#pragma unroll
+      for (int c = 0; c < FA; ++c) {
+        fr.a[c] &= listed(t, c) ? 0xffffffffu : 0u;
+      }
+    }
+  };
+  if (n_w > 0) {
     // under way after the wait for a step: the loads of the next one (of step 1 ahead of step 0's wait its A loads: the B loads of
     // both were issued before)
     if (n_w > 1) PIT_WAIT_VMCNT(NA);
@@ -244,6 +277,7 @@ k_gather_m_ring(const GemmArgs g) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage has been read
         issue_a(t + u + 2, u);
         issue_b(t + u + 2, u);
+        mask_rows(t + u, fr);
         mfmas(fr);
         PIT_WAIT_VMCNT(LOADS);
       }
@@ -255,9 +289,46 @@ k_gather_m_ring(const GemmArgs g) {
         issue_a(t + 2, t & 1);
         issue_b(t + 2, t & 1);
       }
+      mask_rows(t, fr);
       mfmas(fr);
       if (t + 2 < n_w) PIT_WAIT_VMCNT(LOADS);
       else PIT_WAIT_VMCNT(0);
+    }
+    if constexpr (MODE == SLABS) {
+      // An infinity or a NaN in B must not reach the rows that are not listed.  It reaches all rows of its column here (0 x inf is a
+      // NaN), so sums that are all finite met none; otherwise the wave takes its steps again, each into registers of its own,
+      // and adds the listed rows' results.
+      float big = 0.f;
+#pragma unroll
+      for (int i = 0; i < FB; ++i)
+#pragma unroll
+        for (int j = 0; j < FA; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) big = fmaf(acc[i][j][e], 0.f, big);    // 0 or a NaN
+      if (__any(big != 0.f)) {
+#pragma unroll
+        for (int i = 0; i < FB; ++i)
+#pragma unroll
+          for (int j = 0; j < FA; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (t = 0; t < n_w; ++t) {
+          issue_a(t, 0);
+          issue_b(t, 0);
+          PIT_WAIT_VMCNT(0);
+          read_frags(0, fr);
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+          for (int j = 0; j < FA; ++j) {
+            const bool on = listed(t, j);
+#pragma unroll
+            for (int i = 0; i < FB; ++i) {
+              const f32x4_t p = mfma16r<BF>(fr.b[i], fr.a[j], f32x4_t{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[i][j][e] = on ? acc[i][j][e] + p[e] : acc[i][j][e];
+            }
+          }
+        }
+      }
     }
   }
 
@@ -275,8 +346,9 @@ k_gather_m_ring(const GemmArgs g) {
     const int m = (tid + 64 * NW * v) / VPR;
     const int tok = MODE == ROUTE ? __shfl(rows, min(m, cnt - 1)) : 0;
     if constexpr (MODE == ROUTE) crow[v] = m < cnt ? tok : -1;
+    else if constexpr (MODE == SLABS) crow[v] = m < cnt ? begin + m : -1;
     else crow[v] = m < cnt ? (g.c_scatter ? g.idx[begin + m] : begin + m) : -1;
-    scale[v] = EPI == EPI_STORE && MODE != ONE && g.gate && m < cnt ? g.gate[crow[v]] : 1.f;
+    scale[v] = EPI == EPI_STORE && MODE != ONE && MODE != SLABS && g.gate && m < cnt ? g.gate[crow[v]] : 1.f;
   }
   __syncthreads();
 #pragma unroll
@@ -293,7 +365,7 @@ k_gather_m_ring(const GemmArgs g) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       if constexpr (EPI == EPI_GELU) s[e] = gelu_erf_fast(s[e]);
-      if constexpr (EPI == EPI_STORE && MODE != ONE) s[e] *= scale[v];
+      if constexpr (EPI == EPI_STORE && MODE != ONE && MODE != SLABS) s[e] *= scale[v];
     }
     const int64_t o = (int64_t)crow[v] * g.ldc + n0 + 4 * c;
     if constexpr (CT == 0) *reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(g.C) + o) = s;
@@ -305,7 +377,7 @@ template <bool BF, int EPI, int CT, int TR, int TC, int NW, int MODE>
 int launch_tile(const GemmArgs& g, int64_t total_rows, hipStream_t st) {
   // (where unlisted rows are to be cleared, one workgroup more for every 64 rows of C: whatever the list holds, none without a tile
   // looks at more than a chunk of 64 rows.  With 8 more, a full list of 4070 rows: 13.2 us instead of 6.)
-  const int64_t row_tiles = MODE != ONE ? std::min<int64_t>(total_rows, total_rows / TR + g.nseg) : ceil_div(total_rows, TR);
+  const int64_t row_tiles = MODE != ONE && MODE != SLABS ? std::min<int64_t>(total_rows, total_rows / TR + g.nseg) : ceil_div(total_rows, TR);
   const int64_t wgs = row_tiles * (g.N / TC) + (g.zero_rest ? ceil_div(g.M, 64) : 0);
   hipLaunchKernelGGL((k_gather_m_ring<BF, EPI, CT, TR, TC, NW, MODE>), dim3((unsigned)wgs), dim3(64 * NW), 0, st, g);
   PIT_LAUNCH_CHECK();
@@ -313,7 +385,7 @@ int launch_tile(const GemmArgs& g, int64_t total_rows, hipStream_t st) {
 }
 template <bool BF, int EPI, int CT, int MODE>
 int launch_mode(const GemmArgs& g, int64_t total_rows, RingMTile tile, hipStream_t st) {
-  if constexpr (MODE == ONE) {
+  if constexpr (MODE == ONE || MODE == SLABS) {
     switch (tile) {
       case RINGM_32x32: return launch_tile<BF, EPI, CT, 32, 32, 8, MODE>(g, total_rows, st);
       case RINGM_32x64_8: return launch_tile<BF, EPI, CT, 32, 64, 8, MODE>(g, total_rows, st);
@@ -402,6 +474,30 @@ RingMTile ring_m_tile(int epi, const GemmArgs& g, int64_t total_rows) {
 bool gather_m_routes(const GemmArgs& g) {
   if (g.M > 64 || g.b_seg_stride == 0 || ring_m_tile(EPI_STORE, g, g.M) == RINGM_NONE) return false;
   return g.nseg > 512 || hit_segments(g, g.M) * g.N * g.slab * 2.0 <= 300e6;
+}
+
+// Micro-tiles along k: all rows of a tile are multiplied, those that a slab does not list as zeros, where that takes less time than
+// strips of C in LDS over the listed rows alone (pit_slab.hip): the strips' time is their chain of list searches and visits.  How
+// many rows are listed the device knows.  Product alone, us, strips / 32 x 32, 32 x 64, 64 x 64 by four waves, by eight (rows listed in %):
+//   327 x 3648 x 256, 1 x 64 (30 %, 24 tiles of 64 x 64) 24.5 / 12.0, 13.9, 17.2, 14.2;  930 x 2496 x 256, 1 x 64 (6 %, 60) 17.7 / 9.9, 9.9, 13.7, 11.9
+//   538 x 1984 x 768, 1 x 64 (10 %, 108) 13.9 / 11.5, 9.4, 11.3, 11.0;  401 x 832 x 1408, 1 x 64 (46 %, 154) 11.8 / 14.7, 15.0, 8.9, 8.7
+//   1024^3, 1 x 32 (10 %, 256) 12.2 / 17.5, 15.3, 9.4, 9.7;  1229 x 3072 x 512, 1 x 32 (8 %, 160) 29.4 / 31.5, 30.4, 22.0, 19.6
+// The line is at one workgroup of 64 x 64 per compute unit: beyond it the strips are ahead where few rows are listed (2097 x 1216 x 512,
+// 1 x 64, 1 %, 264 tiles: 10.0 / 11.2 by four waves; 755 x 3456 x 1536, 1 x 128, 11 %, 288: 22.9 / 25.2), but for the 32-wide slabs that cost them most
+// (1669 x 1984 x 640, 16 %, 270: 24.6 / 19.5; 321 x 1568 x 3456, 4 %, 324: 21.2 / 14.8; 2295 x 1504 x 768, 7 %, 432: 20.9 / 17.3; not with a long
+// k: 488 x 4032 x 2816, 2 %, 352: 28.2 / 34.3).  Up to it, 40 products of 300 - 4096 x 512 - 4096 x 256 - 4096: 0.77, the slowest 1.07 (1529 x 512 x 384, 1 x
+// 128, 2 %).
+RingMTile ring_slab_tile(const GemmArgs& g) {
+  const int64_t cus = compute_units(), t64 = ceil_div(g.M, 64) * (g.N / 64);
+  if (g.nseg > SLABS_MAX || g.K > (1 << 16)) return RINGM_NONE;
+  if (4 * t64 <= cus) return RINGM_32x32;
+  if (2 * t64 <= cus) return RINGM_32x64_8;
+  if (t64 <= cus) return g.K > 2048 ? RINGM_64x64_8 : RINGM_64x64;
+  return g.slab == 32 && 4 * t64 <= 7 * cus && g.K <= 2048 ? RINGM_64x64 : RINGM_NONE;
+}
+
+int launch_slab_ring(bool bf, const GemmArgs& g, RingMTile tile, hipStream_t st) {
+  return bf ? launch_mode<true, EPI_STORE, 0, SLABS>(g, g.M, tile, st) : launch_mode<false, EPI_STORE, 0, SLABS>(g, g.M, tile, st);
 }
 
 int launch_gather_m_ring(bool bf, int epi, int c_is_in_type, const GemmArgs& g, int64_t total_rows, RingMTile tile, hipStream_t st) {

@@ -2,6 +2,7 @@
 // (paper Section 3.1, sparse kernel template), for gfx950.  bf16 or f16 inputs, fp32 accumulation and results.
 //   k_slab_strip       strips of 32 x 128 (four per workgroup, added at the end)
 //   k_slab_strip_tall  the same for products that fill the chip with strips of 64 or 128 rows
+//   (k_gather_m_ring, pit_gemm_m_ring.hip, takes products with few tiles: ring_slab_tile)
 // Which one: the rule is at launch_slab_strip_bf.
 #include "pit_gemm.hpp"
 #include "pit_gemm_dev.hpp"
@@ -629,6 +630,8 @@ int launch_slab_strip_bf(const GemmArgs& g, hipStream_t st) {
 }  // namespace
 
 int launch_slab_strip(bool bf, const GemmArgs& g, hipStream_t st) {
+  const RingMTile ring = ring_slab_tile(g);
+  if (ring != RINGM_NONE) return launch_slab_ring(bf, g, ring, st);
   return bf ? launch_slab_strip_bf<true>(g, st) : launch_slab_strip_bf<false>(g, st);
 }
 

@@ -541,6 +541,72 @@ def test_microtile_wider_slab(pit):
     assert np.array_equal(C.cpu().numpy().astype(np.float64), orc.gemm(w.A, w.B))
 
 
+# micro-tiles along k (M, K, N, mt) on either side of the lines of ring_slab_tile (256 compute units), and their kernels
+SLABS_FEW = {(300, 256, 384, 32): "ring<%s, 32, 32, 8", (1000, 576, 256, 64): "ring<%s, 32, 32, 8", (70, 2080, 4096, 32): "ring<%s, 32, 64, 8",
+             (500, 1152, 1024, 128): "ring<%s, 32, 64, 8", (1000, 384, 1024, 96): "ring<%s, 64, 64, 4", (4100, 320, 128, 64): "ring<%s, 64, 64, 4",
+             (900, 2112, 1024, 64): "ring<%s, 64, 64, 8", (1500, 96, 1152, 32): "ring<%s, 64, 64, 4", (1500, 128, 1152, 64): "strip"}
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("shape", SLABS_FEW)
+def test_microtile_few_tiles(pit, shape, dtype):
+    """Each tile of the kernel for few tiles.  An index of the caller's own, which lists fewer micro-tiles than hold something: what
+    it does not list counts for nothing, whatever is in it (NaN in A there) and whatever B holds in those rows (an infinity, a
+    NaN).  Lists of no row, of every row, of runs, of single rows; pitches beyond the rows, a sentinel beyond the result.  Exact
+    on integers; then the places of the infinities and NaN."""
+    M, K, N, mt = shape
+    g = np.random.default_rng(M + K)
+    nseg = K // mt
+    listed = g.random((nseg, M)) < g.choice([0.0, 0.02, 0.3, 1.0], size=(nseg, 1))
+    listed[nseg // 2] = (np.arange(M) // 40) % 3 == 0
+    listed[-1] = np.arange(M) == M - 1
+    a, b = g.integers(-2, 3, size=(M, K)).astype(np.float32), g.integers(-2, 3, size=(K, N)).astype(np.float32)
+    on = np.repeat(listed.T, mt, axis=1)
+    ref = np.where(on, a, 0).astype(np.float64) @ b.astype(np.float64)
+    bigA, bigB = torch.full((M, K + 8), float("nan"), dtype=dtype, device=dev()), torch.full((K, N + 128), float("nan"), dtype=dtype, device=dev())
+    bigA[:, :K] = torch.from_numpy(np.where(on, a, np.where(g.random((M, K)) < 0.1, np.nan, a))).to(dtype)
+    bigB[:, :N] = torch.from_numpy(b).to(dtype)
+    A, B = bigA[:, :K], bigB[:, :N]
+    seg = np.concatenate([[0], np.cumsum(listed.sum(1))]).astype(np.int32)
+    idx = np.concatenate([np.nonzero(r)[0] for r in listed]).astype(np.int32)
+    ix = pit.PitIndex(to_dev(seg), to_dev(idx), None, nseg, len(idx))
+
+    def product():
+        C = torch.full((M, N + 32), 9.0, device=dev())
+        pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, A, B, ix, mt, M, N, K, out=C[:, :N])
+        assert bool((C[:, N:] == 9.0).all())
+        return C[:, :N].double().cpu().numpy()
+
+    assert np.array_equal(product(), ref)
+    for k, n, v in ((K - 1, 3, np.inf), (mt * (nseg // 2), N - 1, np.nan), (0, 64, -np.inf)):
+        B[k, n] = v
+        s = k // mt
+        with np.errstate(invalid="ignore"):
+            ref[listed[s], n] += a[listed[s], k].astype(np.float64) * v
+    got = product()
+    assert np.array_equal(got, ref, equal_nan=True)
+    names = kernels(product, "k_", 1)
+    assert names is None or (SLABS_FEW[shape] % "false, 0, 0" if dtype == torch.float16 and "ring" in SLABS_FEW[shape]
+                             else SLABS_FEW[shape] % "true, 0, 0" if "ring" in SLABS_FEW[shape] else "k_slab_strip") in names[0], names
+
+
+@pytest.mark.parametrize("M,K,N,mt,p", [(1024, 4096, 1024, 64, 0.5), (2048, 1600, 512, 64, 0.4)])
+def test_microtile_few_tiles_rounds_no_more_than_strips(pit, M, K, N, mt, p):
+    """Against 64 bits: the four or eight waves' chains against the four chains of the 32-row strips (the same product with so many
+    more columns, 576 tiles of 64 x 64, that those take it); both are estimates over a million elements: 5 %."""
+    g = torch.Generator(device="cuda").manual_seed(K)
+    keep = (torch.rand((M, K // mt), generator=g, device="cuda") < p).repeat_interleave(mt, dim=1)
+    A, B = (torch.randn((M, K), generator=g, device="cuda") * keep).to(torch.bfloat16), torch.randn((K, N), generator=g, device="cuda").to(torch.bfloat16)
+    ix = pit.pit_build_index(A, 1, mt, 0)
+    run = lambda w: pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, A, w, ix, mt, M, w.shape[1], K)
+    ref = A.double() @ B.double()
+    wide = torch.cat([B] * 3, dim=1)[:, :64 * 576 // (M // 64)]
+    few, strips = run(B) - ref, run(wide)[:, :N] - ref
+    names = kernels(lambda: run(wide), "k_slab", 1)
+    assert names is None or "k_slab_strip<" in names[0], names
+    assert float(few.norm()) <= 1.05 * float(strips.norm()), (float(few.norm() / ref.norm()), float(strips.norm() / ref.norm()))
+
+
 # strips of 64 rows (one or two k-steps per visit) and of 128 rows: last strips of 32, 56, 72 and 1 rows, more than 64 slabs,
 # three visits per slab, lists of up to two blocks, of many blocks and of every row, both types; 5, 9 and 13 tile columns
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
