@@ -44,6 +44,7 @@ typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef short v4i16_t __attribute__((__vector_size__(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x16_t __attribute__((ext_vector_type(16)));
 #define PIT_LDS __attribute__((address_space(3)))
 
 constexpr int QB = 32;          // queries per block (micro-tile height)
@@ -69,7 +70,13 @@ typedef float f32x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void split_bf16x2(float a, float b, uint32_t& hi2, uint32_t& lo2) {
   const f32x2_t v = {a, b};
   hi2 = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
-  const f32x2_t r = {a - __builtin_bit_cast(float, hi2 << 16), b - __builtin_bit_cast(float, hi2 & 0xFFFF0000u)};
+  // (a - hi(a) as a product of pairs with (-1, 0): one instruction where the shift and the subtraction are two.  The pairs are
+  // opaque registers: as a literal the compiler takes (-1, 0) for the inline constant -1.0.)
+  uint32_t first = 0x0000bf80u, second = 0xbf800000u;
+  asm("" : "+s"(first), "+s"(second));
+  const bf16x2_t h = __builtin_bit_cast(bf16x2_t, hi2);
+  const f32x2_t r = {__builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2_t, first), a, false),
+                     __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2_t, second), b, false)};
   lo2 = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2_t));
 }
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
@@ -100,6 +107,16 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)"
 // wait for this wave's LDS operations (reads of a tile must have returned before a direct load refills it)
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// the larger (the sum) of a lane's value and that of the lane 32 away: an exchange of the wave's halves in registers
+__device__ __forceinline__ float max_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+  return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
+}
+__device__ __forceinline__ float add_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+
 // byte offset of 16-byte chunk c16 (8 d) of key row r inside a V tile [32 keys][64 d]; the two
 // 64-byte halves of a row are swapped on rows with (r >> 1) odd so that the 4 consecutive rows a
 // transposing read touches land in 4 different quarters of the 256-byte bank row.
@@ -107,6 +124,10 @@ __device__ __forceinline__ uint32_t v_off(int r, int c16) {
   return (uint32_t)(r * 128 + ((((c16 >> 2) ^ ((r >> 1) & 1)) << 6) | ((c16 & 3) << 4)));
 }
 
+// Bound by vector instructions: about 200 of them a chunk beside 12 matrix instructions (bf16), the vector units busy 65 - 70 % of the
+// time, the matrix units 24 % (12 heads, S = 4096, window 256 and 5 %).  With the occupancy words as lane masks in scalar
+// registers, the wave's halves exchanged by v_permlane32_swap, the halves' sums met once at the end and the remainders of P from
+// one instruction each, that call went from 28.6 to 27.6 us; error against 64 bits 0.999 - 1.000 of the former one.
 // OT: 0 = fp32, 1 = bf16, 2 = fp16 output; NW waves per workgroup (the rule is at the launch)
 template <bool BF, int OT, int NW>
 __global__ void __launch_bounds__(64 * NW, 3)
@@ -116,8 +137,8 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   // per wave (private): two V tiles and one K tile of 4 KiB; after the loop the first 8 KiB carry partial outputs to another
   // wave (32 floats per lane, laid out [value][lane]) and the next 512 bytes per chain its maxima and sums
   __shared__ __attribute__((aligned(1024))) char s_kv[NW][3 * V_TILE_BYTES];
-  // per wave, for two chunks: the 32 listed keys, then their 32 occupancy words
-  __shared__ __attribute__((aligned(256))) uint32_t s_list[NW][2][2 * KC];
+  // per wave, for two chunks: the 32 listed keys
+  __shared__ __attribute__((aligned(256))) uint32_t s_list[NW][2][KC];
 
   // Consecutive workgroup ids go to different XCDs (8, each with its own L2): renumber so that an XCD
   // works on a contiguous run of (head, query block) pairs, i.e. on the K and V of one or two heads
@@ -146,7 +167,20 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   for (int ks = 0; ks < 4; ++ks)
     qf[ks] = *reinterpret_cast<const uint4*>(Q + head_off + (int64_t)(qb * QB + ql) * HD + ks * 16 + h * 8);
 
-  float m_run = -INFINITY, l_run = 0.f;
+  // Scores are scaled inside the exponent, exp2(scale (s - max s)): exactly 1 at the largest, and a small difference times the scale
+  // has less to round than a score times the scale.  That wants scale > 0: a negative one changes the signs of Q instead (exact); with zero, an
+  // infinity or NaN the scores are scaled beforehand.
+  float scale = scale_log2e;
+  if (scale < 0.f) {
+    scale = -scale;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) { qf[ks].x ^= 0x80008000u; qf[ks].y ^= 0x80008000u; qf[ks].z ^= 0x80008000u; qf[ks].w ^= 0x80008000u; }
+  }
+  const bool scale_first = !(scale > 0.f && scale < INFINITY);
+  const float first_scale = scale;
+  if (scale_first) scale = 1.f;
+
+  float m_run = -INFINITY, l_run = 0.f;             // (l_run: this lane's half of the keys; the halves meet after the loop)
   f32x16_t o[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t)
@@ -159,7 +193,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   const char* v_head = reinterpret_cast<const char*>(V + head_off);
 
   // This wave's chunks: those of chain wv, then (two waves) those of chain wv + 2; a chain has every fourth.  The tiles
-  // and the mask words in LDS are private to the wave, so the loop needs no workgroup barrier, and it is
+  // and the lists in LDS are private to the wave, so the loop needs no workgroup barrier, and it is
   // software-pipelined: while chunk i is computed, the list entries of chunk i + 2 and the K and V rows of chunk i + 1
   // are under way.
   const int n_first = nchunks > wv ? (nchunks - wv + 3) >> 2 : 0;
@@ -169,7 +203,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   // row, so that every 128-byte line is requested once; the place of a 16-byte piece inside its row of the
   // tile (the bank swizzle) is expressed by which piece of the source row a lane asks for.
   // Every load is unconditional: positions past the end of the list (in the last chunk, and in the chunk
-  // requested beyond the wave's last one) repeat the list's last key with an occupancy word of zero -- a
+  // requested beyond the wave's last one) repeat the list's last key and score -inf -- a
   // listed key's rows are valid addresses, and with probabilities of exactly zero its finite V contributes
   // nothing.  (The loop only runs when the list is not empty.)
   const uint32_t my_row = (uint32_t)(lane >> 3), my_slot = (uint32_t)(lane & 7);
@@ -177,15 +211,17 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
     const int kk = first_key(i) + ql;
     const uint32_t pos = (uint32_t)(list_begin + min(kk, list_len - 1)) * 4u;
     const uint32_t at = (uint32_t)(uintptr_t)(PIT_LDS char*)&s_list[wv][slot][0];
-    if (lane < KC) {
-      dma4(idx, pos, at);
-      dma4(bits, pos, at + KC * 4);
-    }
+    if (lane < KC) dma4(idx, pos, at);
   };
-  // (after the entries have landed) positions past the end of the list get an occupancy word of zero
-  auto key_finish = [&](int i, int slot) {
-    if (!(i < my_chunks && first_key(i) + ql < list_len)) s_list[wv][slot][KC + ql] = 0u;
-    __builtin_amdgcn_wave_barrier();
+  // The occupancy word of a key has a bit per query = per lane of its half of the wave, so two of a chunk's words side by side
+  // are the lane mask of an accumulator register: they are loaded into scalar registers, one chunk ahead.  (Beyond the
+  // end of the list there are other words of the workspace; the scores there are replaced.)
+  u32x16_t bw[2];
+  auto bits_request = [&](int i) {
+    typedef const u32x16_t __attribute__((address_space(4), aligned(4)))* words_t;
+    const int at = __builtin_amdgcn_readfirstlane(list_begin + first_key(min(i, my_chunks - 1)));
+    const words_t p = (words_t)(uintptr_t)(bits + at);
+    bw[0] = p[0]; bw[1] = p[1];
   };
   // byte offset of this lane's row of the key tile, instruction `it` (tile rows 8 it + lane / 8)
   auto row_offsets = [&](int slot, uint32_t (&ro)[4]) {
@@ -215,8 +251,13 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
     key_request(0, 0);
     key_request(1, 1);
     wait_loads();
-    key_finish(0, 0);
-    key_finish(1, 1);
+  }
+  // (the compiler is to wait for the loads of Q here, on every path: left to its own it waits for them at their first use
+  // inside the loop, in every turn, and with them for all that was requested since)
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(qf[ks].x), "+v"(qf[ks].y), "+v"(qf[ks].z), "+v"(qf[ks].w));
+  if (my_chunks > 0) {
+    bits_request(0);
     row_offsets(0, ro);
     request_v(ro, v_lds0);
     request_k(ro);
@@ -226,7 +267,6 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   auto step = [&](int i, int vb) __attribute__((always_inline)) {
     const uint32_t v_lds = v_lds0 + (uint32_t)vb * V_TILE_BYTES;
     wait_loads();                            // everything requested so far has landed
-    key_finish(i + 1, vb ^ 1);
     row_offsets(vb ^ 1, ro);
     wait_lds();                              // (the other V tile was read by the previous chunk)
     request_v(ro, v_lds0 + (uint32_t)(vb ^ 1) * V_TILE_BYTES);
@@ -238,41 +278,47 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
       ka[ks] = *(PIT_LDS u32x4_t*)(uintptr_t)(k_lds + (uint32_t)(ql * 128 + (((2 * ks + h) ^ ((ql >> 1) & 7)) << 4)));
-    u32x4_t bwv[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      bwv[g] = *(PIT_LDS u32x4_t*)(uintptr_t)((uint32_t)(uintptr_t)(PIT_LDS char*)&s_list[wv][vb][KC + g * 8 + h * 4]);
-    wait_lds();                              // the K tile and this chunk's occupancy words are in registers:
-    request_k(ro);                           // the tile takes the next chunk's rows, the slot the list entries
-    key_request(i + 2, vb);                  // of the chunk after it
+    wait_lds();                              // the K tile is in registers: it takes the next chunk's rows, the slot the
+    request_k(ro);                           // list entries of the chunk after it
+    key_request(i + 2, vb);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) st = mfma_in<BF>(__builtin_bit_cast(uint4, ka[ks]), qf[ks], st);
     {
       // st[j] = S^T[key 8*(j/4) + 4*h + j%4][query ql]
-      float mx = -INFINITY;
+      if (scale_first) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+        for (int e = 0; e < 16; ++e) st[e] *= first_scale;
+      }
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const bool on = (bwv[g][e] >> ql) & 1u;
-          const float sc = on ? st[g * 4 + e] * scale_log2e : -INFINITY;
-          st[g * 4 + e] = sc;
-          mx = fmaxf(mx, sc);
+          const uint64_t on = (uint64_t)bw[g >> 1][(g & 1) * 8 + e] | ((uint64_t)bw[g >> 1][(g & 1) * 8 + 4 + e] << 32);
+          st[4 * g + e] = __builtin_amdgcn_inverse_ballot_w64(on) ? st[4 * g + e] : -INFINITY;
         }
+      const int left = list_len - first_key(i);          // keys of the list from this chunk on
+      if (left < KC) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) st[4 * g + e] = 8 * g + 4 * h + e < left ? st[4 * g + e] : -INFINITY;
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      bits_request(i + 1);
+      float mx = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, st[e]);
+      mx = max_halves(mx);
       const float m_new = fmaxf(m_run, mx);
       const float m_safe = m_new == -INFINITY ? 0.f : m_new;
       // (the arguments are <= 0 or -inf: the bare hardware exp2 needs no range handling here)
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_safe) * scale);
       float psum = 0.f;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const float pe = __builtin_amdgcn_exp2f(st[e] - m_safe);
+        const float pe = __builtin_amdgcn_exp2f((st[e] - m_safe) * scale);
         st[e] = pe;
         psum += pe;
       }
-      psum += __shfl_xor(psum, 32);
       l_run = l_run * alpha + psum;
       // the running output is rescaled only when some query's maximum moved (alpha == 1 otherwise)
       if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0ull) {
@@ -338,6 +384,8 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
   // partial result to the others
   wait_loads();
   wait_lds();
+  l_run = add_halves(l_run);
+  if (NW == 2) l_first = add_halves(l_first);
 
   // merge the chains' partial (m, l, O) per lane in their order.  Four waves: wave 0 finishes.  Two waves: wave w finishes the
   // 32 columns d = 32 w .. of O, each with the other's partial results for them.
@@ -356,7 +404,7 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
     const float m_all = fmaxf(fmaxf(m_c[0], m_c[1]), fmaxf(m_c[2], m_c[3]));
     const float m_safe = m_all == -INFINITY ? 0.f : m_all;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) a_c[c] = exp2f(m_c[c] - m_safe);
+    for (int c = 0; c < 4; ++c) a_c[c] = exp2f((m_c[c] - m_safe) * scale);
     // (fmaf: the same roundings whatever the compiler would contract)
     const float l_all = fmaf(l_c[3], a_c[3], fmaf(l_c[2], a_c[2], fmaf(l_c[0], a_c[0], l_c[1] * a_c[1])));
 #pragma unroll

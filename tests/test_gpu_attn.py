@@ -214,3 +214,23 @@ def test_a_head_does_not_depend_on_the_others(pit, kind, in_dtype):
     if in_dtype == torch.float16 and kind == "full":
         O = run(H, V_inf, torch.float32)[:4].cpu().numpy()
         assert np.all(O[1, :, 3] == np.inf) and np.all(O[2, :, 40] == -np.inf)
+
+
+@pytest.mark.parametrize("scale", [-0.125, 0.0, 1e-30, 1.5])
+@pytest.mark.parametrize("in_dtype", [torch.bfloat16, torch.float16])
+def test_scales_and_lists_that_end_inside_a_chunk(pit, scale, in_dtype):
+    """The scale is applied to differences from the largest score (a negative one through the signs of Q, zero beforehand);
+    lists of 1 to 70 keys end at every kind of place in a chunk of 32, with other lists' words behind them."""
+    S = 160
+    w = wl.sparse_attn(H=2, S=S, seed=11)
+    mask = np.zeros((S, S), dtype=np.uint8)
+    for b, n in enumerate((1, 31, 33, 64, 70)):                  # keys listed by the blocks of 32 queries
+        mask[32 * b:32 * (b + 1), np.random.default_rng(b).permutation(S)[:n]] = 1
+    mask[40, :] = 0                                              # a query without a key
+    Q, K, V = (to_dev(x).to(in_dtype) for x in (w.Q, w.K, w.V))
+    O = pit.pit_sparse_attn(Q, K, V, to_dev(mask), scale)
+    torch.cuda.synchronize()
+    ref = orc.sparse_attn(Q.double().cpu().numpy(), K.double().cpu().numpy(), V.double().cpu().numpy(), mask, scale)
+    # fp16 inputs: probabilities have 11 bits (2^-12 of each at most, so of the row); bf16 inputs: 17 bits
+    tol = 2.0 ** -11 if in_dtype == torch.float16 else 2.0 ** -15
+    assert np.abs(O.cpu().numpy() - ref).max() <= tol * np.abs(ref).max()
