@@ -37,6 +37,10 @@ k_gather_m_ring(const GemmArgs g) {
   constexpr int KS = 32, NST = 2;
   constexpr int A_BYTES = TR * KS * 2, NA = A_BYTES / 1024, NB = LB::LOADS, LOADS = NA + NB, STAGE = A_BYTES + LB::BYTES;
   constexpr int FA = TR / 16, FB = TC / 16;
+  // A B per segment: eight chains of additions whatever the number of waves, chain c with the steps c, c + 8, .. (four waves have
+  // two each).  Four chains round a sum of 2048 - 4096 products 1.08 - 1.19 times as much.
+  constexpr int CH = (MODE == SEGMENTS || MODE == ROUTE) && NW == 4 ? 2 : 1;
+  static_assert(CH == 1 || NST == 2, "a step's stage and chain");
   constexpr int RING = NW * NST * STAGE, PART = TR * TC * 4;
   __shared__ __attribute__((aligned(1024))) char smem[RING > NW * PART ? RING : NW * PART];
   constexpr int MW = (TR + 31) / 32;                       // SLABS: words of the rows listed for a slab
@@ -230,16 +234,18 @@ k_gather_m_ring(const GemmArgs g) {
       fr.b[c] = u32x4_t{lo.x, lo.y, hi.x, hi.y};
     }
   };
-  f32x4_t acc[FB][FA];
+  f32x4_t acc[CH][FB][FA];                                 // chain x of a wave: its steps x, x + CH, ..
 #pragma unroll
-  for (int i = 0; i < FB; ++i)
-#pragma unroll
-    for (int j = 0; j < FA; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  auto mfmas = [&](const Frags& fr) {
+  for (int x = 0; x < CH; ++x)
 #pragma unroll
     for (int i = 0; i < FB; ++i)
 #pragma unroll
-      for (int j = 0; j < FA; ++j) acc[i][j] = mfma16r<BF>(fr.b[i], fr.a[j], acc[i][j]);
+      for (int j = 0; j < FA; ++j) acc[x][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto mfmas = [&](const Frags& fr, f32x4_t (&to)[FB][FA]) {
+#pragma unroll
+    for (int i = 0; i < FB; ++i)
+#pragma unroll
+      for (int j = 0; j < FA; ++j) to[i][j] = mfma16r<BF>(fr.b[i], fr.a[j], to[i][j]);
   };
   if (n_w > 0) {
 #pragma unroll
@@ -278,7 +284,7 @@ k_gather_m_ring(const GemmArgs g) {
         issue_a(t + u + 2, u);
         issue_b(t + u + 2, u);
         mask_rows(t + u, fr);
-        mfmas(fr);
+        mfmas(fr, acc[u % CH]);
         PIT_WAIT_VMCNT(LOADS);
       }
     }
@@ -290,7 +296,8 @@ k_gather_m_ring(const GemmArgs g) {
         issue_b(t + 2, t & 1);
       }
       mask_rows(t, fr);
-      mfmas(fr);
+      if (CH == 2 && (t & 1)) mfmas(fr, acc[CH - 1]);
+      else mfmas(fr, acc[0]);
       if (t + 2 < n_w) PIT_WAIT_VMCNT(LOADS);
       else PIT_WAIT_VMCNT(0);
     }
@@ -304,12 +311,12 @@ k_gather_m_ring(const GemmArgs g) {
 #pragma unroll
         for (int j = 0; j < FA; ++j)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) big = fmaf(acc[i][j][e], 0.f, big);    // 0 or a NaN
+          for (int e = 0; e < 4; ++e) big = fmaf(acc[0][i][j][e], 0.f, big);    // 0 or a NaN
       if (__any(big != 0.f)) {
 #pragma unroll
         for (int i = 0; i < FB; ++i)
 #pragma unroll
-          for (int j = 0; j < FA; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+          for (int j = 0; j < FA; ++j) acc[0][i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
         for (t = 0; t < n_w; ++t) {
           issue_a(t, 0);
@@ -324,7 +331,7 @@ k_gather_m_ring(const GemmArgs g) {
             for (int i = 0; i < FB; ++i) {
               const f32x4_t p = mfma16r<BF>(fr.b[i], fr.a[j], f32x4_t{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-              for (int e = 0; e < 4; ++e) acc[i][j][e] = on ? acc[i][j][e] + p[e] : acc[i][j][e];
+              for (int e = 0; e < 4; ++e) acc[0][i][j][e] = on ? acc[0][i][j][e] + p[e] : acc[0][i][j][e];
             }
           }
         }
@@ -332,12 +339,24 @@ k_gather_m_ring(const GemmArgs g) {
     }
   }
 
+  auto leave = [&](const f32x4_t (&from)[FB][FA], int slot) {          // a chain's partial tile -> LDS
+#pragma unroll
+    for (int i = 0; i < FB; ++i)
+#pragma unroll
+      for (int j = 0; j < FA; ++j)
+        *(PIT_LDS f32x4_t*)(uintptr_t)(lds0 + (uint32_t)(slot * PART) + partial_place<TC, FA>(16 * j + (lane & 15), 4 * i + (lane >> 4))) = from[i][j];
+  };
+  // a partial tile per chain, or, where they don't fit into the rings' place, per wave
+  constexpr int TILES = CH * NW * PART <= RING ? CH : 1;
+  if constexpr (TILES < CH) {
+#pragma unroll
+    for (int i = 0; i < FB; ++i)
+#pragma unroll
+      for (int j = 0; j < FA; ++j) acc[0][i][j] += acc[1][i][j];
+  }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < FB; ++i)
-#pragma unroll
-    for (int j = 0; j < FA; ++j)
-      *(PIT_LDS f32x4_t*)(uintptr_t)(lds0 + (uint32_t)(wv * PART) + partial_place<TC, FA>(16 * j + (lane & 15), 4 * i + (lane >> 4))) = acc[i][j];
+  for (int x = 0; x < TILES; ++x) leave(acc[x], x * NW + wv);
   constexpr int VPR = TC / 4, VECS = TR * VPR, PER = (VECS + 64 * NW - 1) / (64 * NW);
   int crow[PER];
   float scale[PER];
@@ -356,12 +375,12 @@ k_gather_m_ring(const GemmArgs g) {
     const int x = tid + 64 * NW * v, m = x / VPR, c = x % VPR;
     if (crow[v] < 0 || x >= VECS) continue;
     const uint32_t at = lds0 + partial_place<TC, FA>(m, c);
-    f32x4_t part[NW];
+    f32x4_t part[TILES * NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) part[w] = *(PIT_LDS f32x4_t*)(uintptr_t)(at + (uint32_t)(w * PART));
+    for (int w = 0; w < TILES * NW; ++w) part[w] = *(PIT_LDS f32x4_t*)(uintptr_t)(at + (uint32_t)(w * PART));
     f32x4_t s = part[0];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) s += part[w];
+    for (int w = 1; w < TILES * NW; ++w) s += part[w];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       if constexpr (EPI == EPI_GELU) s[e] = gelu_erf_fast(s[e]);
@@ -464,7 +483,8 @@ RingMTile ring_m_tile(int epi, const GemmArgs& g, int64_t total_rows) {
   const double wide = (rows / 128 + hit) * (g.N / 256.0) / (2 * cus);
   if (per > 150) return wide <= 0.16 ? RINGM_64x64 : RINGM_NONE;
   const int R = per <= 12 ? 16 : 32;
-  if ((rows / R + hit) * (g.N / 64) * (R + 64) * 2.0 * g.slab > 500e6) return RINGM_NONE;
+  const bool few = std::min(rows, hit + (double)(total_rows / 16)) * (g.N / 64) <= 2 * cus && (g.N >= 512 || per <= 16) && hit * g.N * g.slab * 2.0 <= 200e6;
+  if (!few && (rows / R + hit) * (g.N / 64) * (R + 64) * 2.0 * g.slab > 500e6) return RINGM_NONE;
   if (wide > (per <= 16 ? 1.17 : per <= 64 ? 0.94 : 0.22)) return RINGM_NONE;
   return R == 16 ? RINGM_16x64 : RINGM_32x64;
 }

@@ -172,6 +172,49 @@ def test_many_rows_per_expert_in_tiles_of_few(pit, T, d_model, d_ff, E, route):
     assert np.array_equal(Y.double().cpu().numpy(), ref)
 
 
+# calls whose products (the letters; - is one by the general kernel) are tiles of few rows: both ways of finding the rows, four waves
+# and eight, and a k so long that the tiles read more than 500 MB
+CHAINS = [(48, 768, 3072, 64, "cc"), (200, 384, 768, 64, "CC"), (500, 384, 512, 32, "DD"), (64, 512, 4096, 1, "da"), (1008, 512, 512, 2, "EE"),
+          (300, 512, 512, 16, "BB"), (521, 512, 14848, 8, "-D")]
+
+
+@pytest.mark.parametrize("T,d_model,d_ff,E,tiles", CHAINS)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_eight_chains_of_additions_along_k(pit, T, d_model, d_ff, E, tiles, dtype):
+    """Steps of 32 along k go to eight chains of additions in turn, whatever the tile.  A column holds 2^24 in step a, one in step b
+    of a + 1 .. a + 7 and -2^24 in step a + 8: one chain for a and b, or fewer than eight, and the one is lost (2^24 + 1 is
+    2^24 in fp32)."""
+    g = np.random.default_rng(T + d_ff)
+
+    def column_sums(K, N):                                # [K, N], to be multiplied by rows of 2^12
+        n = np.arange(N)
+        a = g.integers(0, K // 32 - 8, size=N)
+        w = np.zeros((K, N), dtype=np.float32)
+        i = g.integers(0, 32, size=N)
+        w[32 * a + i, n], w[32 * (a + 8) + i, n] = 4096.0, -4096.0
+        w[32 * (a + 1 + n % 7) + g.integers(0, 32, size=N), n] = 2.0 ** -12
+        return torch.from_numpy(w).to(dtype).cuda()
+
+    eid = torch.arange(T, dtype=torch.int32, device="cuda") % E
+    X = torch.zeros((T, d_model), dtype=dtype, device="cuda")
+    W1, W2 = (torch.zeros((E, a, b), dtype=dtype, device="cuda") for a, b in ((d_model, d_ff), (d_ff, d_model)))
+    call = lambda: pit.pit_moe_dispatch_gemm(X, eid, None, W1, W2, act=1)
+    X[:, 5] = 1.0                                         # the second product: hidden rows of 2^12
+    W1[:, 5] = 4096.0
+    W2[:] = column_sums(d_ff, d_model)
+    assert bool((call() == 1.0).all())
+    if tiles[0] != "-":                                   # the first: its results are copied
+        X[:] = 4096.0
+        W1[:] = column_sums(d_model, d_ff)
+        W2[:] = 0.0
+        n = torch.arange(d_model, device="cuda")
+        W2[:, (n * 37 + 11) % d_ff, n] = 1.0
+        assert bool((call() == 1.0).all())
+    names = kernels(call, "k_gather_m", 2)
+    if names and torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert all(t in ("-", letter(n)) for t, n in zip(tiles, names)), names
+
+
 @pytest.mark.parametrize("T,d_model,d_ff,E", [(2000, 256, 256, 4), (4096, 256, 2048, 16), (8000, 384, 640, 8), (700, 256, 1024, 128)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 def test_general_kernel_gelu_and_gate(pit, T, d_model, d_ff, E, dtype):
