@@ -303,8 +303,9 @@ k_gather_m_ring(const GemmArgs g) {
     }
     if constexpr (MODE == SLABS) {
       // An infinity or a NaN in B must not reach the rows that are not listed.  It reaches all rows of its column here (0 x inf is a
-      // NaN), so sums that are all finite met none; otherwise the wave takes its steps again, each into registers of its own,
-      // and adds the listed rows' results.
+      // NaN), so sums that are all finite met none; otherwise the wave takes its steps again and keeps each one's results for the
+      // rows that it lists.  The others keep what they had, which is what adding zeros gives: the same roundings both times, so
+      // sums that meet no infinity have the same bits whether another one does or not.
       float big = 0.f;
 #pragma unroll
       for (int i = 0; i < FB; ++i)
@@ -329,9 +330,9 @@ k_gather_m_ring(const GemmArgs g) {
             const bool on = listed(t, j);
 #pragma unroll
             for (int i = 0; i < FB; ++i) {
-              const f32x4_t p = mfma16r<BF>(fr.b[i], fr.a[j], f32x4_t{0.f, 0.f, 0.f, 0.f});
+              const f32x4_t p = mfma16r<BF>(fr.b[i], fr.a[j], acc[0][i][j]);
 #pragma unroll
-              for (int e = 0; e < 4; ++e) acc[0][i][j][e] = on ? acc[0][i][j][e] + p[e] : acc[0][i][j][e];
+              for (int e = 0; e < 4; ++e) acc[0][i][j][e] = on ? p[e] : acc[0][i][j][e];
             }
           }
         }

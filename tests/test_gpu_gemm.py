@@ -590,6 +590,31 @@ def test_microtile_few_tiles(pit, shape, dtype):
                              else SLABS_FEW[shape] % "true, 0, 0" if "ring" in SLABS_FEW[shape] else "k_slab_strip") in names[0], names
 
 
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("shape", SLABS_FEW)
+def test_microtile_infinities_leave_the_other_sums_alone(pit, shape, dtype):
+    """The order of additions depends on the shape only: an infinity or a NaN, in B or in a listed row of A, changes no bit of the
+    sums it has no part in."""
+    M, K, N, mt = shape
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    keep = torch.rand((M, K // mt), generator=g, device="cuda") < 0.4
+    A = (torch.randn((M, K), generator=g, device="cuda") * keep.repeat_interleave(mt, dim=1)).to(dtype)
+    B = torch.randn((K, N), generator=g, device="cuda").to(dtype)
+    ix = pit.pit_build_index(A, 1, mt, 0)
+    product = lambda: pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, A, B, ix, mt, M, N, K)
+    before = product()
+    part = torch.zeros((M, N), dtype=torch.bool, device="cuda")
+    for k, n, v in ((K - 1, 3, np.inf), (mt * (K // mt // 2), N - 1, np.nan), (0, 64, -np.inf), (K // 3, 65, np.inf)):
+        B[k, n] = v
+        part[:, n] |= keep[:, k // mt]
+    r = int(torch.nonzero(keep[:, 1])[-1])
+    A[r, mt] = np.inf
+    part[r] = True
+    after = product()
+    assert bool(torch.isfinite(before).all()) and not bool(torch.isfinite(after[part]).any())
+    assert torch.equal(torch.where(part, 0.0, after), torch.where(part, 0.0, before))
+
+
 @pytest.mark.parametrize("M,K,N,mt,p", [(1024, 4096, 1024, 64, 0.5), (2048, 1600, 512, 64, 0.4)])
 def test_microtile_few_tiles_rounds_no_more_than_strips(pit, M, K, N, mt, p):
     """Against 64 bits: the four or eight waves' chains against the four chains of the 32-row strips (the same product with so many
