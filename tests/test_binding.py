@@ -1,4 +1,8 @@
 """The native binding answers as the general path through ctypes does: the same refusals (no GPU needed), the same results."""
+import os
+import shutil
+import subprocess
+import sys
 import types
 
 import pytest
@@ -67,6 +71,38 @@ def test_the_same_refusals(monkeypatch):
         seen.add(native[0])
         n += 1
     assert n > 500 and {"PitError", "AssertionError", "AttributeError", "KeyError"} <= seen
+
+
+@pytest.mark.parametrize("native,says", [(None, "cannot import name"), (b"not a library", "file too short")])
+def test_the_package_loads_without_the_native_module(tmp_path, native, says):
+    """The ctypes path needs the library alone: without the module, or with one that does not load, calls take that path and a
+    warning says what the loader said."""
+    here = os.path.dirname(os.path.abspath(pit.__file__))
+    to = tmp_path / "paper_2301_10936_amd"
+    to.mkdir()
+    for name in ("__init__.py", "pit.py", "libpit_hip.so"):
+        shutil.copy(os.path.join(here, name), to / name)
+    if native is not None:
+        (to / "_pit_native.so").write_bytes(native)
+    code = """if True:
+        import warnings
+        with warnings.catch_warnings(record=True) as seen:
+            warnings.simplefilter("always")
+            from paper_2301_10936_amd import pit
+        import torch
+        print(pit.__file__, [str(w.message) for w in seen if "native binding" in str(w.message)])
+        print(pit.pit_select_kernel([{"mt_rows": 1, "mt_cols": 128, "tile_cost": 1.0}], [[1]], [[2]]))
+        pit._stream = lambda: 0
+        ix = pit.PitIndex(torch.zeros(3, dtype=torch.int32), torch.zeros(8, dtype=torch.int32), None, 2, 8)
+        try:
+            pit.pit_build_index(torch.zeros((4, 256), dtype=torch.bfloat16), 1, 100, 0, out=ix, ws=torch.zeros(64, dtype=torch.uint8))
+        except pit.PitError as e:
+            print(e)
+    """
+    p = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, env={**os.environ, "PYTHONPATH": str(tmp_path)}, capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stderr
+    assert str(tmp_path) in p.stdout and "(0, [1.0])" in p.stdout and "pit_build_index: PIT_ESHAPE" in p.stdout
+    assert says in p.stdout, p.stdout
 
 
 @pytest.mark.gpu
