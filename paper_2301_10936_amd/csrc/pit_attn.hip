@@ -168,15 +168,16 @@ k_sparse_attn(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, co
     qf[ks] = *reinterpret_cast<const uint4*>(Q + head_off + (int64_t)(qb * QB + ql) * HD + ks * 16 + h * 8);
 
   // Scores are scaled inside the exponent, exp2(scale (s - max s)): exactly 1 at the largest, and a small difference times the scale
-  // has less to round than a score times the scale.  That wants scale > 0: a negative one changes the signs of Q instead (exact); with zero, an
-  // infinity or NaN the scores are scaled beforehand.
+  // has less to round than a score times the scale.  That wants scale > 0: a negative one changes the signs of Q instead (exact).  With zero,
+  // an infinity or NaN the scores are scaled beforehand, and below 2^-100: the difference of two finite scores can be an infinity, which is
+  // no other result only where 2^128 times the scale leaves nothing of exp2.
   float scale = scale_log2e;
   if (scale < 0.f) {
     scale = -scale;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) { qf[ks].x ^= 0x80008000u; qf[ks].y ^= 0x80008000u; qf[ks].z ^= 0x80008000u; qf[ks].w ^= 0x80008000u; }
   }
-  const bool scale_first = !(scale > 0.f && scale < INFINITY);
+  const bool scale_first = !(scale >= 0x1p-100f && scale < INFINITY);
   const float first_scale = scale;
   if (scale_first) scale = 1.f;
 

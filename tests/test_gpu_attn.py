@@ -234,3 +234,23 @@ def test_scales_and_lists_that_end_inside_a_chunk(pit, scale, in_dtype):
     # fp16 inputs: probabilities have 11 bits (2^-12 of each at most, so of the row); bf16 inputs: 17 bits
     tol = 2.0 ** -11 if in_dtype == torch.float16 else 2.0 ** -15
     assert np.abs(O.cpu().numpy() - ref).max() <= tol * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("scale", [1e-38, -1e-38])
+@pytest.mark.parametrize("H,S", [(2, 64), (4, 6208)])
+def test_finite_scores_whose_difference_is_not(pit, H, S, scale):
+    """Scores of +-2.25e38 with a scale that leaves differences of up to 4.5 of them: the difference of two is beyond fp32.  (Blocks of
+    four waves, and of two between three and four blocks per compute unit.)"""
+    if S > 64 and not 3 < H * S / 32 / torch.cuda.get_device_properties(0).multi_processor_count <= 4:
+        pytest.skip("sizes for 256 compute units")
+    g = torch.Generator(device="cuda").manual_seed(S)
+    Q, K = (torch.zeros((H, S, 64), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    Q[:, :, 9] = 1.5e19
+    K[:, :, 9] = 1.5e19 * (1.0 - (torch.arange(S, device="cuda") % 9) / 4.0)
+    V = torch.randn((H, S, 64), generator=g, device="cuda").to(torch.bfloat16)
+    mask = torch.zeros((S, S), dtype=torch.uint8, device="cuda")
+    mask[:, :64] = 1
+    O = pit.pit_sparse_attn(Q, K, V, mask, scale)
+    w = torch.softmax(scale * (Q[:, :1, 9].double() * K[:, :64, 9].double()), dim=1)
+    ref = (w[:, :, None] * V[:, :64].double()).sum(dim=1, keepdim=True)
+    assert float((O - ref).abs().max()) <= 2.0 ** -15 * float(ref.abs().max())
