@@ -41,6 +41,7 @@ k_gather_m_ring(const GemmArgs g) {
   // two each).  Four chains round a sum of 2048 - 4096 products 1.08 - 1.19 times as much.
   constexpr int CH = (MODE == SEGMENTS || MODE == ROUTE) && NW == 4 ? 2 : 1;
   static_assert(CH == 1 || NST == 2, "a step's stage and chain");
+  static_assert(MODE != ROUTE || TR < 64, "lane 63 holds no row's token");
   constexpr int RING = NW * NST * STAGE, PART = TR * TC * 4;
   __shared__ __attribute__((aligned(1024))) char smem[RING > NW * PART ? RING : NW * PART];
   constexpr int MW = (TR + 31) / 32;                       // SLABS: words of the rows listed for a slab
@@ -419,7 +420,9 @@ int launch_mode(const GemmArgs& g, int64_t total_rows, RingMTile tile, hipStream
       case RINGM_16x64: return launch_tile<BF, EPI, CT, 16, 64, 4, MODE>(g, total_rows, st);
       case RINGM_16x64_8: return launch_tile<BF, EPI, CT, 16, 64, 8, MODE>(g, total_rows, st);
       case RINGM_32x64: return launch_tile<BF, EPI, CT, 32, 64, 4, MODE>(g, total_rows, st);
-      case RINGM_64x64: return launch_tile<BF, EPI, CT, 64, 64, 4, MODE>(g, total_rows, st);
+      case RINGM_64x64:                                    // (more than 150 rows per segment: never ROUTE)
+        if constexpr (MODE == SEGMENTS) return launch_tile<BF, EPI, CT, 64, 64, 4, MODE>(g, total_rows, st);
+        return PIT_EINVAL;
       default: return PIT_EINVAL;
     }
   }

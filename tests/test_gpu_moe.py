@@ -215,6 +215,53 @@ def test_eight_chains_of_additions_along_k(pit, T, d_model, d_ff, E, tiles, dtyp
         assert all(t in ("-", letter(n)) for t, n in zip(tiles, names)), names
 
 
+def _exact(pit, T, d_model, d_ff, E, eids, dtype, tiles):
+    """A call without an activation on whole numbers, its results against 64 bits, tokens without an expert among them."""
+    g = torch.Generator(device="cuda").manual_seed(T + d_ff + E)
+    draw = lambda *shape: torch.randint(-1, 2, shape, generator=g, device="cuda", dtype=torch.int8)
+    X = (draw(T, d_model) * (torch.rand((T, d_model), generator=g, device="cuda") < 0.2)).to(dtype)     # |hidden| <= 128: exact
+    W1, W2 = draw(E, d_model, d_ff).to(dtype), draw(E, d_ff, d_model).to(dtype)
+    for eid in eids:
+        eid = torch.from_numpy(np.asarray(eid).astype(np.int32)).cuda()
+        status, Y = torch.full((1,), -1, dtype=torch.int32, device="cuda"), torch.full((T, d_model), 5.0, device="cuda")
+        call = lambda: pit.pit_moe_dispatch_gemm(X, eid, None, W1, W2, out=Y, act=1, status=status)
+        call()
+        live = (eid >= 0) & (eid < E)
+        assert int(status[0]) == int((~live).sum())
+        ref = torch.zeros((T, d_model), dtype=torch.float64, device="cuda")
+        for e in torch.unique(eid[live]).tolist():
+            rows = eid == e
+            hidden = X[rows].double() @ W1[e].double()
+            assert float(hidden.abs().max()) <= 256
+            ref[rows] = hidden @ W2[e].double()
+        assert torch.equal(Y.double(), ref)
+    names = kernels(call, "k_gather_m", 2)
+    if names and torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert "".join(letter(n) for n in names) == tiles, names
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("T,E,tiles", [(64, 1, "da"), (64, 4, "da"), (49, 2, "da"), (64, 3, "da")])
+def test_few_tokens_in_tiles_of_32_rows(pit, T, E, tiles, dtype):
+    """No index and 32 rows a tile: experts with 1, 31, 32, 33 and all rows, tokens in order and shuffled, ids out of range."""
+    rng = np.random.default_rng(T + E)
+    ones = lambda n: np.where(np.arange(T) < n, 0, E - 1)
+    lost = rng.integers(0, E, size=T)
+    lost[[0, 31, 32, T - 1]] = [-1, E, -2**31, 2**31 - 1]
+    eids = [np.zeros(T), *(rng.permutation(ones(n)) for n in (1, 31, 32, 33)), ones(32), lost, np.full(T, -1), rng.integers(0, E, size=T)]
+    _exact(pit, T, 128, 6144 if E == 3 else 4096, E, eids, dtype, tiles)
+
+
+@pytest.mark.parametrize("T,tiles", [(70, "BB"), (300, "CC"), (3000, "CC")])
+def test_more_than_64_experts_per_lane(pit, T, tiles):
+    """5000 experts: a lane of the search for a tile's expert counts 79, which are looked at 64 at a time.  Few of them, at the ends of a
+    lane's and of its first 64; all tokens on one lane's; any."""
+    rng = np.random.default_rng(T)
+    ends = np.array([0, 63, 64, 78, 79, 142, 143, 157, 4095, 4096, 4977, 4998, 4999])
+    _exact(pit, T, 128, 128, 5000, [ends[rng.integers(len(ends), size=T)], rng.integers(79 * 40, 79 * 41, size=T), rng.integers(-1, 5001, size=T)],
+           torch.bfloat16, tiles)
+
+
 @pytest.mark.parametrize("T,d_model,d_ff,E", [(2000, 256, 256, 4), (4096, 256, 2048, 16), (8000, 384, 640, 8), (700, 256, 1024, 128)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 def test_general_kernel_gelu_and_gate(pit, T, d_model, d_ff, E, dtype):
