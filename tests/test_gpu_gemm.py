@@ -291,6 +291,60 @@ def test_gather_k_few_tiles_large_last_row_and_rounding(pit, shape):
     assert float((C - ref).norm() / ref.norm()) <= 1.1e-7
 
 
+# the forms of k_gather_k_direct with the K from which on k_gather_k_ring leaves them a product: (waves per tile, rows of a tile) and
+# (M, K, N, mt) on 256 compute units
+DIRECT = {(4, 32): (1024, 300, 1024, 32), (4, 64): (1152, 1100, 1024, 64), (4, 64, 128): (1152, 1100, 1024, 128)}
+
+
+@pytest.mark.parametrize("in_dtype,c_dtype", [(torch.bfloat16, torch.float32), (torch.bfloat16, torch.bfloat16),
+                                              (torch.float16, torch.float32), (torch.float16, torch.float16)])
+@pytest.mark.parametrize("form", DIRECT)
+def test_gather_k_direct_four_waves_every_length(pit, form, in_dtype, c_dtype):
+    """Lists of every length around the boundaries of the slabs of four waves, pitches beyond the rows (NaN there), a sentinel beyond the
+    result.  Exact on integers (16-bit results: the rounded exact sum).  The dense mode on the same operands, too."""
+    M, K, N, mt = DIRECT[form]
+    lengths = [0, 1, 2, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 161, 193, 224, 255, 257, 300]
+    g = np.random.default_rng(M + N + mt)
+    Xt = np.zeros((K, M), dtype=np.float32)
+    for s in range(M // mt):
+        rows = g.choice(K, size=lengths[(5 * s + 3) % len(lengths)], replace=False)
+        Xt[rows, mt * s:mt * (s + 1)] = g.integers(-2, 3, size=(len(rows), mt))
+        Xt[rows, mt * s] = 1.0                                            # keep the listed rows non-zero
+    W = g.integers(-2, 3, size=(K, N)).astype(np.float32)
+    ref = torch.from_numpy(Xt.T.astype(np.float64) @ W.astype(np.float64)).to(c_dtype)
+    bigX, bigW = (torch.full((K, n), float("nan"), dtype=in_dtype, device=dev()) for n in (M + 64, N + 128))
+    bigX[:, :M] = torch.from_numpy(Xt).to(in_dtype)
+    bigW[:, :N] = torch.from_numpy(W).to(in_dtype)
+    X, B = bigX[:, :M], bigW[:, :N]
+    ix = pit.pit_build_index(X, 1, mt, 0)
+    for mode, index in ((pit.PIT_GEMM_GATHER_K, ix), (pit.PIT_GEMM_DENSE_K, None)):
+        C = torch.full((M, N + 32), 9.0, dtype=c_dtype, device=dev())
+        pit.pit_sread_gemm(mode, X, B, index, mt, M, N, K, out=C[:, :N])
+        torch.cuda.synchronize()
+        assert torch.equal(C[:, :N].cpu(), ref), mode
+        assert bool((C[:, N:] == 9.0).all())
+
+
+@pytest.mark.parametrize("form", list(DIRECT) + [f for f in FORMS if f not in ((4, 32), (4, 64))])
+def test_gather_k_direct_large_last_row_and_kernel(pit, form):
+    """The last listed row holds the largest finite values, or an infinity: positions past the end of a list re-read it and must add
+    nothing.  And the form that the product takes, those of test_gather_k_every_form among them."""
+    M, K, N, mt = DIRECT[form] if form in DIRECT else (FORMS[form][0], 203, *FORMS[form][1:])
+    g = torch.Generator(device="cuda").manual_seed(M)
+    for last in (3.0e38, float("inf")):
+        X = torch.randint(-2, 3, (K, M), generator=g, device="cuda").float() * (torch.rand((K, M), generator=g, device="cuda") < 0.3)
+        X[K - 1] = last
+        W = torch.randint(-2, 3, (K, N), generator=g, device="cuda").float()
+        W[K - 1] = 1.0
+        X, W = X.to(torch.bfloat16), W.to(torch.bfloat16)
+        ix = pit.pit_build_index(X, 1, mt, 0)
+        C = pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_K, X, W, ix, mt, M, N, K)
+        assert torch.equal(C, X[K - 1].float()[:, None].expand(M, N))      # the other rows' sums are far below half a unit
+    names = kernels(lambda: pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_K, X, W, ix, mt, M, N, K), "k_gather_k", 1)
+    if names and torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert f"k_gather_k_direct<true, 0, {form[0]}, {form[1] // 16}" in names[0], names
+
+
 @pytest.mark.parametrize("M,K,mt", [(4224, 1300, 32), (8448, 1300, 64)])
 def test_gather_k_one_wave_rounds_no_more_than_two(pit, M, K, mt):
     """From eight tiles per compute unit on a wave works alone on a tile.  It adds in two chains, like the two waves that
