@@ -767,6 +767,71 @@ def test_microtile_long_lists_many_slabs(pit, M, K, N, mt, p):
     assert np.array_equal(C.cpu().numpy().astype(np.float64), orc.gemm(w.A, w.B))
 
 
+# products that the 32-row strips take (on 256 compute units): slabs of 32, 64, 96 and 128; 126 and 65 slabs, and more than the masks of
+# the kernel for few tiles hold; lists of up to 6000 rows (two rounds of the 64-ary search), of every row and of none; last strips of 1,
+# 8, 24, 28 and 32 rows
+STRIPS = [(488, 4032, 2816, 32, 0.02), (96, 32 * 600, 128, 32, 0.3), (33, 128 * 520, 128, 128, 0.3), (6300, 2080, 256, 32, 0.7),
+          (6300, 192, 256, 64, 0.95), (4161, 384, 512, 128, 0.5), (3000, 288, 512, 96, 0.3), (1500, 128, 1152, 64, 1.0), (1500, 384, 1152, 128, 0.0)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("M,K,N,mt,p", STRIPS)
+def test_microtile_strips(pit, M, K, N, mt, p, dtype):
+    """Exact on integers, pitches beyond the rows with NaN beyond the operands and a sentinel beyond the result, the same bits twice."""
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    keep = torch.rand((M, K // mt), generator=g, device="cuda") < p
+    ints = lambda *s: torch.randint(-4, 5, s, generator=g, device="cuda", dtype=torch.int8)
+    a, b = ints(M, K) * keep.repeat_interleave(mt, dim=1), ints(K, N)
+    bigA, bigB = (torch.full(s, float("nan"), dtype=dtype, device=dev()) for s in ((M, K + 64), (K, N + 128)))
+    bigA[:, :K], bigB[:, :N] = a.to(dtype), b.to(dtype)
+    ix = pit.pit_build_index(bigA[:, :K], 1, mt, 0)
+    ref = a.double() @ b.double()
+    assert float(ref.abs().max()) < 2.0 ** 24
+
+    def product():
+        C = torch.full((M, N + 32), -7.0, device=dev())
+        pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, bigA[:, :K], bigB[:, :N], ix, mt, M, N, K, out=C[:, :N])
+        assert bool((C[:, N:] == -7.0).all())
+        return C[:, :N].double()
+
+    assert torch.equal(product(), ref) and torch.equal(product(), ref)
+    names = kernels(product, "k_", 1)
+    if names and torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert "k_slab_strip<" in names[0], names
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("M,K,N,mt", [(488, 4032, 2816, 32), (1500, 256, 1152, 64), (1700, 512, 1024, 128)])
+def test_microtile_strips_clustered(pit, M, K, N, mt, dtype):
+    """Long runs in some strips, none in most, a slab that lists nothing, the last row everywhere: the 32-row strips on the cases of
+    the tall ones."""
+    test_microtile_tall_strips_clustered_strided_reproducible(pit, M, K, N, mt, dtype)
+
+
+@pytest.mark.parametrize("M,K,N,mt,p", [(2048, 2080, 1024, 32, 0.5), (2048, 2048, 2048, 64, 0.5),        # strips of 64 rows
+                                        (4096, 2080, 4096, 32, 0.5), (4096, 2080, 4096, 32, 0.1),       # of 128 rows, 32 k
+                                        (3456, 2048, 2176, 64, 0.5), (3456, 2048, 2176, 64, 0.1), (3456, 2048, 2176, 128, 0.2)])
+def test_microtile_tall_strips_round_no_more_than_low_ones(pit, M, K, N, mt, p):
+    """A product that fills the chip with tall strips and slices of it that the 32-row strips take, four chains of additions each: the
+    error of the whole result against 64 bits is no larger (an estimate over millions of elements: 1 %)."""
+    w = wl.microtile_gemm(M=M, K=K, N=N, mt_k=mt, p_keep=p, seed=mt)
+    A, B = to_dev(w.A), to_dev(w.B)
+    ix = pit.pit_build_index(A, 1, mt, 0)
+    run = lambda b: pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, A, b, ix, mt, M, b.shape[1], K)
+    ref = A.double() @ B.double()
+    width = 640 if M == 2048 else 384                   # 160 - 224 strips of 64 rows
+    starts = list(range(0, N - width, width)) + [N - width]
+    tall = (run(B) - ref).norm()
+    low = torch.empty_like(ref)
+    for n in starts:
+        low[:, n:n + width] = run(B[:, n:n + width])
+    low = (low - ref).norm()
+    assert tall <= 1.01 * low, (float(tall / ref.norm()), float(low / ref.norm()))
+    names = kernels(lambda: run(B[:, :width]), "k_", 1), kernels(lambda: run(B), "k_", 1)
+    if all(names) and torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert "k_slab_strip<" in names[0][0] and "k_slab_strip_tall<" in names[1][0], names
+
+
 def test_microtile_clustered_rows(pit):
     """Live micro-tiles bunched in a few row ranges: long runs of listed rows in some strips, none in
     most, and lists whose first entry lies far above the first strips."""
