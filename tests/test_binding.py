@@ -139,3 +139,60 @@ def test_the_same_results(monkeypatch):
     monkeypatch.setattr(pit, "_native", types.SimpleNamespace(**{n: lambda *a: None for n in NAMES}))
     got = everything(lambda t: t)
     assert all(torch.equal(a, b) if isinstance(a, torch.Tensor) else a == b for a, b in zip(native, got))
+
+
+class Recorder:
+    """_native with what each call of it answered"""
+    def __init__(self, native):
+        self.answers = []
+        for n in NAMES:
+            setattr(self, n, lambda *a, f=getattr(native, n): self.answers.append(f(*a)) or self.answers[-1])
+
+
+def _refused(wrap, dev="cpu"):
+    """One call of each function that ends at the library's own checks."""
+    z = lambda *s, dtype=torch.bfloat16: torch.zeros(s, dtype=dtype, device=dev)
+    i32 = lambda n: torch.zeros(n, dtype=torch.int32, device=dev)
+    ix = pit.PitIndex(i32(3), i32(1024), None, 2, 1024)
+    X, W, C, ws = wrap(z(512, 256)), z(512, 100), z(256, 128, dtype=torch.float32), z(4096, dtype=torch.uint8)
+    yield lambda: pit.pit_build_index(X, 1, 100, 0, out=ix, ws=ws)
+    yield lambda: pit.pit_relu_channel_major_index(wrap(z(512, 100)), out_xt=z(100, 512), out=ix, ws=ws)
+    yield lambda: pit.pit_sread_gemm(1, X, W, ix, 128, 256, 100, 512, out=C)
+    yield lambda: pit.pit_select_and_run_gemm([{"mt_rows": 1, "mt_cols": 100, "tile_cost": 1.0}], [[1]], [[2]], X, W, 256, 100, 512, out=C, ws=ws)
+    yield lambda: pit.pit_moe_dispatch_gemm(X, i32(512), None, z(2, 256, 100), z(2, 100, 256), out=C, ws=ws)
+    yield lambda: pit.pit_sparse_attn(wrap(z(2, 256, 48)), z(2, 256, 48), z(2, 256, 48), z(256, 256, dtype=torch.uint8), 1.0, out=C, ws=ws)
+
+
+def test_ordinary_calls_are_answered_natively(monkeypatch):
+    """An ordinary call gets the library's status from the native side; a subclass of Tensor gets None there and the same refusal from the
+    general path.  (Without a native binding every call would pass the tests of equal results.)"""
+    monkeypatch.setattr(pit, "_stream", lambda: 0)
+    for wrap, native in ((lambda t: t, True), (torch.nn.Parameter, True), (lambda t: t.as_subclass(Sub), False)):
+        for name, call in zip(NAMES, _refused(wrap)):
+            with monkeypatch.context() as m:
+                rec = Recorder(pit._native)
+                m.setattr(pit, "_native", rec)
+                with pytest.raises(pit.PitError):
+                    call()
+            assert len(rec.answers) == 1, name
+            status = rec.answers[0][0] if isinstance(rec.answers[0], tuple) else rec.answers[0]
+            assert (status in (pit.PIT_EINVAL, pit.PIT_ESHAPE, pit.PIT_ECAPACITY)) if native else status is None, (name, rec.answers)
+
+
+@pytest.mark.gpu
+def test_ordinary_calls_are_answered_natively_on_the_device(monkeypatch):
+    """The handle of the current stream is what the native side takes, and each function answers PIT_OK."""
+    z = lambda *s, dtype=torch.bfloat16: torch.zeros(s, dtype=dtype, device="cuda")
+    ix, ws = pit.PitIndex(z(3, dtype=torch.int32), z(1024, dtype=torch.int32), None, 2, 1024), z(1 << 22, dtype=torch.uint8)
+    X, W, C = z(512, 256), z(512, 128), z(256, 128, dtype=torch.float32)
+    cands = [{"mt_rows": 1, "mt_cols": 128, "tile_cost": 1.0}]
+    rec = Recorder(pit._native)
+    monkeypatch.setattr(pit, "_native", rec)
+    pit.pit_build_index(X, 1, 128, 0, out=ix, ws=ws)
+    pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_K, X, W, ix, 128, 256, 128, 512, out=C)
+    pit.pit_relu_channel_major_index(z(256, 512), out_xt=X, out=ix, ws=ws)
+    pit.pit_select_and_run_gemm(cands, [[900]], [[1024]], X, W, 256, 128, 512, out=C, ws=ws)
+    pit.pit_moe_dispatch_gemm(z(96, 128), z(96, dtype=torch.int32), None, z(4, 128, 256), z(4, 256, 128), out=z(96, 128, dtype=torch.float32), ws=ws)
+    pit.pit_sparse_attn(z(2, 256, 64), z(2, 256, 64), z(2, 256, 64), z(256, 256, dtype=torch.uint8), 0.125, out=z(2, 256, 64, dtype=torch.float32), ws=ws)
+    torch.cuda.synchronize()
+    assert rec.answers == [0, 0, 0, (0, 0), 0, 0]
