@@ -254,3 +254,30 @@ def test_finite_scores_whose_difference_is_not(pit, H, S, scale):
     w = torch.softmax(scale * (Q[:, :1, 9].double() * K[:, :64, 9].double()), dim=1)
     ref = (w[:, :, None] * V[:, :64].double()).sum(dim=1, keepdim=True)
     assert float((O - ref).abs().max()) <= 2.0 ** -15 * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("scale", [-0.125, 0.0, 0.125])
+@pytest.mark.parametrize("in_dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("H,S", [(2, 160), (16, 1600)])
+@pytest.mark.parametrize("at", [0, 1])
+def test_lists_with_set_bits_behind_their_ends(pit, H, S, in_dtype, scale, at):
+    """A workspace of ones: each word that is read past the end of a list has all its bits set (a mask at an even address: a
+    list per S words), or it is another list's (at an odd one: the lists side by side).  Four waves per block, and two (800 blocks
+    on 256 compute units); scales that take the signs of Q and the scores scaled beforehand in both."""
+    w = wl.sparse_attn(H=H, S=S, seed=11)
+    mask = np.zeros((S, S), dtype=np.uint8)
+    for b in range(S // 32):                                     # keys listed by the blocks of 32 queries
+        keys = np.random.default_rng(b).permutation(S)[:(1, 31, 33, 64, 70)[b % 5]]
+        mask[32 * b:32 * (b + 1), keys] = 1
+    mask[40, :] = 0                                              # a query without a key
+    mask[50, np.nonzero(mask[50])[0][1:]] = 0                    # and one with one
+    Q, K, V = (to_dev(x).to(in_dtype) for x in (w.Q, w.K, w.V))
+    buf = torch.zeros(S * S + 16, dtype=torch.uint8, device=dev())
+    tm = buf[at:at + S * S].view(S, S)
+    tm.copy_(to_dev(mask))
+    ws = torch.full((pit.pit_sparse_attn_workspace(H, S, 64),), 255, dtype=torch.uint8, device=dev())
+    O = pit.pit_sparse_attn(Q, K, V, tm, scale, out=torch.full((H, S, 64), 9.0, device=dev()), ws=ws)
+    ref = orc.sparse_attn(Q.double().cpu().numpy(), K.double().cpu().numpy(), V.double().cpu().numpy(), mask, scale)
+    # fp16 inputs: probabilities have 11 bits (2^-12 of each at most, so of the row); bf16 inputs: 17 bits
+    tol = 2.0 ** -11 if in_dtype == torch.float16 else 2.0 ** -15
+    assert np.abs(O.cpu().numpy() - ref).max() <= tol * np.abs(ref).max()
