@@ -289,18 +289,20 @@ k_gather_m_ring(const GemmArgs g) {
         PIT_WAIT_VMCNT(LOADS);
       }
     }
-    for (; t < n_w; ++t) {
-      read_frags(t & 1, fr);
-      if (t + 2 < n_w) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        issue_a(t + 2, t & 1);
-        issue_b(t + 2, t & 1);
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {                          // the last three steps at most
+      if (t + u < n_w) {
+        read_frags(u & 1, fr);
+        if (u == 0 && t + 2 < n_w) {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          issue_a(t + 2, 0);
+          issue_b(t + 2, 0);
+        }
+        mask_rows(t + u, fr);
+        mfmas(fr, acc[u % CH]);
+        if (u == 0 && t + 2 < n_w) PIT_WAIT_VMCNT(LOADS);
+        else PIT_WAIT_VMCNT(0);
       }
-      mask_rows(t, fr);
-      if (CH == 2 && (t & 1)) mfmas(fr, acc[CH - 1]);
-      else mfmas(fr, acc[0]);
-      if (t + 2 < n_w) PIT_WAIT_VMCNT(LOADS);
-      else PIT_WAIT_VMCNT(0);
     }
     if constexpr (MODE == SLABS) {
       // An infinity or a NaN in B must not reach the rows that are not listed.  It reaches all rows of its column here (0 x inf is a
