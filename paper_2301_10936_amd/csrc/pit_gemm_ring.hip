@@ -38,14 +38,18 @@ k_gather_k_ring(const GemmArgs g, const int tm_tiles) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // tiles in the order of k_gather_k_direct: a contiguous run per XCD, in bands of 4 tile columns x all tile rows
+  // tiles in the order of k_gather_k_direct: a contiguous run per XCD, in bands of 4 tile columns x all tile rows.  8 where there
+  // are two workgroups per compute unit, as wide as that kernel's bands: each band reads A again, and an operand that the launch before
+  // wrote does not come from this XCD's L2.  The producer and 3328 x 768 x 384: 18.9 us by that kernel, 20.9 in bands of 4, 19.2 of 8;
+  // 64 products of 264 - 512 tiles behind the producer 0.99 of its time in bands of 4, the slowest 1.17, and 0.97 of 8 (1.03).  With one workgroup per
+  // compute unit 4 is better for 32 x 64 (the index and 512 x 11160 x 512: 1.24 times as long in bands of 8) and the same for 64 x 64.
   const int tn = g.N / TB, total = tn * tm_tiles;
   const bool wide = tn > 2 * tm_tiles;
   int row, n0;
   {
     const int lin = blockIdx.x, x = lin & 7, rr = total & 7;
     const int lp = x * (total >> 3) + min(x, rr) + (lin >> 3);
-    constexpr int G = 4;
+    constexpr int G = NW == 4 ? 8 : 4;
     const int across = wide ? tn : tm_tiles, along = wide ? tm_tiles : tn;
     const int band = lp / (G * across), within = lp - band * (G * across), n = min(G, along - band * G);
     const int thin = band * G + within % n, len = within / n;
