@@ -277,6 +277,55 @@ k_gather_m_ring(const GemmArgs g) {
     else PIT_WAIT_VMCNT(0);
     Frags fr;
     int t = 0;
+    if constexpr (MODE == SLABS) {
+      // Steps whose slab lists no row of the tile would add zeros.  Where an eighth of them or more do, the wave takes the first two, which
+      // are under way, and those that list a row (bits of `rest`; the lanes look at a step each).  Index and product, us, all steps / those,
+      // 1 % kept: 1050 x 1952 x 1536, 1 x 32 27.3 / 22.5, 775 x 3584 x 768, 1 x 128 25.7 / 21.9.  A loop over such steps in every case takes longer
+      // where few are left out: 1024^3, 1 x 32, 10 % kept 16.8 / 17.5.
+      uint32_t any = 0u;
+#pragma unroll
+      for (int w = 0; w < MW; ++w) any |= lane < n_w ? s_mask[slab_of(lane) * MW + w] : 0u;
+      uint64_t rest = __ballot(any != 0u) & ~3ull;
+      if (n_w <= 64 && 8 * (__builtin_popcountll(rest) + 2) <= 7 * n_w) {
+        auto next = [&]() -> int {                         // n_w: none
+          if (rest == 0ull) return n_w;
+          const int step = __builtin_ctzll(rest);
+          rest &= rest - 1ull;
+          return step;
+        };
+        int s[2] = {0, 1}, ahead[2] = {next(), next()};    // in the stages; the steps after those
+        for (; ahead[1] < n_w; ahead[0] = next(), ahead[1] = next()) {
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            read_frags(u, fr);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            issue_a(ahead[u], u);
+            issue_b(ahead[u], u);
+            mask_rows(s[u], fr);
+            mfmas(fr, acc[0]);
+            PIT_WAIT_VMCNT(LOADS);
+            s[u] = ahead[u];
+          }
+        }
+        const bool third = ahead[0] < n_w;
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+          if (u < 2 || third) {                            // (n_w >= 3 here)
+            read_frags(u & 1, fr);
+            if (u == 0 && third) {
+              asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+              issue_a(ahead[0], 0);
+              issue_b(ahead[0], 0);
+            }
+            mask_rows(u == 2 ? ahead[0] : s[u], fr);
+            mfmas(fr, acc[0]);
+            if (u == 0 && third) PIT_WAIT_VMCNT(LOADS);
+            else PIT_WAIT_VMCNT(0);
+          }
+        }
+        t = n_w;
+      }
+    }
     for (; t + 3 < n_w; t += 2) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -508,11 +557,12 @@ bool gather_m_routes(const GemmArgs& g) {
 //   327 x 3648 x 256, 1 x 64 (30 %, 24 tiles of 64 x 64) 24.5 / 12.0, 13.9, 17.2, 14.2;  930 x 2496 x 256, 1 x 64 (6 %, 60) 17.7 / 9.9, 9.9, 13.7, 11.9
 //   538 x 1984 x 768, 1 x 64 (10 %, 108) 13.9 / 11.5, 9.4, 11.3, 11.0;  401 x 832 x 1408, 1 x 64 (46 %, 154) 11.8 / 14.7, 15.0, 8.9, 8.7
 //   1024^3, 1 x 32 (10 %, 256) 12.2 / 17.5, 15.3, 9.4, 9.7;  1229 x 3072 x 512, 1 x 32 (8 %, 160) 29.4 / 31.5, 30.4, 22.0, 19.6
-// The line is at one workgroup of 64 x 64 per compute unit: beyond it the strips are ahead where few rows are listed (2097 x 1216 x 512,
-// 1 x 64, 1 %, 264 tiles: 10.0 / 11.2 by four waves; 755 x 3456 x 1536, 1 x 128, 11 %, 288: 22.9 / 25.2), but for the 32-wide slabs that cost them most
-// (1669 x 1984 x 640, 16 %, 270: 24.6 / 19.5; 321 x 1568 x 3456, 4 %, 324: 21.2 / 14.8; 2295 x 1504 x 768, 7 %, 432: 20.9 / 17.3; not with a long
-// k: 488 x 4032 x 2816, 2 %, 352: 28.2 / 34.3).  Up to it, 40 products of 300 - 4096 x 512 - 4096 x 256 - 4096: 0.77, the slowest 1.07 (1529 x 512 x 384, 1 x
-// 128, 2 %).
+// (Those times are without the steps left out in the kernel.)  The line is at one workgroup of 64 x 64 per compute unit: beyond it the
+// strips are ahead where few rows are listed (2097 x 1216 x 512, 1 x 64, 1 %, 264 tiles: 10.0 / 11.2 by four waves; 755 x 3456 x 1536, 1 x 128,
+// 11 %, 288: 22.9 / 25.2), but for the 32-wide slabs that cost them most (1669 x 1984 x 640, 16 %, 270: 24.6 / 19.5; 321 x 1568 x 3456, 4 %, 324: 21.2 /
+// 14.8; 2295 x 1504 x 768, 7 %, 432: 20.9 / 17.3; not with a long k: 488 x 4032 x 2816, 2 %, 352: 28.2 / 34.3).  Index and product of 100
+// drawn calls, 300 - 4096 x 512 - 4096 x 256 - 4096, 1 - 50 % kept, against strips in all of them: 0.92, none more than 2 % slower; the slowest looked for, at 1 %
+// and slabs of 128: 775 x 3584 x 768 20.0 / 21.8, 1529 x 512 x 384 12.9 / 13.4.
 RingMTile ring_slab_tile(const GemmArgs& g) {
   const int64_t cus = compute_units(), t64 = ceil_div(g.M, 64) * (g.N / 64);
   if (g.nseg > SLABS_MAX || g.K > (1 << 16)) return RINGM_NONE;

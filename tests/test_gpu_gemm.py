@@ -669,6 +669,38 @@ def test_microtile_infinities_leave_the_other_sums_alone(pit, shape, dtype):
     assert torch.equal(torch.where(part, 0.0, after), torch.where(part, 0.0, before))
 
 
+# (M, K, N, mt) with 2 - 9, 16, 64 and 72 steps per wave in each tile of the kernel for few tiles
+SLABS_SPARSE = [(70, 2080, 128, 32), (40, 16384, 128, 128), (40, 18432, 128, 64), (500, 1152, 1024, 128), (1000, 384, 1024, 96), (4100, 320, 128, 64),
+                (900, 2112, 1024, 64), (1000, 2048, 1024, 32)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("M,K,N,mt", SLABS_SPARSE)
+def test_microtile_steps_that_list_no_row(pit, M, K, N, mt, dtype):
+    """Waves that leave out the steps whose slab lists no row of the tile: none listed, the first slab alone, the last, the last two, every fifth,
+    two in three, all but one, single rows of few tiles.  NaN in A where nothing is listed, an infinity in the rows of B of slabs that
+    list nothing anywhere.  Exact on integers."""
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    nseg = K // mt
+    ints = lambda *s: torch.randint(-2, 3, s, generator=g, device="cuda", dtype=torch.int8)
+    a, b = ints(M, K), ints(K, N)
+    slab = torch.arange(nseg, device="cuda")
+    rows = (torch.rand((M, nseg), generator=g, device="cuda") < 0.3) | (torch.arange(M, device="cuda") % 32 == 31)[:, None]
+    single = torch.rand((M, nseg), generator=g, device="cuda") < 0.5 / 64
+    for keep in (rows & (slab < 0), rows & (slab == 0), rows & (slab == nseg - 1), rows & (slab >= nseg - 2), rows & (slab % 5 == 3), rows & (slab % 3 > 0),
+                 rows & (slab != nseg // 2), single):
+        on = keep.repeat_interleave(mt, dim=1)
+        A = torch.where(on, a.float(), torch.where(torch.rand((M, K), generator=g, device="cuda") < 0.1, float("nan"), a.float())).to(dtype)
+        B = b.to(dtype)
+        B[~keep.any(dim=0).repeat_interleave(mt), :] = float("inf")
+        seg = torch.cat([torch.zeros(1, device="cuda"), keep.sum(dim=0).cumsum(0)]).to(torch.int32)
+        idx = torch.nonzero(keep.t())[:, 1].to(torch.int32)
+        ix = pit.PitIndex(seg, idx if len(idx) else torch.zeros(1, dtype=torch.int32, device="cuda"), None, nseg, len(idx))
+        C = torch.full((M, N), 9.0, device=dev())
+        pit.pit_sread_gemm(pit.PIT_GEMM_GATHER_M, A, B, ix, mt, M, N, K, out=C)
+        assert torch.equal(C.double(), (a * on).double() @ b.double())
+
+
 @pytest.mark.parametrize("M,K,N,mt,p", [(1024, 4096, 1024, 64, 0.5), (2048, 1600, 512, 64, 0.4)])
 def test_microtile_few_tiles_rounds_no_more_than_strips(pit, M, K, N, mt, p):
     """Against 64 bits: the four or eight waves' chains against the four chains of the 32-row strips (the same product with so many
