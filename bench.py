@@ -505,7 +505,7 @@ def bench_microtile(pit, wl, steps, warmup, pool=8):
     alg_bytes = float(ws[0].keep.sum()) * 64 + K * N * 2 + M * N * 4
     return {"sec_per_step": sec, "eff_flops": eff, "dense_ms": dense_ms, "dense_flops": 2.0 * M * K * N,
             "extra": {"gemm_kernel_ms": round(k_s * 1e3, 4),
-                      "roofline": _roofline("hbm", alg_bytes / k_s / 1e9, "k_slab_strip (f16)", "latency-bound at this size: three dependent launches of 3-14 us")}}
+                      "roofline": _roofline("hbm", alg_bytes / k_s / 1e9, "k_gather_m_ring (f16)", "latency-bound at this size: three dependent launches of 3-14 us")}}
 
 
 def bench_moe(pit, wl, steps, warmup, pool=4):

@@ -238,9 +238,10 @@ typedef enum pit_gemm_mode {
    * segments, segment s listing the k whose micro-tile At[k, s*mt .. (s+1)*mt) is non-zero.
    * C[s*mt .. (s+1)*mt, :] = sum over listed k of At[k, rows]^T . B[k, :].  Plain stores; every
    * element of C is written.  mt is 128, 64 or 32: the dense tile is mt rows x 128 columns (paper
-   * Section 3.2: the micro-tile takes the dense tile's extent on the other axes).  A lower tile
-   * follows a finer sparsity pattern -- fewer all-zero micro-tiles are multiplied (Table 3, "sparsity
-   * ratio after cover") -- and reads B once per mt rows of C instead of once per 128; which one is
+   * Section 3.2: the micro-tile takes the dense tile's extent on the other axes), or, where that leaves
+   * compute units idle, 32 or 64 rows of it x 32, 64 or 128 columns; the tiles of a micro-tile row share
+   * its list.  A lower micro-tile follows a finer sparsity pattern -- fewer all-zero micro-tiles are
+   * multiplied (Table 3, "sparsity ratio after cover") -- and B is read once per tile row; which one is
    * cheaper for given data is what pit_select_kernel decides.
    */
   PIT_GEMM_GATHER_K = 1,

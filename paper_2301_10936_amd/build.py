@@ -1,7 +1,7 @@
 """Build the HIP library in-tree:  python -m paper_2301_10936_amd.build
 
 hipcc cross-compiles for gfx950 without a GPU.  The result, libpit_hip.so, sits next to this file
-and is what the ctypes binding loads.
+and is what the binding loads; _pit_native.so beside it is the native part of that binding.
 """
 from __future__ import annotations
 

@@ -9,13 +9,14 @@
 //   SRead   A rows (K-minor) and B rows (K-major) travel global -> LDS directly.  A: 16 listed rows x 64 bytes per instruction,
 //           the 16-byte chunk c of row r at c ^ ((r >> 2) & 3), operands read with ds_read_b128.  B: as in k_gather_k_ring,
 //           operands read with the transposing LDS read.
-//   SWrite  partial tiles added in the order of the waves; rows go where the index says, 16 lanes filling 256 contiguous bytes of
+//   SWrite  partial tiles added in the order of the waves (with a B per segment of eight chains along k); rows go where the index says, 16 lanes filling 256 contiguous bytes of
 //           an fp32 row.  The rows that a list does not name are cleared by the workgroups without a tile, when asked for.
 //   SLABS   micro-tiles along k: the tile's rows are those of C; which of them a slab lists comes as bits in LDS
-//           (build_slab_masks, while the first operands travel), and the A operands of the others are set to zero in registers.
+//           (build_slab_masks, while the first operands travel), and the A operands of the others are set to zero in registers; a wave
+//           that meets many steps without a listed row leaves those out.
 // Product alone, k_gather_m_lds / here, us: 186 rows (140 listed) x 1408 x 384 14.6 / 4.0, 732 (308) x 1920 x 1792 19.0 / 7.8, 2911 x
 // 1408 x 512 14.2 / 7.8.  Whole mixture-of-experts calls, us, before (segments of few rows went to a kernel with the weights in
-// registers) / here: 1 token, 896 x 1792, 8 experts 11.6 / 8.0; 48, 768 x 3072, 64 43.4 / 40; 515, 640 x 1920, 8 31.6 / 21.5.
+// registers) / here: 1 token, 896 x 1792, 8 experts 11.6 / 8.0; 515, 640 x 1920, 8 31.6 / 21.5; 48, 768 x 3072, 64, bound by the memory, 56.2 / 55.2.
 // Tried: four steps per ring (fewer workgroups per compute unit: up to 1.7 times the time), three with 16 x 64 and eight waves (the same).
 #include "pit_ring.hpp"
 #include "pit_gather_m.hpp"
@@ -518,8 +519,9 @@ double hit_segments(const GemmArgs& g, int64_t rows) { return g.nseg * (1.0 - st
 //   wide             per <= 16: up to 1.17 (482, 768 x 1536, 128: 118 / 108);  per <= 64: 0.94 (2595, 512 x 1024, 64: 51.1 / 46.7 and 2916, 512 x 1536, 64
 //                    60.3 / 61.9 at 1.02);  per <= 150: 0.22 (4646, 384 x 1536, 32, first product 44.7 / 51.0 at 0.80, second 44.8 / 44.1)
 //   16 rows a tile up to 12 per segment, else 32: 721, 640 x 1280, 128 (7) 84.1 by 32, 83.0 by 16; 459, 768 x 3072, 16 (29) 51.5, 54.4
-// Over 80 calls of 1 - 8192 tokens, 256 - 1024 wide, 8 - 128 experts: 0.83 of the time before, 4 slower by more than 2 % (the most: 5 %, 152 tokens, 1024 x
-// 4096, 8 experts).
+// Over 120 calls of 1 - 8192 tokens and 120 of 3 - 200, 256 - 1024 wide, 8 - 128 experts: 0.83 and 0.81 of the time before, 4 slower by more than 2 % (1551 tokens, 512 x
+// 1024, 128 experts 59.4 / 62.6; besides 152, 1024 x 4096, 8 36.3 / 37.5 and 24, 1024 x 2048, 128 25.7 / 26.9, which no tile here gives).  Each product of 190 such calls by every tile:
+// the best one every time takes 0.985 of this rule.
 RingMTile ring_m_tile(int epi, const GemmArgs& g, int64_t total_rows) {
   const double cus = compute_units(), rows = (double)total_rows;
   if (g.b_seg_stride == 0) {

@@ -6,8 +6,8 @@ Importing this module raises if the library has not been built -- there is no ot
 
 The calls that a layer makes on every step go through the module _pit_native (csrc/pit_binding.cpp), which reads the tensors
 natively; it answers None for arguments out of the ordinary (subclasses of Tensor, other types, ...), and those take the
-general path through ctypes below it, which accepts or refuses them.  ctypes costs 3 - 4.5 us a call on the host, as much as two
-kernel launches; _pit_native 0.3.  Where _pit_native does not load (not built, or built for another torch or Python) a warning says
+general path through ctypes below it, which accepts or refuses them.  ctypes costs 2.6 - 3.3 us a call on the host, as much as
+a kernel launch or two; _pit_native 0.4, 0.15 of it in the module (calls that the library refuses, the exception taken off).  Where _pit_native does not load (not built, or built for another torch or Python) a warning says
 why and every call takes the general path.
 """
 from __future__ import annotations
@@ -27,7 +27,7 @@ _lib = ctypes.CDLL(LIB_PATH)
 try:
     from . import _pit_native as _native
 except ImportError as e:
-    warnings.warn(f"the native binding does not load ({e}): calls cost 3 - 4.5 us more on the host; build it with "
+    warnings.warn(f"the native binding does not load ({e}): calls cost 2 - 3 us more on the host; build it with "
                   "`python -m paper_2301_10936_amd.build`", RuntimeWarning, stacklevel=2)
 
     class _native:                                   # every argument is out of the ordinary
